@@ -130,9 +130,11 @@ struct KParams {
     double nu_ee;        // binary collisions: rate at relative speed ee_vref (0 = off)
     double ee_vref;
     int32_t binary;      // 1 if the binary-collision kernel runs (nu_ee > 0 and a species takes part)
-    int64_t *ee_tile;    // [tiles] binary-collision pairs scattered in the tile this step
-    uint32_t *ee_ent;    // binary collisions: each tile's participants in cell order (slot | species << 29),
+    uint32_t *ee_ent;    // binary collisions: each tile's participants (slot | species << 29) by block of cells,
                          // the tile's list at the sum over participating species of its bin starts
+    uint32_t *ee_off;    // [tiles][blocks] end of each block's part of the tile's list
+    uint32_t *ee_part;   // [ee_nparts] pairs scattered this step by each workgroup of the binary-collision kernel
+    int32_t ee_nparts;
     // Gauss-law and continuity checks (PIC_FLAG_GAUSS_RESIDUAL only; null otherwise)
     double *rho_tile;    // [tiles][(T+1)^ndim] per-tile charge partials
     double *rho0;        // [cells] charge on the nodes at step 0
@@ -179,10 +181,17 @@ constexpr int kStepKernels = 13;
 constexpr int kKernelGroup[kStepKernels] = {0, 1, 2, 2, 2, 2, 2, 2, 3, 4, 4, 4, 5};
 // A single run's step is kStepKernels launches, plus four with
 // PIC_FLAG_GAUSS_RESIDUAL (the charge deposits and residuals of the Gauss
-// and continuity checks, group 0) and one with binary collisions (group 1).
+// and continuity checks, group 0) and two with binary collisions
+// (group 1).
 // step_kernel_groups fills groups[] with each launch's group and returns the
 // number of launches.
 int step_kernel_groups(const KParams &hp, int *groups);
+// Workgroups per tile of the binary-collision kernel, and the cells each
+// takes, for ppc participants per cell.
+int binary_blocks(bool mixed, int64_t tile_cells, int64_t ppc, int *width);
+// Room for the parameter block in the part of the scratch that a checkpoint
+// holds (the block itself lies behind that part).
+constexpr size_t kCkptParamBytes = 3256;
 // ev: NULL, or 2 * kStepKernels events (start/stop of each dispatch)
 hipError_t launch_step(const KParams &hp, const KParams *dp, hipStream_t s, hipEvent_t *ev = nullptr);
 // Batch step: the particle kernel is one launch per tile group (empty groups

@@ -1357,18 +1357,7 @@ __global__ __launch_bounds__(256) void k_continuity(const KParams *__restrict__ 
 // heavier particle takes its new momentum with probability w_small/w_large
 // (Nanbu and Yonemura 1998).
 //
-// One workgroup per tile.  The tile's participants are counted per cell and
-// put in cell order by a counting sort into a list in scratch memory (store
-// slot and species of each), then handled in ranges of consecutive cells
-// holding at most kBinCap of them: the range's entries go to LDS with the
-// 64-bit key (Philox key << 32 | id), each entry's rank among its cell's
-// entries in key order places it (a rank sort per cell: a cell holds a few
-// hundred participants at most, and the lanes of a wave mostly share one
-// cell, so they read the same keys), and the pairs (a triple counts as one
-// unit, done by one thread in order) are spread over the threads; the
-// momenta are read and written in the particle store in place.
-constexpr int kBinCap = 2048;                       // 4096: 8% slower (LDS: 2 workgroups per CU, not 4)
-
+// A workgroup takes a block of consecutive cells of one tile (see k_binary).
 template <typename R>
 __device__ __forceinline__ void boost_frame(const R (&bv)[3], R b2, R gc, R sign, R &e, R (&p)[3])
 {
@@ -1383,10 +1372,13 @@ __device__ __forceinline__ void boost_frame(const R (&bv)[3], R b2, R gc, R sign
 
 // One pair (a first).  Returns true if the pair scattered; ua, ub hold the
 // momenta (gamma v / c) of the particles that take their new momenta.
-template <typename R>
+// UNIT: both masses are 1 (electrons); the products and quotients with them
+// are left out.
+template <typename R, bool UNIT>
 __device__ bool binary_pair(R (&ua)[3], R ma, R wa, uint32_t ida, R (&ub)[3], R mb, R wb, R f, uint32_t step,
                             uint32_t seed0, uint32_t seed1, uint32_t run, R cee)
 {
+    if constexpr (UNIT) ma = mb = R(1);
     const R ga = sqrt(R(1) + ua[0] * ua[0] + ua[1] * ua[1] + ua[2] * ua[2]);
     const R gb = sqrt(R(1) + ub[0] * ub[0] + ub[1] * ub[1] + ub[2] * ub[2]);
     R dv[3];
@@ -1461,215 +1453,423 @@ __device__ bool binary_pair(R (&ua)[3], R ma, R wa, uint32_t ida, R (&ub)[3], R 
     return true;
 }
 
-constexpr int kBinThreads = 512;
+// Work split of the binary collisions.  A tile's particles lie in its bin in
+// no particular order, so whoever handles a cell has to find that cell's
+// particles first, and a gather of u and id by slot in cell order costs one
+// cache-line access per word (at C3 that was 7.6 of 11.9 ms).  So a workgroup
+// takes a block of `width` consecutive cells.  k_binary_list (one workgroup
+// per tile) first sorts the tile's slots by block, keeping them nearly in
+// slot order inside a block, so that k_binary's reads of id and u go through
+// ascending slots, several words of each line, and so does the write-back.
+// Everything in between happens in LDS: the participants are ordered within
+// their cells by a counting sort over kBinBuckets buckets of (cell, leading
+// bits of the key) -- about two buckets per participant, so a bucket holds one
+// or two entries and the rank inside it is a compare or two -- and the pairs
+// read and write the momenta there.  The width is chosen on the host so that
+// the block's nominal load is 80% of the LDS capacity; a block that outgrows
+// it (the beam filaments) is taken in halves that fit.
+//   capacity: entries of 30 (FP32) / 42 (FP64) bytes; two workgroups of 512
+//   threads per CU in FP32, one of 1024 in FP64 (160 KB of LDS per CU)
+// Measured on 1024^2 cells x 128 participants in mixed precision (67M pairs a
+// step): 11.9 -> 4.2 ms, and 0.4 ms for the list (floor of its bytes: 1.1 ms).
+// What bounds it now: VALU issue about 60% of the time (trigonometry,
+// divisions and the Philox rounds of the pairs), then the waits at the
+// barriers between the phases.  Tried and left out: every block scanning the
+// whole tile's cells instead of the list (7.3 ms, half of it the scan), the
+// three pairs of a triple done by one lane at once (a third more).
+constexpr int kBinLimit = 2048;                     // participants of one cell
+constexpr int kBinBuckets = 4096;
+constexpr int kBinMaxWidth = 512;                   // cells per block
+template <typename R> constexpr int kBinCap = sizeof(R) == 4 ? 2176 : 3072;
+template <typename R> constexpr int kBinThreads = sizeof(R) == 4 ? 512 : 1024;
+constexpr int kBinListThreads = 512;
 
-template <typename R, int D, int T>
-__global__ __launch_bounds__(kBinThreads) void k_binary(const KParams *__restrict__ kp)
+// Exclusive prefix over the workgroup's threads (at most 1024); *total: the sum.
+__device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t *swave, uint32_t *total)
 {
-    constexpr int TC = D == 3 ? T * T * T : T * T;      // cells of the tile
-    constexpr uint32_t kSlotMask = (1u << 29) - 1u;
-    __shared__ uint32_t s_cnt[TC];                       // participants per cell, then fill cursors
-    __shared__ uint32_t s_off[TC + 1];                   // tile-wide exclusive prefix of the counts
-    __shared__ uint32_t s_unit[TC + 1];                  // prefix of the work units of the range's cells
-    __shared__ uint64_t s_k64[kBinCap];                  // sort key of each entry: Philox key << 32 | id
-    __shared__ uint32_t s_ent[kBinCap];                  // slot | species << 29 of each entry
-    __shared__ uint16_t s_cell[kBinCap];                 // cell (in the range) of each entry
-    __shared__ uint16_t s_idx[kBinCap];                  // entry at each sorted position
-    __shared__ uint32_t s_range[2];
-    __shared__ uint32_t s_pairs;
-    const DevState *st = kp->state;
-    DevState *stw = kp->state;
-    if (st->fatal & 4) return;                           // the store was not re-laid out
-    const uint32_t step = (uint32_t)st->step;
-    const int par = st->rebin ? st->par : st->par ^ 1;   // where this step's particles now are
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t t = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += t;
+    }
+    __syncthreads();
+    if (lane == 63) swave[wave] = inc;
+    __syncthreads();
+    uint32_t off = 0, tot = 0;
+    for (int w = 0; w < nw; ++w) {
+        const uint32_t x = swave[w];
+        off += w < wave ? x : 0u;
+        tot += x;
+    }
+    *total = tot;
+    return off + inc - v;
+}
+
+// Cell within its tile of the particle in `slot`, T^D if it lies outside.
+template <typename R, int D, int T>
+__device__ __forceinline__ uint32_t bin_cell(const SpeciesDev &S, int par, uint32_t slot, const int (&t0)[3])
+{
+    if constexpr (sizeof(R) == 4) {
+        return ld(gbl((const uint16_t *)S.cell[par]), slot);
+    } else {
+        uint32_t l = 0;
+        bool inside = true;
+#pragma unroll
+        for (int a = D - 1; a >= 0; --a) {
+            const int c = (int)floor(ld(gbl((const double *)S.pos[par][a]), slot)) - t0[a];
+            inside = inside && c >= 0 && c < T;
+            l = l * T + (uint32_t)c;
+        }
+        return inside ? l : (uint32_t)(D == 3 ? T * T * T : T * T);
+    }
+}
+
+// First list entry of a tile: the sum of the participating species' bin
+// starts (bins are laid out in tile order in every species, so the lists of
+// different tiles do not overlap).
+__device__ __forceinline__ uint64_t bin_list_base(const KParams *__restrict__ kp, int tile)
+{
+    uint64_t base = 0;
+    for (int s = 0; s < kp->nspecies; ++s)
+        if (kp->sp[s].binary) base += (uint64_t)kp->sp[s].start[tile];
+    return base;
+}
+
+// The tile's participants by block of cells (cell / width, inv = ceil(2^22 /
+// width)): ee_ent from the tile's first entry on, ee_off[tile][block] the end
+// of each block's part.  HBM-bound: the cell read twice (2 bytes; FP64: the
+// positions), the entry written once.
+template <typename R, int D, int T>
+__global__ __launch_bounds__(kBinListThreads) void k_binary_list(const KParams *__restrict__ kp, uint32_t inv, int nblk)
+{
+    constexpr uint32_t TC = D == 3 ? T * T * T : T * T;
+    constexpr int NT = kBinListThreads;
+    __shared__ uint32_t s_cnt[TC];
+    __shared__ uint32_t s_wave[NT / 64];
+    DevState *state = kp->state;
+    if (state->fatal & 4) return;                        // the store was not re-laid out
+    const int par = uniform_par(kp) ^ (wave_uniform(state->rebin) ? 0 : 1);   // where this step's particles now are
     const int tile = blockIdx.x, ntiles = kp->g.ntiles;
     const int ntx = kp->g.nt[0], nty = kp->g.nt[1];
     const int t0[3] = {(tile % ntx) * T, ((tile / ntx) % nty) * T, (tile / (ntx * nty)) * T};
+    GLB uint32_t *list = gbl(kp->ee_ent + bin_list_base(kp, tile));
+    auto each = [&](auto &&f) {
+        for (int s = 0; s < kp->nspecies; ++s) {
+            const SpeciesDev &S = kp->sp[s];
+            if (!S.binary) continue;
+            const uint32_t nf = S.cnt_front[par * ntiles + tile], nb = S.cnt_back[par * ntiles + tile];
+            const uint32_t b0 = (uint32_t)S.start[tile], b1 = b0 + (uint32_t)S.cap[tile];
+            // four particles of a thread are loaded before the first is used
+            for (uint32_t k0 = threadIdx.x; k0 < nf + nb; k0 += 4 * NT) {
+                uint32_t c[4], slot[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t k = k0 + j * NT;
+                    slot[j] = k < nf ? b0 + k : b1 - nb + (k - nf);
+                    c[j] = TC;
+                    if (k < nf + nb) c[j] = bin_cell<R, D, T>(S, par, slot[j], t0);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (k0 + j * NT < nf + nb) f(s, slot[j], c[j]);
+            }
+        }
+    };
+    for (int i = threadIdx.x; i < nblk; i += NT) s_cnt[i] = 0;
+    __syncthreads();
+    each([&](int, uint32_t, uint32_t c) {
+        if (c >= TC) atomicOr(&state->fatal, 8);
+        else atomicAdd(&s_cnt[(c * inv) >> 22], 1u);
+    });
+    __syncthreads();
+    {
+        constexpr int PER = ((int)TC + NT - 1) / NT;     // nblk <= TC
+        uint32_t v[PER], sum = 0, tot;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int i = threadIdx.x * PER + j;
+            v[j] = i < nblk ? s_cnt[i] : 0u;
+            sum += v[j];
+        }
+        uint32_t run = block_excl(sum, s_wave, &tot);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int i = threadIdx.x * PER + j;
+            if (i < nblk) {
+                s_cnt[i] = run;
+                run += v[j];
+                kp->ee_off[(size_t)tile * nblk + i] = run;
+            }
+        }
+    }
+    __syncthreads();
+    each([&](int s, uint32_t slot, uint32_t c) {
+        if (c < TC) list[atomicAdd(&s_cnt[(c * inv) >> 22], 1u)] = slot | ((uint32_t)s << 29);
+    });
+}
+
+template <typename R, int D, int T, bool UNIT>
+__global__ __launch_bounds__(kBinThreads<R>) void k_binary(const KParams *__restrict__ kp, int width, int nblk)
+{
+    constexpr int TC = D == 3 ? T * T * T : T * T;      // cells of the tile
+    constexpr int NT = kBinThreads<R>;
+    constexpr uint32_t CAP = kBinCap<R>;
+    constexpr uint32_t kSlotMask = (1u << 29) - 1u;
+    constexpr int HW = kBinBuckets / 2;                  // bucket counters, two per word
+    constexpr uint16_t kEmpty = 0xFFFFu, kTriple = 0x8000u;
+    static_assert(CAP >= kBinLimit && CAP < 0x8000u, "a full cell fits, entries leave the mark's bit free");
+    static_assert(HW % NT == 0 && kBinMaxWidth <= NT, "counters and cells per thread");
+    __shared__ uint32_t s_ent[CAP];                      // slot | species << 29, in scan order
+    __shared__ uint32_t s_key[CAP];                      // Philox key
+    __shared__ uint32_t s_id[CAP];
+    __shared__ R s_u[3][CAP];
+    __shared__ uint16_t s_cell[CAP];                     // cell within the range
+    __shared__ uint16_t s_perm[CAP];                     // entries in bucket order
+    __shared__ uint16_t s_idx[CAP + kBinMaxWidth + 1];   // entries in pairing order, every cell at an even place
+    __shared__ uint32_t s_hist[HW];                      // bucket counts, then ends
+    __shared__ uint16_t s_pad[kBinMaxWidth];             // first place of each cell in s_idx
+    __shared__ uint32_t s_wave[NT / 64];
+    __shared__ R s_m[kMaxSpecies], s_w[kMaxSpecies];
+    __shared__ const void *s_ptr[kMaxSpecies][5];        // id, u and cell (FP32) arrays of the set in use
+    __shared__ uint16_t s_tri[kBinMaxWidth];             // places of the triples
+    __shared__ uint32_t s_n, s_ntri, s_pairs;
+    DevState *state = kp->state;
+    if (state->fatal & 4) return;                        // the store was not re-laid out
+    const uint32_t step = (uint32_t)uniform_step(kp);
+    const int par = uniform_par(kp) ^ (wave_uniform(state->rebin) ? 0 : 1);   // where this step's particles now are
+    const int ntiles = kp->g.ntiles;
+    // workgroup b runs on XCD b mod 8: the blocks of one tile go to one XCD,
+    // one after the other, so that its particles are read into one L2 once
+    int tile, blk;
+    {
+        const int b = blockIdx.x, full = ntiles & ~7;
+        if (b < full * nblk) {
+            tile = b / (8 * nblk) * 8 + (b & 7);
+            blk = (b >> 3) % nblk;
+        } else {
+            const int r = b - full * nblk;
+            tile = full + r / nblk;
+            blk = r % nblk;
+        }
+    }
     const uint32_t seed0 = (uint32_t)kp->seed, seed1 = (uint32_t)(kp->seed >> 32), run = kp->run;
     const R cee = R(0.5 * kp->nu_ee * kp->g.dt * kp->ee_vref * kp->ee_vref * kp->ee_vref);
-
-    // local cell of a stored particle (-1 if outside the tile)
-    auto local_cell = [&](const SpeciesDev &S, int64_t slot) {
-        int l[3] = {0, 0, 0};
-        bool inside = true;
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-            int ic;
-            if constexpr (sizeof(R) == 4)
-                ic = t0[a] + (int)(((uint32_t)S.cell[par][slot] >> (a * kp->g.tshift[0])) & (uint32_t)(T - 1));
-            else
-                ic = (int)floor(((const double *)S.pos[par][a])[slot]);
-            l[a] = ic - t0[a];
-            inside = inside && l[a] >= 0 && l[a] < T;
-        }
-        return inside ? (l[2] * T + l[1]) * T + l[0] : -1;
-    };
-    auto slot_of = [&](const SpeciesDev &S, int64_t k, int64_t nf, int64_t nb) {
-        return k < nf ? (int64_t)S.start[tile] + k : (int64_t)S.start[tile] + S.cap[tile] - nb + (k - nf);
-    };
-    // the tile's list of participants: at the sum of the participating
-    // species' bin starts (bins are laid out in tile order in every species,
-    // so the lists of different tiles do not overlap)
-    int64_t lbase = 0;
-    for (int s = 0; s < kp->nspecies; ++s)
-        if (kp->sp[s].binary) lbase += kp->sp[s].start[tile];
-    uint32_t *list = kp->ee_ent + lbase;
-
-    for (int c = threadIdx.x; c < TC; c += blockDim.x) s_cnt[c] = 0;
+    if (threadIdx.x < (unsigned)kp->nspecies) {
+        s_m[threadIdx.x] = R(kp->sp[threadIdx.x].m);
+        const SpeciesDev &S = kp->sp[threadIdx.x];
+        s_w[threadIdx.x] = R(S.w);
+        s_ptr[threadIdx.x][0] = S.id[par];
+        for (int c = 0; c < 3; ++c) s_ptr[threadIdx.x][1 + c] = S.u[par][c];
+        s_ptr[threadIdx.x][4] = S.cell[par];
+    }
     if (threadIdx.x == 0) s_pairs = 0;
     __syncthreads();
-    for (int s = 0; s < kp->nspecies; ++s) {
-        const SpeciesDev &S = kp->sp[s];
-        if (!S.binary) continue;
-        const int64_t nf = S.cnt_front[par * ntiles + tile], nb = S.cnt_back[par * ntiles + tile];
-        for (int64_t k = threadIdx.x; k < nf + nb; k += blockDim.x) {
-            const int lc = local_cell(S, slot_of(S, k, nf, nb));
-            if (lc < 0) atomicOr(&stw->fatal, 8);
-            else atomicAdd(&s_cnt[lc], 1u);
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run_total = 0;
-        for (int c = 0; c < TC; ++c) {
-            s_off[c] = run_total;
-            run_total += s_cnt[c];
-        }
-        s_off[TC] = run_total;
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < TC; c += blockDim.x) s_cnt[c] = 0;
-    __syncthreads();
-    // counting sort of the participants by cell into the tile's list (the
-    // order inside a cell is free: the rank sort below fixes it)
-    for (int s = 0; s < kp->nspecies; ++s) {
-        const SpeciesDev &S = kp->sp[s];
-        if (!S.binary) continue;
-        const int64_t nf = S.cnt_front[par * ntiles + tile], nb = S.cnt_back[par * ntiles + tile];
-        for (int64_t k = threadIdx.x; k < nf + nb; k += blockDim.x) {
-            const int64_t slot = slot_of(S, k, nf, nb);
-            const int lc = local_cell(S, slot);
-            if (lc < 0) continue;
-            const uint32_t pos = s_off[lc] + atomicAdd(&s_cnt[lc], 1u);
-            list[pos] = (uint32_t)slot | ((uint32_t)s << 29);
-        }
-    }
-    __syncthreads();                                     // the list is visible to the whole workgroup
+    auto id_of = [&](uint32_t e) { return ld(gbl((const uint32_t *)s_ptr[e >> 29][0]), e & kSlotMask); };
+    auto u_of = [&](uint32_t e, int c) { return ld(gbl((const R *)s_ptr[e >> 29][1 + c]), e & kSlotMask); };
+    auto hist_get = [&](uint32_t b) { return (s_hist[b >> 1] >> ((b & 1u) * 16u)) & 0xFFFFu; };
+    auto hist_add = [&](uint32_t b) {
+        return (atomicAdd(&s_hist[b >> 1], 1u << ((b & 1u) * 16u)) >> ((b & 1u) * 16u)) & 0xFFFFu;
+    };
+
+    const int ntx = kp->g.nt[0], nty = kp->g.nt[1];
+    const int t0[3] = {(tile % ntx) * T, ((tile / ntx) % nty) * T, (tile / (ntx * nty)) * T};
+    const uint32_t l0 = blk ? kp->ee_off[(size_t)tile * nblk + blk - 1] : 0u;
+    const uint32_t nlist = wave_uniform((int)(kp->ee_off[(size_t)tile * nblk + blk] - l0));
+    const GLB uint32_t *list = gbl((const uint32_t *)kp->ee_ent + bin_list_base(kp, tile) + l0);
+
     uint32_t my_pairs = 0;
-    int c0 = 0;
-    while (c0 < TC) {
-        if (threadIdx.x == 0) {
-            int c1 = c0;
-            while (c1 < TC && s_off[c1 + 1] - s_off[c0] <= (uint32_t)kBinCap) ++c1;
-            if (c1 == c0) {                                  // one cell above the limit: left alone
-                atomicOr(&stw->fatal, 16);
-                c1 = c0 + 1;
-                s_range[1] = 1;
-            } else {
-                s_range[1] = 0;
-            }
-            s_range[0] = (uint32_t)c1;
-        }
-        __syncthreads();
-        const int c1 = (int)s_range[0];
-        const bool skip = s_range[1] != 0;
-        const uint32_t base = s_off[c0], n_in = s_off[c1] - base;
-        if (!skip && n_in >= 2) {
-            // the range's entries with their sort keys and cells
-            for (uint32_t i = threadIdx.x; i < n_in; i += blockDim.x) {
-                const uint32_t e = list[base + i];
-                const uint32_t slot = e & kSlotMask;
-                const uint32_t id = kp->sp[e >> 29].id[par][slot];
-                const uint32_t key = philox10(make_uint4(id, step, kPurposeBinaryKey, run), seed0, seed1).x;
-                s_k64[i] = ((uint64_t)key << 32) | id;
-                s_ent[i] = e;
-                int lo = c0, hi = c1 - 1;                    // cell holding list position base + i
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (s_off[mid] <= base + i) lo = mid;
-                    else hi = mid - 1;
+    int c0 = blk * width;
+    const int cend = min(c0 + width, TC);
+    int w = cend - c0;
+    while (c0 < cend) {
+        // ---- the block's entries in the cells [c0, c0 + w): all of them if
+        // they fit, else the range is halved until it does
+        auto cell_of = [&](uint32_t e) {
+            if constexpr (sizeof(R) == 4)
+                return (uint32_t)ld(gbl((const uint16_t *)s_ptr[e >> 29][4]), e & kSlotMask) - (uint32_t)c0;
+            else
+                return bin_cell<R, D, T>(kp->sp[e >> 29], par, e & kSlotMask, t0) - (uint32_t)c0;
+        };
+        uint32_t n = nlist;
+        if (nlist > CAP) {
+            for (;;) {
+                if (threadIdx.x == 0) s_n = 0;
+                __syncthreads();
+                for (uint32_t i = threadIdx.x; i < nlist; i += NT) {
+                    const uint32_t e = list[i];
+                    if (cell_of(e) < (uint32_t)w) {
+                        const uint32_t at = atomicAdd(&s_n, 1u);
+                        if (at < CAP) s_ent[at] = e;
+                    }
                 }
-                s_cell[i] = (uint16_t)(lo - c0);
+                __syncthreads();
+                n = s_n;
+                __syncthreads();                         // everyone has read s_n
+                if (n <= CAP || w == 1) break;
+                w = (w + 1) >> 1;
+            }
+        }
+        const uint32_t bpc = kBinBuckets / (uint32_t)w;  // buckets per cell
+        if (n > CAP) {                                   // one cell above the limit: left alone
+            if (threadIdx.x == 0) atomicOr(&state->fatal, 16);
+        } else if (n >= 2) {
+            // ---- cell, id, key and momentum of each entry; bucket counts.
+            // All loads of a thread are issued before the first is used: the
+            // chain list -> slot -> words is paid once per workgroup
+            for (int i = threadIdx.x; i < HW; i += NT) s_hist[i] = 0;
+            if (threadIdx.x == 0) s_ntri = 0;
+            __syncthreads();
+            {
+                constexpr int PER = (CAP + NT - 1) / NT;
+                uint32_t e[PER], c[PER], id[PER];
+                R u[PER][3];
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    const uint32_t i = threadIdx.x + j * NT;
+                    e[j] = 0;
+                    if (i < n) e[j] = nlist > CAP ? s_ent[i] : list[i];
+                }
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    const uint32_t i = threadIdx.x + j * NT;
+                    c[j] = id[j] = 0;
+                    u[j][0] = u[j][1] = u[j][2] = R(0);
+                    if (i < n) {
+                        c[j] = cell_of(e[j]);
+                        id[j] = id_of(e[j]);
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) u[j][k] = u_of(e[j], k);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    const uint32_t i = threadIdx.x + j * NT;
+                    if (i < n) {
+                        const uint32_t key = philox10(make_uint4(id[j], step, kPurposeBinaryKey, run), seed0, seed1).x;
+                        s_ent[i] = e[j];
+                        s_cell[i] = (uint16_t)c[j];
+                        s_id[i] = id[j];
+                        s_key[i] = key;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) s_u[k][i] = u[j][k];
+                        (void)hist_add(c[j] * bpc + __umulhi(key, bpc));
+                    }
+                }
             }
             __syncthreads();
-            // rank of each entry among its cell's entries in (key, id) order
-            // (ties, only possible with repeated ids, by list position)
-            for (uint32_t i = threadIdx.x; i < n_in; i += blockDim.x) {
-                const int c = c0 + s_cell[i];
-                const uint32_t lo = s_off[c] - base, hi = s_off[c + 1] - base;
-                const uint64_t k = s_k64[i];
-                uint32_t r = 0;
+            // ---- exclusive prefix of the bucket counts
+            {
+                constexpr int PER = HW / NT;
+                uint32_t v[PER], sum = 0, tot;
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    v[j] = s_hist[threadIdx.x * PER + j];
+                    sum += (v[j] & 0xFFFFu) + (v[j] >> 16);
+                }
+                uint32_t run_ = block_excl(sum, s_wave, &tot);
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    const uint32_t a = v[j] & 0xFFFFu, b = v[j] >> 16;
+                    s_hist[threadIdx.x * PER + j] = run_ | ((run_ + a) << 16);
+                    run_ += a + b;
+                }
+            }
+            __syncthreads();
+            for (uint32_t i = threadIdx.x; i < n; i += NT)
+                s_perm[hist_add((uint32_t)s_cell[i] * bpc + __umulhi(s_key[i], bpc))] = (uint16_t)i;
+            __syncthreads();                             // a bucket's counter now holds its end
+            auto cell_start = [&](uint32_t c) { return c ? hist_get(c * bpc - 1) : 0u; };
+            // ---- places: a cell's N entries take N (N + 1 if N is odd) places
+            uint32_t total;
+            {
+                uint32_t N = 0;
+                if (threadIdx.x < (unsigned)w) {
+                    N = hist_get((threadIdx.x + 1) * bpc - 1) - cell_start(threadIdx.x);
+                    if (N > (uint32_t)kBinLimit) atomicOr(&state->fatal, 16);
+                }
+                const uint32_t p0 = block_excl((N + 1) & ~1u, s_wave, &total);
+                if (threadIdx.x < (unsigned)w) s_pad[threadIdx.x] = (uint16_t)p0;
+            }
+            for (uint32_t i = threadIdx.x; i < total; i += NT) s_idx[i] = kEmpty;
+            __syncthreads();
+            // rank in (key, id) order (ties, only possible with repeated ids,
+            // by entry) among the entries of the bucket
+            for (uint32_t i = threadIdx.x; i < n; i += NT) {
+                const uint32_t c = s_cell[i], key = s_key[i], id = s_id[i];
+                const uint32_t b = c * bpc + __umulhi(key, bpc);
+                const uint32_t lo = b ? hist_get(b - 1) : 0u, hi = hist_get(b);
+                uint32_t r = lo;
                 for (uint32_t j = lo; j < hi; ++j) {
-                    const uint64_t kj = s_k64[j];
-                    r += (kj < k || (kj == k && j < i)) ? 1u : 0u;
+                    const uint32_t o = s_perm[j], ko = s_key[o];
+                    if (ko < key) ++r;
+                    else if (ko == key && o != i) {
+                        const uint32_t io = s_id[o];
+                        r += (io < id || (io == id && o < i)) ? 1u : 0u;
+                    }
                 }
-                s_idx[lo + r] = (uint16_t)i;
-            }
-            // work units per cell: N/2 pairs, or the triple and (N-3)/2 pairs
-            if (threadIdx.x == 0) {
-                uint32_t u = 0;
-                for (int c = c0; c < c1; ++c) {
-                    s_unit[c - c0] = u;
-                    const uint32_t N = s_off[c + 1] - s_off[c];
-                    u += (N & 1u) ? (N >= 3 ? 1u + (N - 3) / 2 : 0u) : N / 2;
-                }
-                s_unit[c1 - c0] = u;
+                const uint32_t cs = cell_start(c), N = hist_get((c + 1) * bpc - 1) - cs;
+                r -= cs;
+                const bool odd3 = (N & 1u) && N >= 3;
+                if (N <= (uint32_t)kBinLimit)
+                    s_idx[s_pad[c] + r + (odd3 && r >= 3 ? 1u : 0u)] = (uint16_t)(i | (odd3 && r == 0 ? kTriple : 0u));
             }
             __syncthreads();
-            const uint32_t units = s_unit[c1 - c0];
-            for (uint32_t w = threadIdx.x; w < units; w += blockDim.x) {
-                int lo = 0, hi = c1 - c0 - 1;                    // cell holding unit w
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (s_unit[mid] <= w) lo = mid;
-                    else hi = mid - 1;
-                }
-                const int c = c0 + lo;
-                const uint32_t N = s_off[c + 1] - s_off[c], seg = s_off[c] - base, ui = w - s_unit[lo];
-                int np;
-                uint32_t ea[3], eb[3];
-                R fct;
-                if ((N & 1u) && ui == 0) {                       // the triple
-                    np = 3;
-                    fct = R(0.5);
-                    ea[0] = s_idx[seg]; eb[0] = s_idx[seg + 1];
-                    ea[1] = s_idx[seg + 1]; eb[1] = s_idx[seg + 2];
-                    ea[2] = s_idx[seg + 2]; eb[2] = s_idx[seg];
-                } else {
-                    np = 1;
-                    fct = R(1);
-                    const uint32_t k = (N & 1u) ? 3 + 2 * (ui - 1) : 2 * ui;
-                    ea[0] = s_idx[seg + k];
-                    eb[0] = s_idx[seg + k + 1];
-                }
-                for (int q = 0; q < np; ++q) {
-                    const SpeciesDev &SA = kp->sp[s_ent[ea[q]] >> 29];
-                    const SpeciesDev &SB = kp->sp[s_ent[eb[q]] >> 29];
-                    const uint32_t sa = s_ent[ea[q]] & kSlotMask, sb = s_ent[eb[q]] & kSlotMask;
-                    R ua[3], ub[3];
+            // ---- the pairs: places (2q, 2q + 1); a triple has its mark on the
+            // first of its three entries, its fourth place is empty.  Its
+            // second and third pair follow in a pass of their own: done at
+            // once they would hold up the 63 other lanes of nearly every wave
+            auto pair = [&](uint32_t a, uint32_t b, R fct) {
+                R ua[3] = {s_u[0][a], s_u[1][a], s_u[2][a]}, ub[3] = {s_u[0][b], s_u[1][b], s_u[2][b]};
+                const uint32_t sa = s_ent[a] >> 29, sb = s_ent[b] >> 29;
+                if (binary_pair<R, UNIT>(ua, s_m[sa], s_w[sa], s_id[a], ub, s_m[sb], s_w[sb], fct, step, seed0, seed1,
+                                         run, cee)) {
+                    ++my_pairs;
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        ua[i] = ((const R *)SA.u[par][i])[sa];
-                        ub[i] = ((const R *)SB.u[par][i])[sb];
-                    }
-                    if (binary_pair<R>(ua, R(SA.m), R(SA.w), (uint32_t)s_k64[ea[q]], ub, R(SB.m), R(SB.w), fct,
-                                       step, seed0, seed1, run, cee)) {
-                        ++my_pairs;
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            ((R *)SA.u[par][i])[sa] = ua[i];
-                            ((R *)SB.u[par][i])[sb] = ub[i];
-                        }
+                    for (int c = 0; c < 3; ++c) {
+                        s_u[c][a] = ua[c];
+                        s_u[c][b] = ub[c];
                     }
                 }
+            };
+            for (uint32_t q = threadIdx.x; 2 * q < total; q += NT) {
+                const uint32_t e0 = s_idx[2 * q], e1 = s_idx[2 * q + 1];
+                if (e0 == kEmpty || e1 == kEmpty) continue;
+                if (e0 & kTriple) s_tri[atomicAdd(&s_ntri, 1u)] = (uint16_t)(2 * q);
+                pair(e0 & ~(uint32_t)kTriple, e1, (e0 & kTriple) ? R(0.5) : R(1));
+            }
+            __syncthreads();
+            for (uint32_t q = threadIdx.x; q < s_ntri; q += NT) {
+                const uint32_t p = s_tri[q], e0 = s_idx[p] & ~(uint32_t)kTriple, e1 = s_idx[p + 1], e2 = s_idx[p + 2];
+#pragma unroll 1
+                for (int k = 0; k < 2; ++k) pair(k ? e2 : e1, k ? e0 : e2, R(0.5));
+            }
+            __syncthreads();
+            // ---- momenta back to the store
+            for (uint32_t i = threadIdx.x; i < n; i += NT) {
+                const uint32_t e = s_ent[i];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) st(gbl((R *)s_ptr[e >> 29][1 + c]), e & kSlotMask, s_u[c][i]);
             }
         }
-        __syncthreads();                                     // the LDS lists are rebuilt for the next range
-        c0 = c1;
+        __syncthreads();                                 // the LDS lists are rebuilt for the next range
+        c0 += w;
+        w = min(w, cend - c0);
     }
     atomicAdd(&s_pairs, my_pairs);
     __syncthreads();
-    if (threadIdx.x == 0) kp->ee_tile[tile] = (int64_t)s_pairs;
+    if (threadIdx.x == 0) kp->ee_part[blockIdx.x] = s_pairs;
+}
+
+int binary_blocks(bool mixed, int64_t tile_cells, int64_t ppc, int *width)
+{
+    const int64_t cap = mixed ? kBinCap<float> : kBinCap<double>;
+    const int64_t w = std::max<int64_t>(1, std::min<int64_t>({cap * 4 / 5 / std::max<int64_t>(1, ppc), tile_cells,
+                                                              (int64_t)kBinMaxWidth}));
+    const int64_t nblk = (tile_cells + w - 1) / w;
+    *width = (int)((tile_cells + nblk - 1) / nblk);
+    return (int)nblk;
 }
 
 template <typename R>
@@ -2153,7 +2353,7 @@ __device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int
         double ee = 0.0;
         if (kp->binary) {
             double a[1] = {0.0};
-            for (int t = threadIdx.x; t < ntiles; t += blockDim.x) a[0] += (double)kp->ee_tile[t];
+            for (int t = threadIdx.x; t < kp->ee_nparts; t += blockDim.x) a[0] += (double)kp->ee_part[t];
             block_sum<1>(a, (double(*)[1])sred);
             ee = a[0];
         }
@@ -2594,7 +2794,18 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
     L(k_rebin_finalize, dim3(nst), dim3(256), dp);
     if (hp.binary) {
         L.grp = 1;
-        L(k_binary<R, D, T>, dim3(ntiles), dim3(kBinThreads), dp);
+        int64_t ppc = 0;
+        bool unit = true;
+        for (int s = 0; s < hp.nspecies; ++s)
+            if (hp.sp[s].binary) {
+                ppc += hp.sp[s].ppc;
+                unit = unit && R(hp.sp[s].m) == R(1);
+            }
+        int width;
+        const int nblk = binary_blocks(sizeof(R) == 4, D == 3 ? T * T * T : T * T, ppc, &width);
+        L(k_binary_list<R, D, T>, dim3(ntiles), dim3(kBinListThreads), dp, ((1u << 22) + width - 1) / width, nblk);
+        L(unit ? k_binary<R, D, T, true> : k_binary<R, D, T, false>, dim3((unsigned)(ntiles * nblk)),
+          dim3(kBinThreads<R>), dp, width, nblk);
     }
     L.grp = 3;
     L(k_reduce_j<R, D>, dim3(cb), dim3(256), dp);

@@ -26,6 +26,7 @@ thread_local std::string g_last_error;
 struct Layout {
     size_t particle_bytes[kMaxSpecies] = {};
     size_t field_bytes = 0, scratch_bytes = 0, diag_bytes = 0;
+    size_t state_bytes = 0;                                 // leading part of the scratch that a checkpoint holds
     // offsets inside the particle buffer of each species
     struct Sp {
         size_t cell[3], pos[3][3], u[3][3], id[3];
@@ -36,8 +37,9 @@ struct Layout {
     size_t F, J;                                            // field buffer
     size_t Jtile, tile_diag, field_diag, moments, state, kparams, rb[4], order, bucket;   // scratch
     size_t rho_tile, rho0, rho_n, gauss_part, cont_part;    // scratch (Gauss-law and continuity checks)
-    size_t ee_tile;                                         // scratch (binary-collision counts per tile)
-    size_t ee_ent = 0;                                      // scratch (binary collisions: cell-sorted participants)
+    size_t ee_part = 0, ee_off = 0;                         // scratch (binary collisions: pairs and list ends per workgroup)
+    size_t ee_ent = 0;                                      // scratch (binary collisions: participants by block of cells)
+    int ee_blocks = 0;                                      // workgroups per tile of the binary-collision kernel
     bool checks = false;                                    // PIC_FLAG_GAUSS_RESIDUAL: the above are carved
     Geometry g;
     int nj;
@@ -207,15 +209,15 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
         L->field_diag = c.take((size_t)kFieldDiagBlocks * kFieldDiag * 8);
         L->moments = c.take((size_t)kMomentBlocks * kMomentVals * 8);
         L->state = c.take(sizeof(DevState));
-        L->kparams = c.take(sizeof(KParams));
+        c.take(kCkptParamBytes);
         for (int i = 0; i < 4; ++i) L->rb[i] = c.take((size_t)ns * G.ntiles * 4);
         L->order = c.take((size_t)G.ntiles * 4);
         L->bucket = c.take((size_t)G.ntiles);
-        L->ee_tile = c.take((size_t)G.ntiles * 8);
+        c.take((size_t)G.ntiles * 8);
         {
             // binary collisions: one 32-bit entry (slot | species << 29) per
             // store slot of each participating species
-            int64_t ent = 0;
+            int64_t ent = 0, ppc = 0;
             const bool ee_on = g->nu_ee > 0.0 && !(g->flags & PIC_FLAG_NO_COLLIDE);
             for (int s = 0; ee_on && s < ns; ++s)
                 if (sp[s].binary) {
@@ -223,8 +225,13 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
                         return fail(err, PIC_E_CAPACITY, "species %d: binary collisions need a store below 2^29 "
                                     "slots (%lld)", s, (long long)L->sp[s].ncap);
                     ent += L->sp[s].ncap;
+                    ppc += sp[s].ppc;
                 }
-            if (ent > 0) L->ee_ent = c.take((size_t)ent * 4);
+            if (ent > 0) {
+                int width;
+                L->ee_ent = c.take((size_t)ent * 4);
+                L->ee_blocks = binary_blocks(g->precision == PIC_PREC_MIXED, tile_cells, ppc, &width);
+            }
         }
         L->checks = (g->flags & PIC_FLAG_GAUSS_RESIDUAL) != 0;
         if (L->checks) {
@@ -235,6 +242,15 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
             L->rho_n = c.take((size_t)G.cells * 8);
             L->gauss_part = c.take((size_t)((G.cells + 255) / 256) * 2 * 8);
             L->cont_part = c.take((size_t)((G.cells + 255) / 256) * 2 * 8);
+        }
+        // What a step makes afresh, and the parameter block with this run's
+        // addresses, come after the part that a checkpoint holds, whose
+        // layout files depend on.
+        L->state_bytes = c.off;
+        L->kparams = c.take(sizeof(KParams));
+        if (L->ee_blocks) {
+            L->ee_part = c.take((size_t)G.ntiles * L->ee_blocks * 4);
+            L->ee_off = c.take((size_t)G.ntiles * L->ee_blocks * 4);
         }
         L->scratch_bytes = c.off;
     }
@@ -858,8 +874,12 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
     r->dp = (KParams *)at(buffers->scratch, L.kparams);
     K.fd_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(kFieldDiagBlocks, (L.g.cells + 2047) / 2048));
     K.order = (int32_t *)at(buffers->scratch, L.order);
-    K.ee_tile = (int64_t *)at(buffers->scratch, L.ee_tile);
-    K.ee_ent = L.ee_ent ? (uint32_t *)at(buffers->scratch, L.ee_ent) : nullptr;
+    if (L.ee_blocks) {
+        K.ee_part = (uint32_t *)at(buffers->scratch, L.ee_part);
+        K.ee_nparts = L.g.ntiles * L.ee_blocks;
+        K.ee_ent = (uint32_t *)at(buffers->scratch, L.ee_ent);
+        K.ee_off = (uint32_t *)at(buffers->scratch, L.ee_off);
+    }
     K.tile_bucket = (uint8_t *)at(buffers->scratch, L.bucket);
     if (L.checks) {
         K.rho_tile = (double *)at(buffers->scratch, L.rho_tile);
@@ -1286,7 +1306,7 @@ int ckpt_buffers(const pic_run *r, void *ptr[kMaxSpecies + 3], uint64_t bytes[kM
     ptr[kMaxSpecies] = r->buf.fields;
     bytes[kMaxSpecies] = r->L.field_bytes;
     ptr[kMaxSpecies + 1] = r->buf.scratch;
-    bytes[kMaxSpecies + 1] = r->L.scratch_bytes;
+    bytes[kMaxSpecies + 1] = r->L.state_bytes;
     ptr[kMaxSpecies + 2] = r->buf.diag;
     bytes[kMaxSpecies + 2] = r->L.diag_bytes;
     return PIC_OK;

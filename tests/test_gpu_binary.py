@@ -110,6 +110,43 @@ def test_binary_capacity_limit_is_reported(pic):
     g.close()
 
 
+@pytest.mark.parametrize("prec,bar", [("fp64", 1e-11), ("mixed", 1e-3)])
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_binary_crowded_cells(pic, tile, prec, bar):
+    """Uneven cells, so that a workgroup's block of cells outgrows its LDS
+    lists and is taken in parts: 2048 participants (the limit) and 2047 in
+    neighbouring cells, 1500 two cells on, then 3, 1 and 0, the rest as
+    loaded; one step against the oracle, pairs equal, momenta by id to the
+    bars of the cases above.  The particles keep off the cell faces, so both
+    precisions pair alike."""
+    log(f"case binary crowded cells tile {tile} {prec}")
+    wl = synth.beam_plasma((32, 32), ppc=32, u_th_beam=0.0, u_th_plasma=0.02, nu_ee=0.5, ee_vref=0.1,
+                           binary=(False, True), steps=1)
+    parts = synth.load(wl)
+    rng = np.random.default_rng(7)
+    x, d = parts[1].x, wl.d[0]
+    N = x.shape[1]
+    cell = np.stack([rng.integers(0, 32, N), rng.integers(0, 32, N)])
+    cell[1, cell[1] == 5] = 6                         # row 5 holds only what follows
+    at = 0
+    for i, n in ((4, 2048), (5, 2047), (7, 1500), (8, 3), (9, 1)):
+        cell[:, at:at + n] = [[i], [5]]
+        at += n
+    x[:] = (cell + rng.uniform(0.2, 0.8, x.shape)) * d
+    parts[1].u[:] -= parts[1].u.mean(axis=1, keepdims=True)
+    orc = oracle_run(wl, parts)
+    ro = orc.step(1, diag=True)
+    g = gpu_run(wl, parts, pic.PIC_PREC_FP64 if prec == "fp64" else pic.PIC_PREC_MIXED, tile=tile, diag_every=1)
+    g.step(1)
+    assert g.history()[-1]["ee_pairs"] == ro[-1]["ee_pairs"]
+    _, u, _ = by_id(*g.read_particles(1))
+    _, uo, _ = by_id(orc.species[1].x, orc.species[1].u, orc.species[1].id)
+    worst = float(np.max(np.abs(u - uo)) / np.max(np.abs(uo)))
+    log(f"  worst |du|/max|u| {worst:.2e}")
+    g.close()
+    assert worst < bar
+
+
 def test_binary_refused_in_a_batch(pic):
     log("case binary batch refusal")
     wl = synth.beam_plasma((32, 32), ppc=4, nu_ee=0.5, ee_vref=0.2)
