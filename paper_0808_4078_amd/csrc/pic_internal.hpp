@@ -27,6 +27,10 @@ constexpr int kRing = 4096;          // diagnostic records kept on the device
 constexpr int kTileDiag = 6;         // per tile and species: KE, px, py, pz, count, collisions
 constexpr int kFieldDiag = 10;       // per block: W[6], p_field[3], unused
 constexpr int kFieldDiagBlocks = 512;
+constexpr int64_t kSplitGroups = 1024;             // workgroups that a grid with few tiles is split into
+constexpr int64_t kSplitMin = 512;                 // particles that a workgroup of a split tile takes at least
+constexpr int64_t kSplitBytes = int64_t(24) << 20; // bound of the split tiles' partial currents
+constexpr int kSplitLine = 32;                     // words per counter of a split tile: a cache line
 constexpr int kBinAlign = 64;        // particle-store bins start at multiples of this many slots
 constexpr int kMomentBlocks = 1024;  // loader reductions
 constexpr int kMomentVals = 6;
@@ -122,6 +126,11 @@ struct KParams {
     int32_t *rb_cap;     // [nspecies][tiles]
     int32_t *rb_fill;    // [nspecies][tiles]
     int fd_blocks;       // blocks (and partial records) of the field-diagnostic reduction
+    int32_t split;       // workgroups per tile of the particle kernel (1, or more where the grid has few tiles)
+    void *Jsplit;        // split > 1: [tiles][split][3][nj^ndim] FP64 partial currents
+    uint32_t *split_cnt;    // split > 1: [nspecies][tiles][2][kSplitLine] particles written to the bin's front
+                            // and back so far this step
+    double *split_diag;  // split > 1: [tiles][split][nspecies][kTileDiag]
     int32_t *order;      // [tiles] particle-kernel work order (XCD class, then decreasing load)
     uint8_t *tile_bucket;   // [tiles] load bucket of each tile, written by the particle kernel
     double order_scale;  // bucket = round(particles in the tile * order_scale): 16 per nominal load
@@ -208,8 +217,17 @@ hipError_t batch_particle_occupancy(int precision, int ndim, int g, bool coulomb
 // Initialisation shared by pic_init (static_device = -1, the caller's
 // scratch) and pic_init_static_scratch (the library's scratch of that
 // device, already claimed; pic_destroy releases it).
+// static_scratch_needed: bytes of that scratch that count against
+// PIC_STATIC_SCRATCH_BYTES; parts of the scratch that a run can do without are
+// left out where the whole does not fit.
+size_t static_scratch_needed(const pic_grid_desc *grid, const pic_species_desc *species, int nspecies);
 int init_run(const pic_grid_desc *grid, const pic_species_desc *species, int nspecies,
              const pic_buffers *buffers, void *hip_stream, pic_run **out, int static_device);
+// The library's scratch: what a caller may count on, and room for what lies
+// behind the part of the scratch that a checkpoint holds (parameter block,
+// binary-collision counts: far below 1 MiB for any run whose other scratch
+// fits PIC_STATIC_SCRATCH_BYTES).
+constexpr size_t kStaticScratch = PIC_STATIC_SCRATCH_BYTES + ((size_t)1 << 20);
 // One run at a time per device may hold the library's scratch of that device.
 constexpr int kMaxDevices = 64;
 bool claim_static_scratch(int device);     // false if held

@@ -163,6 +163,22 @@ __device__ __forceinline__ bool diag_step(KP kp, int64_t step)
     return kp->diag_every > 0 && (step % kp->diag_every) == 0;
 }
 
+// Workgroup b of a launch in which `parts` consecutive workgroups of one XCD
+// (b, b + 8, ...: workgroups go to the 8 XCDs in turn) share an item; items
+// keep their order and XCD class (item mod 8).
+__device__ __forceinline__ void split_item(int b, int nitems, int parts, int *item, int *part)
+{
+    const int full = nitems & ~(kBatchXcds - 1);
+    if (b < full * parts) {
+        *item = b / (kBatchXcds * parts) * kBatchXcds + b % kBatchXcds;
+        *part = b / kBatchXcds % parts;
+    } else {
+        const int r = b - full * parts;
+        *item = full + r / parts;
+        *part = r % parts;
+    }
+}
+
 // Block-wide FP64 sum of N values held per thread; result valid in thread 0.
 // Fixed reduction order, so repeated runs give identical bits.
 template <int N>
@@ -497,8 +513,15 @@ constexpr int kMoverStage = sizeof(R) == 4 ? (D == 3 ? 24 : 64) : 1;
 // BS: the field stage issues all of a thread's loads before its LDS writes
 // (one workgroup per tile); the persistent batched kernel keeps the plain
 // loop, whose registers do not add to those it holds across work items.
-template <typename R, typename A, int D, int T, bool CB, int SH, bool BS, typename KP>
-__device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
+// SPLIT: `parts` workgroups share a tile (a grid with few tiles), each taking
+// an equal part of every species' particles: workgroup `part` deposits into a
+// partial current of its own (Jsplit), and the stayers of all of them fill the
+// bin's front through a counter in memory.  Each of a tile's two counters of a
+// species has a cache line to itself: with the counters of 32 tiles in one
+// line (a small grid then has a dozen lines in all) the atomics of every
+// workgroup queued up there.
+template <typename R, typename A, int D, int T, bool CB, int SH, bool BS, bool SPLIT, typename KP>
+__device__ __forceinline__ void particle_body(KP kp, int tile, int part, int parts)
 {
     constexpr int kBlock = kShapeBlock[SH];
     constexpr int kBatch = kShapeInflight[SH];
@@ -522,11 +545,10 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
     __shared__ uint32_t s_front[kMaxSpecies];           // stayers written to the front of each species' bin
     __shared__ double sred[kBlock / 64][kTileDiag];
 
-    const int tile = bid;
-    (void)nb;
     const int ntx = kp->g.nt[0], nty = kp->g.nt[1];
     const int n[3] = {kp->g.n[0], kp->g.n[1], kp->g.n[2]};
     const int ntiles = kp->g.ntiles;
+    const int item = SPLIT ? tile * parts + part : tile;   // partial current and diagnostics of this workgroup
     int t0[3];
     t0[0] = (tile % ntx) * T;
     t0[1] = ((tile / ntx) % nty) * T;
@@ -608,6 +630,16 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
         const uint32_t nb = S.cnt_back[src * ntiles + tile];
         const uint32_t total = nf + nb;
         load += total;
+        // this workgroup's particles [k0, k1): all, or one of `parts` runs of
+        // whole waves
+        uint32_t k0 = 0, k1 = total;
+        if constexpr (SPLIT) {
+            const uint32_t per = ((total + (uint32_t)parts - 1u) / (uint32_t)parts + 63u) & ~63u;
+            k0 = min(total, per * (uint32_t)part);
+            k1 = min(total, k0 + per);
+        }
+        // split tiles: the front and back counters of tile t
+        GLB uint32_t *cnt = SPLIT ? gbl(kp->split_cnt + (size_t)s * ntiles * 2 * kSplitLine) : nullptr;
         const R qm = R(S.qmdt2);
         R kd[3];                                            // q w d_a/dt
         for (int a = 0; a < 3; ++a) kd[a] = R(S.qw * kp->g.d[a] / kp->g.dt);
@@ -719,9 +751,10 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
                 }
             }
         };
+        auto back_of = [&](int t) { return SPLIT ? cnt + 2 * kSplitLine * t + kSplitLine : cb_dst + t; };
         // reserve one slot in tile t and write m there (unstaged path)
         auto emit_now = [&](int t, const Raw &m) {
-            const uint32_t slot = __hip_atomic_fetch_add(cb_dst + t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t slot = __hip_atomic_fetch_add(back_of(t), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             emit_mover(slot, tcap[t] - (int32_t)cf_src[t] - (int32_t)cb_src[t], tstart[t] + tcap[t] - 1, m);
         };
         uint32_t mv_n = 0;                                   // staged movers of this wave (uniform)
@@ -748,7 +781,7 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
             uint32_t b0 = 0;
             int32_t room = 0, top = 0;
             if (valid && lane == leader) {
-                b0 = __hip_atomic_fetch_add(cb_dst + td, lead_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                b0 = __hip_atomic_fetch_add(back_of(td), lead_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 room = tcap[td] - (int32_t)cf_src[td] - (int32_t)cb_src[td];
                 top = tstart[td] + tcap[td] - 1;
             }
@@ -768,23 +801,46 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
             __builtin_amdgcn_wave_barrier();
             mv_n = 0;
         };
+        // A particle that stays goes to the bin's front, at the slot that its
+        // wave reserved (base, in the leader's lane) plus its rank.  Split
+        // tiles reserve in memory: the atomic's round trip would add 1-2 us to
+        // every iteration, so a wave stores the stayers of one iteration in the
+        // next, when the answer has long arrived.
+        struct Stayer {
+            bool stay;
+            int leader;
+            uint32_t base, rank;
+            Raw m;
+        };
+        auto store_stayer = [&](const Stayer &w) {
+            const uint32_t o = (uint32_t)bstart + (uint32_t)__builtin_amdgcn_readlane(w.base, w.leader) + w.rank;
+            if (!w.stay) return;
+            if constexpr (sizeof(R) == 4) st(ocell, o, (uint16_t)w.m.c);
+#pragma unroll
+            for (int a = 0; a < D; ++a) st(opos_a[a], o, w.m.p[a]);
+            st(ou0, o, w.m.u[0]);
+            st(ou1, o, w.m.u[1]);
+            st(ou2, o, w.m.u[2]);
+            if (track) st(oid, o, w.m.id);
+        };
+        Stayer held{};
         Raw q[kBatch];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const uint32_t kk = u * kBlock + threadIdx.x;
-            if (kk < total) fetch(kk, q[u]);
+            const uint32_t kk = k0 + u * kBlock + threadIdx.x;
+            if (kk < k1) fetch(kk, q[u]);
         }
 #pragma unroll 1
-        for (uint32_t base = 0; base < total; base += kBlock) {
+        for (uint32_t base = k0; base < k1; base += kBlock) {
             {
             const uint32_t k = base + threadIdx.x;
-            const bool active = k < total;
+            const bool active = k < k1;
             const Raw cur = q[0];
 #pragma unroll
             for (int v = 0; v + 1 < kBatch; ++v) q[v] = q[v + 1];
             {
                 const uint32_t kn = k + kBatch * kBlock;
-                if (kn < total) fetch(kn, q[kBatch - 1]);
+                if (kn < k1) fetch(kn, q[kBatch - 1]);
             }
             int ic1[D];
             R off1[D];
@@ -995,19 +1051,16 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
             // ---- binning
             const bool stay = active && t1 == tile;
             const uint64_t smask = __ballot(stay);
-            uint32_t opos = 0;
-            bool wr = false;
-            if (smask) {
-                const int leader = __ffsll((unsigned long long)smask) - 1;
-                uint32_t bfront = 0;
-                if (lane == leader) bfront = atomicAdd(&s_front[s], (uint32_t)__popcll(smask));
-                bfront = __builtin_amdgcn_readlane(bfront, leader);
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(smask >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)smask, 0u));
-                if (stay) {
-                    opos = (uint32_t)bstart + bfront + rank;
-                    wr = true;
-                }
+            const int leader = smask ? __ffsll((unsigned long long)smask) - 1 : 0;
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(smask >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)smask, 0u));
+            uint32_t bfront = 0;                               // valid in the leader's lane
+            if (smask && lane == leader) {
+                if constexpr (SPLIT)
+                    bfront = __hip_atomic_fetch_add(cnt + 2 * kSplitLine * tile, (uint32_t)__popcll(smask), __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+                else
+                    bfront = atomicAdd(&s_front[s], (uint32_t)__popcll(smask));
             }
             uint32_t cpack = 0, lpack = 0;             // global (movers) and in-tile (stayers) cell
             if constexpr (sizeof(R) == 4) {
@@ -1064,22 +1117,27 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
                     emit_now(t1, m);
                 }
             }
-            if (wr) {
-                if constexpr (sizeof(R) == 4) {
-                    st(ocell, opos, (uint16_t)lpack);
+            Stayer now;
+            now.stay = stay;
+            now.leader = leader;
+            now.base = bfront;
+            now.rank = rank;
+            now.m.c = lpack;
 #pragma unroll
-                    for (int a = 0; a < D; ++a) st(opos_a[a], opos, off1[a]);
-                } else {
-#pragma unroll
-                    for (int a = 0; a < D; ++a) st(opos_a[a], opos, R((double)ic1[a] + off1[a]));
-                }
-                st(ou0, opos, ux);
-                st(ou1, opos, uy);
-                st(ou2, opos, uz);
-                if (track) st(oid, opos, pid);
+            for (int a = 0; a < D; ++a) now.m.p[a] = sizeof(R) == 4 ? off1[a] : R((double)ic1[a] + off1[a]);
+            now.m.u[0] = ux;
+            now.m.u[1] = uy;
+            now.m.u[2] = uz;
+            now.m.id = pid;
+            if constexpr (SPLIT) {
+                store_stayer(held);
+                held = now;
+            } else {
+                store_stayer(now);
             }
             }
         }
+        if constexpr (SPLIT) store_stayer(held);
         if constexpr (MS > 1) {
             if (mv_n) flush_movers();
         }
@@ -1092,15 +1150,22 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
             block_sum<kTileDiag>(acc, sred);
             if (threadIdx.x == 0)
                 for (int v = 0; v < kTileDiag; ++v)
-                    kp->tile_diag[((int64_t)tile * kp->nspecies + s) * kTileDiag + v] = acc[v];
+                    (SPLIT ? kp->split_diag : kp->tile_diag)[((int64_t)item * kp->nspecies + s) * kTileDiag + v] = acc[v];
         }
     }
     __syncthreads();
-    if (threadIdx.x < (unsigned)kp->nspecies) kp->sp[threadIdx.x].cnt_front[dst * ntiles + tile] = s_front[threadIdx.x];
-    if (threadIdx.x == 0)
+    if constexpr (!SPLIT)
+        if (threadIdx.x < (unsigned)kp->nspecies)
+            kp->sp[threadIdx.x].cnt_front[dst * ntiles + tile] = s_front[threadIdx.x];
+    if (threadIdx.x == 0 && part == 0)
         kp->tile_bucket[tile] = (uint8_t)min(kOrderBuckets - 1, (int)((double)load * kp->order_scale + 0.5));
-    GLB R *Jt = gbl((R *)kp->Jtile) + (int64_t)tile * 3 * NJ_D;
-    for (int i = threadIdx.x; i < 3 * NJ_D; i += kBlock) Jt[i] = R(sJ[i]);
+    if constexpr (SPLIT) {
+        GLB A *Jt = gbl((A *)kp->Jsplit) + (int64_t)item * 3 * NJ_D;
+        for (int i = threadIdx.x; i < 3 * NJ_D; i += kBlock) Jt[i] = sJ[i];
+    } else {
+        GLB R *Jt = gbl((R *)kp->Jtile) + (int64_t)tile * 3 * NJ_D;
+        for (int i = threadIdx.x; i < 3 * NJ_D; i += kBlock) Jt[i] = R(sJ[i]);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1108,16 +1173,26 @@ __device__ __forceinline__ void particle_body(KP kp, int bid, int nb)
 // Data of the step sits in set dst (bins) and set 2 (overflow list); it is
 // rewritten into set src with capacities count + a uniform reserve, and the
 // parity is kept so that the next step reads set src.
-__device__ __forceinline__ void rebin_count_body(const KParams *__restrict__ kp, int bid, int nb)
+// SPLIT: first the split tiles' counters become the bins' counts (every step)
+// and start over.
+template <bool SPLIT>
+__device__ __forceinline__ void rebin_count_body(const KParams *__restrict__ kp, int bid)
 {
     const DevState *st = kp->state;
-    if (!st->rebin) return;
+    if (!SPLIT && !st->rebin) return;
     const int ntiles = kp->g.ntiles;
     const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
     if (i >= (int64_t)kp->nspecies * ntiles) return;
     const int s = (int)(i / ntiles), t = (int)(i % ntiles);
     const SpeciesDev &S = kp->sp[s];
     const int src = st->par, dst = src ^ 1;
+    if constexpr (SPLIT) {
+        uint32_t *c = kp->split_cnt + i * 2 * kSplitLine;
+        S.cnt_front[dst * ntiles + t] = c[0];
+        S.cnt_back[dst * ntiles + t] = c[kSplitLine];
+        c[0] = c[kSplitLine] = 0;
+        if (!st->rebin) return;
+    }
     const int64_t room = (int64_t)S.cap[t] - S.cnt_front[src * ntiles + t] - S.cnt_back[src * ntiles + t];
     const int64_t vb = min((int64_t)S.cnt_back[dst * ntiles + t], room);
     const int32_t c = (int32_t)(S.cnt_front[dst * ntiles + t] + vb);
@@ -1643,17 +1718,7 @@ __global__ __launch_bounds__(kBinThreads<R>) void k_binary(const KParams *__rest
     // workgroup b runs on XCD b mod 8: the blocks of one tile go to one XCD,
     // one after the other, so that its particles are read into one L2 once
     int tile, blk;
-    {
-        const int b = blockIdx.x, full = ntiles & ~7;
-        if (b < full * nblk) {
-            tile = b / (8 * nblk) * 8 + (b & 7);
-            blk = (b >> 3) % nblk;
-        } else {
-            const int r = b - full * nblk;
-            tile = full + r / nblk;
-            blk = r % nblk;
-        }
-    }
+    split_item(blockIdx.x, ntiles, nblk, &tile, &blk);
     const uint32_t seed0 = (uint32_t)kp->seed, seed1 = (uint32_t)(kp->seed >> 32), run = kp->run;
     const R cee = R(0.5 * kp->nu_ee * kp->g.dt * kp->ee_vref * kp->ee_vref * kp->ee_vref);
     if (threadIdx.x < (unsigned)kp->nspecies) {
@@ -2065,6 +2130,62 @@ __device__ __forceinline__ void rebin_finalize_body(const KParams *__restrict__ 
 // each axis are workgroup-uniform; per node and axis only the choice among
 // them (and the local index) varies, and a partial's offset is the sum of
 // one term per axis.
+// Split tiles: the `parts` FP64 partials of a tile lie one after the other
+// (`pstride` apart).  A tile's partials are summed in order and rounded to the
+// run's precision, as a tile that is not split rounds its LDS sums, and the
+// tiles are then summed in the same order as there: in mixed precision, where
+// the FP64 sums of FP32 terms are exact, the current does not depend on the
+// split.  One thread per node and component, since a small grid has few nodes.
+template <typename R, int D>
+__global__ __launch_bounds__(256) void k_reduce_j_split(const KParams *__restrict__ kp, int parts)
+{
+    const int64_t cells = kp->g.cells;
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q >= cells) return;
+    const int comp = blockIdx.y;
+    const int T = kp->g.tile[0], NJ = T + 3;
+    const int NJ_D = D == 3 ? NJ * NJ * NJ : NJ * NJ;
+    const int n[3] = {kp->g.n[0], kp->g.n[1], kp->g.n[2]};
+    const int idx[3] = {(int)(q % n[0]), (int)((q / n[0]) % n[1]), D == 3 ? (int)(q / ((int64_t)n[0] * n[1])) : 0};
+    int cn[3] = {1, 1, 1}, ct[3][2] = {}, cl[3][2] = {};
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        const int tb = idx[a] / T, r = idx[a] - tb * T, nt = kp->g.nt[a];
+        if (r <= 1) {
+            ct[a][0] = tb == 0 ? nt - 1 : tb - 1;
+            cl[a][0] = r + 1 + T;
+            ct[a][1] = tb;
+            cl[a][1] = r + 1;
+            cn[a] = 2;
+        } else {
+            ct[a][0] = tb;
+            cl[a][0] = r + 1;
+            ct[a][1] = tb + 1 == nt ? 0 : tb + 1;
+            cl[a][1] = 0;
+            cn[a] = r == T - 1 ? 2 : 1;
+        }
+    }
+    const GLB double *Js = gbl((const double *)kp->Jsplit) + (int64_t)comp * NJ_D;
+    const int64_t pstride = 3 * (int64_t)NJ_D;
+    double j = 0.0;
+    for (int iz = 0; iz < cn[2]; ++iz)
+        for (int iy = 0; iy < cn[1]; ++iy)
+            for (int ix = 0; ix < cn[0]; ++ix) {
+                const int64_t t = ((int64_t)ct[2][iz] * kp->g.nt[1] + ct[1][iy]) * kp->g.nt[0] + ct[0][ix];
+                const GLB double *p = Js + t * parts * pstride + ((int64_t)cl[2][iz] * NJ + cl[1][iy]) * NJ + cl[0][ix];
+                double sum = 0.0;
+                for (int k0 = 0; k0 < parts; k0 += 8) {
+                    double v[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[k] = k0 + k < parts ? p[(k0 + k) * pstride] : 0.0;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) sum += v[k];
+                }
+                j += (double)R(sum);
+            }
+    kp->J[(int64_t)comp * cells + q] = j;
+}
+
 template <typename R>
 __device__ __forceinline__ void reduce_j_tile3(const KParams *__restrict__ kp, int bid)
 {
@@ -2284,7 +2405,7 @@ __device__ __forceinline__ void yee_e_body(const KParams *__restrict__ kp, int b
 // ---------------------------------------------------------------------------
 // End of step: diagnostic record, reset of the next destination's mover
 // counters, step and parity update.  One workgroup.
-__device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int bid, int nb)
+__device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int parts)
 {
     __shared__ double sred[kAdvanceThreads / 64][10];
     DevState *st = kp->state;
@@ -2308,8 +2429,9 @@ __device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int
         double pp[3] = {0, 0, 0};
         for (int s = 0; s < ns; ++s) {
             double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            for (int t = threadIdx.x; t < ntiles; t += blockDim.x)
-                for (int v = 0; v < kTileDiag; ++v) a[v] += kp->tile_diag[((int64_t)t * ns + s) * kTileDiag + v];
+            const double *td = parts > 1 ? kp->split_diag : kp->tile_diag;
+            for (int t = threadIdx.x; t < ntiles * parts; t += blockDim.x)
+                for (int v = 0; v < kTileDiag; ++v) a[v] += td[((int64_t)t * ns + s) * kTileDiag + v];
             block_sum<8>(a, (double(*)[8])sred);
             if (threadIdx.x == 0) {
                 rec.kinetic[s] = a[0] * dv;
@@ -2455,7 +2577,17 @@ template <typename R, typename A, int D, int T, bool CB, int SH>
 __global__ __launch_bounds__(kShapeBlock[SH]) void k_particle(const KParams *__restrict__ kp)
 {
     const KParamsC *kc = (const KParamsC *)kp;
-    particle_body<R, A, D, T, CB, SH, true>(kc, wave_uniform(kc->order[blockIdx.x]), 0);
+    particle_body<R, A, D, T, CB, SH, true, false>(kc, wave_uniform(kc->order[blockIdx.x]), 0, 1);
+}
+
+// `parts` workgroups per tile.
+template <typename R, typename A, int D, int T, bool CB>
+__global__ __launch_bounds__(kShapeBlock[0]) void k_particle_split(const KParams *__restrict__ kp, int parts)
+{
+    const KParamsC *kc = (const KParamsC *)kp;
+    int pos, part;
+    split_item(blockIdx.x, kc->g.ntiles, parts, &pos, &part);
+    particle_body<R, A, D, T, CB, 0, true, true>(kc, wave_uniform(kc->order[pos]), part, parts);
 }
 
 // Persistent: workgroup w (on XCD w mod 8) takes the items of its XCD
@@ -2482,7 +2614,7 @@ __global__ __launch_bounds__(kShapeBlock[SH]) void kb_particle(const BatchTable 
             if (i >= len) break;
             const int2 it = items[i];
             const KParamsC *kp = (const KParamsC *)wave_uniform_ptr(bt->kp[wave_uniform(it.x)]);
-            particle_body<R, A, D, T, CB, SH, false>(kp, wave_uniform(kp->order[wave_uniform(it.y)]), 0);
+            particle_body<R, A, D, T, CB, SH, false, false>(kp, wave_uniform(kp->order[wave_uniform(it.y)]), 0, 1);
         }
     }
 }
@@ -2496,10 +2628,19 @@ __global__ __launch_bounds__(kShapeBlock[SH]) void kb_particle(const BatchTable 
     {                                                                                   \
         BODY(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);                                \
     }
-PIC_RUN_KERNELS(rebin_count, rebin_count_body)
 PIC_RUN_KERNELS(rebin_scan, rebin_scan_body)
 PIC_RUN_KERNELS(rebin_finalize, rebin_finalize_body)
 #undef PIC_RUN_KERNELS
+
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void k_rebin_count(const KParams *__restrict__ kp)
+{
+    rebin_count_body<SPLIT>(kp, blockIdx.x);
+}
+__global__ __launch_bounds__(256) void kb_rebin_count(const BatchTable *__restrict__ bt)
+{
+    rebin_count_body<false>(bt->kp[blockIdx.y], blockIdx.x);
+}
 
 template <typename R>
 __global__ __launch_bounds__(256) void k_rebin_count_ovf(const KParams *__restrict__ kp)
@@ -2567,14 +2708,14 @@ __global__ __launch_bounds__(256) void kb_yee_e(const BatchTable *__restrict__ b
     yee_e_body<R, D>(bt->kp[cb.x], cb.y, 0);
 }
 
-__global__ __launch_bounds__(kAdvanceThreads) void k_advance(const KParams *__restrict__ kp)
+__global__ __launch_bounds__(kAdvanceThreads) void k_advance(const KParams *__restrict__ kp, int parts)
 {
-    advance_body(kp, blockIdx.x, gridDim.x);
+    advance_body(kp, parts);
 }
 // one workgroup per run; the first also rewinds the particle-kernel queues
 __global__ __launch_bounds__(kAdvanceThreads) void kb_advance(const BatchTable *__restrict__ bt)
 {
-    advance_body(bt->kp[blockIdx.x], 0, 1);
+    advance_body(bt->kp[blockIdx.x], 1);
     if (blockIdx.x == 0 && threadIdx.x < kBatchGroups * kBatchXcds)
         bt->grp[threadIdx.x / kBatchXcds].queue[threadIdx.x % kBatchXcds] = 0;
 }
@@ -2780,10 +2921,13 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
     L(k_field_diag<R>, dim3(hp.fd_blocks), dim3(256), dp);
     L.grp = 1;
     const unsigned pbk = (unsigned)shape_block(sizeof(R) == 4, hp.shape);
-    if (hp.coulomb) L(particle_kernel<R, A, D, T, true>(hp.shape), dim3(ntiles), dim3(pbk), dp);
+    if (hp.split > 1) {
+        L(hp.coulomb ? k_particle_split<R, A, D, T, true> : k_particle_split<R, A, D, T, false>,
+          dim3((unsigned)(ntiles * hp.split)), dim3(kShapeBlock[0]), dp, hp.split);
+    } else if (hp.coulomb) L(particle_kernel<R, A, D, T, true>(hp.shape), dim3(ntiles), dim3(pbk), dp);
     else L(particle_kernel<R, A, D, T, false>(hp.shape), dim3(ntiles), dim3(pbk), dp);
     L.grp = 2;
-    L(k_rebin_count, dim3(nst), dim3(256), dp);
+    L(hp.split > 1 ? k_rebin_count<true> : k_rebin_count<false>, dim3(nst), dim3(256), dp);
     L(k_rebin_count_ovf<R>, dim3(256), dim3(256), dp);
     L(k_rebin_scan, dim3(hp.nspecies), dim3(256), dp);
     // one workgroup per 8 (species, tile) bins, 1024 to 16384 (the copy
@@ -2808,7 +2952,8 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
           dim3(kBinThreads<R>), dp, width, nblk);
     }
     L.grp = 3;
-    L(k_reduce_j<R, D>, dim3(cb), dim3(256), dp);
+    if (hp.split > 1) L(k_reduce_j_split<R, D>, dim3(cb, 3), dim3(256), dp, hp.split);
+    else L(k_reduce_j<R, D>, dim3(cb), dim3(256), dp);
     if (gauss) {
         L.grp = 0;
         L(k_rho<R, D, T, true>, dim3(ntiles), dim3(256), dp);
@@ -2821,7 +2966,7 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
     L(k_yee_e<R, D>, dim3(cb), dim3(256), dp);
     L(k_yee_b<R, D>, dim3(cb), dim3(256), dp, h);
     L.grp = 5;
-    L(k_advance, dim3(1), dim3(kAdvanceThreads), dp);
+    L(k_advance, dim3(1), dim3(kAdvanceThreads), dp, hp.split);
     return L.dry ? hipSuccess : hipGetLastError();
 }
 

@@ -37,6 +37,8 @@ struct Layout {
     size_t F, J;                                            // field buffer
     size_t Jtile, tile_diag, field_diag, moments, state, kparams, rb[4], order, bucket;   // scratch
     size_t rho_tile, rho0, rho_n, gauss_part, cont_part;    // scratch (Gauss-law and continuity checks)
+    size_t Jsplit = 0, split_cnt = 0, split_diag = 0;                   // scratch (tiles split over workgroups)
+    int split = 1;                                          // workgroups per tile of the particle kernel
     size_t ee_part = 0, ee_off = 0;                         // scratch (binary collisions: pairs and list ends per workgroup)
     size_t ee_ent = 0;                                      // scratch (binary collisions: participants by block of cells)
     int ee_blocks = 0;                                      // workgroups per tile of the binary-collision kernel
@@ -79,7 +81,27 @@ int fail(std::string *err, int code, const char *fmt, ...)
     return code;
 }
 
-int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout *L, std::string *err)
+// Workgroups per tile of the particle kernel.  A grid with few tiles leaves
+// most of the 256 CUs idle, and a heavy tile then finishes long after the
+// others, so its tiles are split into about kSplitGroups workgroups (4 per CU),
+// as long as each has kSplitMin particles.  Measured, particle kernel alone, 1
+// workgroup per tile -> the rule's: 64^2, 16 tiles, 16 + 16 particles per cell
+// 58 -> 16 us (16 per tile); 256^2, 256 tiles, 64 + 64 217 -> 132 us (4);
+// 160^2, 400 tiles, 64 + 64 79 -> 69 us (2).  From 1024 tiles on the split
+// only adds field stages and partial currents (512^2: 422 us unsplit).
+int particle_split(const pic_grid_desc *g, const Geometry &G, int64_t per_tile)
+{
+    if (g->shape != 0) return 1;                             // a shape chosen by the caller is launched as it is
+    int64_t nj = 1;
+    for (int a = 0; a < G.ndim; ++a) nj *= G.tile[a] + 3;
+    int64_t k = kSplitGroups / G.ntiles;
+    k = std::min<int64_t>(k, per_tile / kSplitMin);
+    k = std::min<int64_t>(k, kSplitBytes / (G.ntiles * 3 * nj * 8));
+    return (int)std::max<int64_t>(1, k);
+}
+
+// lean: without the parts of the scratch that a run can do without.
+int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout *L, std::string *err, bool lean = false)
 {
     if (!g || !sp) return fail(err, PIC_E_INVALID_ARG, "null descriptor");
     if (ns < 1 || ns > kMaxSpecies) return fail(err, PIC_E_INVALID_ARG, "nspecies %d out of 1..%d", ns, kMaxSpecies);
@@ -146,7 +168,7 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
     }
     if (used > 32) return fail(err, PIC_E_UNSUPPORTED, "grid too large for the packed 32-bit cell index");
     const int64_t tile_cells = (int64_t)G.tile[0] * G.tile[1] * G.tile[2];
-    int64_t id_total = 0;
+    int64_t id_total = 0, per_tile = 0;
     for (int s = 0; s < ns; ++s) {
         const pic_species_desc &S = sp[s];
         if (S.ppc <= 0) return fail(err, PIC_E_INVALID_ARG, "species %d: ppc %d", s, S.ppc);
@@ -172,7 +194,9 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
             return fail(err, PIC_E_UNSUPPORTED, "species %d: a particle array would exceed 4 GiB", s);
         P.ovf_cap = (uint32_t)std::max<int64_t>(4096, P.ncap / 8);
         id_total += P.nominal;
+        per_tile += P.tile_nominal;
     }
+    L->split = lean ? 1 : particle_split(g, G, per_tile);
     if (id_total > 0xFFFFFFFFll) return fail(err, PIC_E_UNSUPPORTED, "more than 2^32 particles: ids do not fit");
     L->real = g->precision == PIC_PREC_MIXED ? 4 : 8;
     L->nj = G.tile[0] + 3;
@@ -248,6 +272,11 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
         // layout files depend on.
         L->state_bytes = c.off;
         L->kparams = c.take(sizeof(KParams));
+        if (L->split > 1) {
+            L->Jsplit = c.take((size_t)G.ntiles * L->split * 3 * nj_cells * 8);
+            L->split_cnt = c.take((size_t)G.ntiles * ns * 2 * kSplitLine * 4);
+            L->split_diag = c.take((size_t)G.ntiles * L->split * ns * kTileDiag * 8);
+        }
         if (L->ee_blocks) {
             L->ee_part = c.take((size_t)G.ntiles * L->ee_blocks * 4);
             L->ee_off = c.take((size_t)G.ntiles * L->ee_blocks * 4);
@@ -769,6 +798,12 @@ void pic::release_static_scratch(int device)
     g_static_busy[device] = false;
 }
 
+size_t pic::static_scratch_needed(const pic_grid_desc *grid, const pic_species_desc *species, int nspecies)
+{
+    Layout L;
+    return validate(grid, species, nspecies, &L, nullptr, true) == PIC_OK ? L.state_bytes : 0;
+}
+
 int pic::fail_global(int code, const char *fmt, ...)
 {
     char buf[512];
@@ -789,6 +824,12 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
     if (!r) return fail(nullptr, PIC_E_INVALID_ARG, "host allocation failed");
     r->static_device = static_device;
     int rc = validate(grid, species, nspecies, &r->L, &r->err);
+    if (rc == PIC_OK && static_device >= 0 && r->L.scratch_bytes > kStaticScratch) {
+        r->L = Layout();
+        rc = validate(grid, species, nspecies, &r->L, &r->err, true);
+        if (rc == PIC_OK && r->L.scratch_bytes > kStaticScratch)
+            rc = fail(&r->err, PIC_E_BUFFER_TOO_SMALL, "the run needs %zu bytes of scratch", r->L.scratch_bytes);
+    }
     if (rc) { delete r; return rc; }
     for (int s = 0; s < nspecies; ++s)
         if (!buffers->particles[s]) { delete r; return fail(nullptr, PIC_E_INVALID_ARG, "null particle buffer %d", s); }
@@ -865,6 +906,10 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
     K.tile_diag = (double *)at(buffers->scratch, L.tile_diag);
     K.field_diag = (double *)at(buffers->scratch, L.field_diag);
     K.moments = (double *)at(buffers->scratch, L.moments);
+    K.split = L.split;
+    K.Jsplit = L.split > 1 ? at(buffers->scratch, L.Jsplit) : nullptr;
+    K.split_cnt = L.split > 1 ? (uint32_t *)at(buffers->scratch, L.split_cnt) : nullptr;
+    K.split_diag = L.split > 1 ? (double *)at(buffers->scratch, L.split_diag) : nullptr;
     K.state = (DevState *)at(buffers->scratch, L.state);
     K.ring = (pic_diag *)buffers->diag;
     K.rb_count = (int32_t *)at(buffers->scratch, L.rb[0]);
@@ -907,6 +952,7 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
     INIT_CHK(hipMemsetAsync(buffers->fields, 0, L.field_bytes, r->stream));
     INIT_CHK(hipMemsetAsync(K.Jtile, 0, L.tile_diag - L.Jtile, r->stream));
     INIT_CHK(hipMemsetAsync(K.tile_diag, 0, L.state - L.tile_diag, r->stream));
+    if (L.split > 1) INIT_CHK(hipMemsetAsync(K.split_cnt, 0, L.split_diag - L.split_cnt, r->stream));
     INIT_CHK(hipMemsetAsync(buffers->diag, 0, L.diag_bytes, r->stream));
     DevState st0;
     memset(&st0, 0, sizeof(st0));

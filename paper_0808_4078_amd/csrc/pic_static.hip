@@ -17,7 +17,7 @@
 
 namespace {
 
-static __device__ __align__(256) unsigned char scratch[PIC_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[pic::kStaticScratch];
 
 std::mutex g_mu;
 void *g_ptr[pic::kMaxDevices] = {};   // device address of `scratch` on each device
@@ -34,9 +34,10 @@ extern "C" int pic_init_static_scratch(const pic_grid_desc *grid, const pic_spec
     pic_sizes sz;
     int rc = pic_query(grid, species, nspecies, &sz);
     if (rc) return rc;
-    if (sz.scratch_bytes > PIC_STATIC_SCRATCH_BYTES)
+    const size_t need = pic::static_scratch_needed(grid, species, nspecies);
+    if (need > PIC_STATIC_SCRATCH_BYTES)
         return pic::fail_global(PIC_E_BUFFER_TOO_SMALL, "the run needs %zu bytes of scratch; the library holds %zu",
-                                sz.scratch_bytes, (size_t)PIC_STATIC_SCRATCH_BYTES);
+                                need, (size_t)PIC_STATIC_SCRATCH_BYTES);
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return pic::fail_global(PIC_E_HIP, "hipGetDevice: %s", hipGetErrorString(e));
