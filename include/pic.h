@@ -283,7 +283,11 @@ int pic_step(pic_run *run, int32_t nsteps);
  * adds each kernel group's summed kernel milliseconds into group_ms[6]:
  * [0] field diagnostics, [1] particle kernel (gather, push, move, deposit,
  * scattering, binning), [2] store re-layout, [3] current reduction,
- * [4] Yee update, [5] end-of-step bookkeeping.  Synchronising. */
+ * [4] Yee update, [5] end-of-step bookkeeping.  Single runs take several of
+ * these in one launch: in 2D [3] holds the current reduction and the first
+ * half of the Yee update (and the re-layout's counts; on grids of up to 131072
+ * cells also the field diagnostics), [4] the second half (and the re-layout's
+ * copies; with few tiles also the bookkeeping).  Synchronising. */
 int pic_step_profiled(pic_run *run, int32_t nsteps, double *group_ms);
 
 /* Waits for the bound stream; reports device-side capacity failures. */

@@ -125,6 +125,9 @@ struct KParams {
     int32_t *rb_start;   // [nspecies][tiles]
     int32_t *rb_cap;     // [nspecies][tiles]
     int32_t *rb_fill;    // [nspecies][tiles]
+    int32_t *rl_ovf;     // [nspecies][tiles] overflowed particles per new tile (zero between steps)
+    int32_t *rl_ticket;  // [2] workgroups that have ended a re-layout phase (zero between steps)
+    void *Ft;            // 6 planes: E^{n+1} and B^{n+1/2} between the field passes (null: unfused passes)
     int fd_blocks;       // blocks (and partial records) of the field-diagnostic reduction
     int32_t split;       // workgroups per tile of the particle kernel (1, or more where the grid has few tiles)
     void *Jsplit;        // split > 1: [tiles][split][3][nj^ndim] FP64 partial currents
@@ -183,17 +186,13 @@ struct BatchTable {
 constexpr int kBatchRebinBlocks = 256;
 
 // Host-callable launchers (defined in the .hip translation units).
-// Kernels of one step and the group each belongs to: field-diag (0),
-// particle (1), re-layout (2), current reduction (3), Yee (4), advance (5).
+// Groups of a step's kernels: field record and checks (0), particle and binary
+// collisions (1), re-layout launched apart (2), current reduction / first field
+// pass (3), Yee / second field pass (4), end of step (5).  step_kernel_groups
+// fills groups[] with each launch's group and returns the number of launches
+// (at most kMaxStepKernels).
 constexpr int kNumGroups = 6;
-constexpr int kStepKernels = 13;
-constexpr int kKernelGroup[kStepKernels] = {0, 1, 2, 2, 2, 2, 2, 2, 3, 4, 4, 4, 5};
-// A single run's step is kStepKernels launches, plus four with
-// PIC_FLAG_GAUSS_RESIDUAL (the charge deposits and residuals of the Gauss
-// and continuity checks, group 0) and two with binary collisions
-// (group 1).
-// step_kernel_groups fills groups[] with each launch's group and returns the
-// number of launches.
+constexpr int kMaxStepKernels = 16;
 int step_kernel_groups(const KParams &hp, int *groups);
 // Workgroups per tile of the binary-collision kernel, and the cells each
 // takes, for ppc participants per cell.
@@ -201,13 +200,13 @@ int binary_blocks(bool mixed, int64_t tile_cells, int64_t ppc, int *width);
 // Room for the parameter block in the part of the scratch that a checkpoint
 // holds (the block itself lies behind that part).
 constexpr size_t kCkptParamBytes = 3256;
-// ev: NULL, or 2 * kStepKernels events (start/stop of each dispatch)
+// ev: NULL, or two events (start/stop) per launch
 hipError_t launch_step(const KParams &hp, const KParams *dp, hipStream_t s, hipEvent_t *ev = nullptr);
 // Batch step: the particle kernel is one launch per tile group (empty groups
 // launch one workgroup that exits), so a batch step has kBatchKernels
 // dispatches; kBatchKernelGroup maps them to the groups above.
 // pblocks[g]: persistent workgroups of group g's particle launch.
-constexpr int kBatchKernels = kStepKernels + kBatchGroups - 1;
+constexpr int kBatchKernels = 15;
 constexpr int kBatchKernelGroup[kBatchKernels] = {0, 1, 1, 1, 2, 2, 2, 2, 2, 2, 3, 4, 4, 4, 5};
 hipError_t launch_batch_step(int precision, int ndim, const BatchTable &ht, const BatchTable *dt,
                              const int pblocks[kBatchGroups], hipStream_t s, hipEvent_t *ev = nullptr);

@@ -2,20 +2,28 @@
 //
 // One step (gather -> Boris push -> move -> Esirkepov deposit -> scattering ->
 // current reduction -> Yee update) is a fixed sequence of launches:
-//   k_field_diag     FP64 field energies of E^n, B^n on diagnostic steps
-//   k_particle       one workgroup per particle tile: E/B staged in LDS,
+//   k_field_diag     FP64 field energies of E^n, B^n on diagnostic steps (large
+//                    grids; small ones take them in k_mid)
+//   k_particle       one workgroup per particle tile (k_particle_split: several,
+//                    where the grid has few tiles): E/B staged in LDS,
 //                    per-particle gather, push, move, charge-conserving
 //                    deposit into an LDS current tile, scattering, and
 //                    binning of the particle into the next step's store
-//   k_rebin_*        re-layout of the particle store (early exit unless an
-//                    incoming-mover reserve overflowed during the step)
-//   k_reduce_j       fixed-order FP64 sum of the overlapping tile currents
-//   k_yee_b/k_yee_e  B half step, E full step with -J, B half step
+//   k_mid, k_end     the field update in two passes: FP64 sum of the
+//                    overlapping tile currents, B half step and E full step
+//                    with -J; then the second B half step.  They carry the two
+//                    phases of the re-layout of the particle store (idle unless
+//                    an incoming-mover reserve overflowed during the step)
+//   k_binary_list/k_binary (only with binary collisions, after a re-layout
+//                    launched apart) pairing and scattering within each cell
 //   k_rho/k_gauss    (only with PIC_FLAG_GAUSS_RESIDUAL, on diagnostic steps)
 //                    CIC charge of the particles and max |div E - (rho - rho_0)|
 //   k_rho/k_continuity (the same steps, after the current reduction) charge
 //                    after the move and max |rho^{n+1} - rho^n + dt div J|
-//   k_advance        diagnostic record, counter reset, step/parity update
+//   k_advance        diagnostic record, counter reset, step/parity update (with
+//                    few tiles one workgroup of k_end)
+// Ensembles, and runs without room for the second set of field planes, take
+// the passes one by one (rebin_*, reduce_j, yee_b, yee_e, yee_b).
 //
 // The numerical scheme is the relativistic Boris push (Boris 1970), the
 // Esirkepov (2001) charge-conserving deposit with the linear form factor and
@@ -209,6 +217,37 @@ __device__ __forceinline__ void block_sum(double (&v)[N], double (*sred)[N])
 }
 
 // ---------------------------------------------------------------------------
+// Adds node o's terms of the field record to a[9]: F_i^2 per component and
+// E x B per axis.
+template <typename R>
+__device__ __forceinline__ void field_record_node(const KParams *__restrict__ kp, const R *F, int64_t o, double (&a)[9])
+{
+    const int64_t cells = kp->g.cells;
+    const int nx = kp->g.n[0], ny = kp->g.n[1];
+    const int64_t nxy = (int64_t)nx * ny;
+    double v[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+        v[c] = (double)F[c * cells + o];
+        a[c] += v[c] * v[c];
+    }
+    // E x B with each product at its E component's point: B averaged over
+    // the two points around it along the axis where the staggers differ
+    const int i = (int)(o % nx), j = (int)((o / nx) % ny);
+    const int64_t mi = i ? o - 1 : o + nx - 1;                 // i-1
+    const int64_t mj = j ? o - nx : o + nxy - nx;              // j-1
+    const int64_t mk = o >= nxy ? o - nxy : o + cells - nxy;   // k-1 (2D: the same cell)
+    const double bz_i = 0.5 * (v[5] + (double)F[5 * cells + mi]);
+    const double by_i = 0.5 * (v[4] + (double)F[4 * cells + mi]);
+    const double bx_j = 0.5 * (v[3] + (double)F[3 * cells + mj]);
+    const double bz_j = 0.5 * (v[5] + (double)F[5 * cells + mj]);
+    const double by_k = 0.5 * (v[4] + (double)F[4 * cells + mk]);
+    const double bx_k = 0.5 * (v[3] + (double)F[3 * cells + mk]);
+    a[6] += v[1] * bz_i - v[2] * by_i;
+    a[7] += v[2] * bx_j - v[0] * bz_j;
+    a[8] += v[0] * by_k - v[1] * bx_k;
+}
+
 // Field energies W_i = sum F_i^2 dV and z field momentum of E^n, B^n.
 template <typename R>
 __device__ __forceinline__ void field_diag_body(const KParams *__restrict__ kp, int bid, int nb)
@@ -218,31 +257,9 @@ __device__ __forceinline__ void field_diag_body(const KParams *__restrict__ kp, 
     if (!diag_step(kp, step)) return;
     const R *F = (const R *)kp->F;
     const int64_t cells = kp->g.cells;
-    const int nx = kp->g.n[0], ny = kp->g.n[1];
-    const int64_t nxy = (int64_t)nx * ny;
     double a[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     for (int64_t o = (int64_t)bid * 256 + threadIdx.x; o < cells; o += (int64_t)nb * 256) {
-        double v[6];
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            v[c] = (double)F[c * cells + o];
-            a[c] += v[c] * v[c];
-        }
-        // E x B with each product at its E component's point: B averaged over
-        // the two points around it along the axis where the staggers differ
-        const int i = (int)(o % nx), j = (int)((o / nx) % ny);
-        const int64_t mi = i ? o - 1 : o + nx - 1;                 // i-1
-        const int64_t mj = j ? o - nx : o + nxy - nx;              // j-1
-        const int64_t mk = o >= nxy ? o - nxy : o + cells - nxy;   // k-1 (2D: the same cell)
-        const double bz_i = 0.5 * (v[5] + (double)F[5 * cells + mi]);
-        const double by_i = 0.5 * (v[4] + (double)F[4 * cells + mi]);
-        const double bx_j = 0.5 * (v[3] + (double)F[3 * cells + mj]);
-        const double bz_j = 0.5 * (v[5] + (double)F[5 * cells + mj]);
-        const double by_k = 0.5 * (v[4] + (double)F[4 * cells + mk]);
-        const double bx_k = 0.5 * (v[3] + (double)F[3 * cells + mk]);
-        a[6] += v[1] * bz_i - v[2] * by_i;
-        a[7] += v[2] * bx_j - v[0] * bz_j;
-        a[8] += v[0] * by_k - v[1] * bx_k;
+        field_record_node(kp, F, o, a);
     }
     block_sum<9>(a, sred);
     if (threadIdx.x == 0)
@@ -497,6 +514,7 @@ __device__ __forceinline__ void deposit_face(A *sJ, const int (&lc)[3], const R 
 template <int D> constexpr int kQueue = D == 3 ? 192 : 128;
 constexpr int kOrderBuckets = 64;
 constexpr int kAdvanceThreads = 1024;    // workgroup size of the end-of-step kernel (one workgroup per run)
+constexpr int kAdvanceTiles = 2048;      // partial records up to which the end of the step joins the field pass
 constexpr int kXcds = kBatchXcds;        // accelerator dies (XCDs), each with its own L2
 
 // Movers staged per wave in mixed mode before they are written, grouped by
@@ -1176,13 +1194,11 @@ __device__ __forceinline__ void particle_body(KP kp, int tile, int part, int par
 // SPLIT: first the split tiles' counters become the bins' counts (every step)
 // and start over.
 template <bool SPLIT>
-__device__ __forceinline__ void rebin_count_body(const KParams *__restrict__ kp, int bid)
+__device__ __forceinline__ void rebin_count_bin(const KParams *__restrict__ kp, int64_t i)
 {
     const DevState *st = kp->state;
     if (!SPLIT && !st->rebin) return;
     const int ntiles = kp->g.ntiles;
-    const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)kp->nspecies * ntiles) return;
     const int s = (int)(i / ntiles), t = (int)(i % ntiles);
     const SpeciesDev &S = kp->sp[s];
     const int src = st->par, dst = src ^ 1;
@@ -1198,6 +1214,12 @@ __device__ __forceinline__ void rebin_count_body(const KParams *__restrict__ kp,
     const int32_t c = (int32_t)(S.cnt_front[dst * ntiles + t] + vb);
     kp->rb_count[i] = c;
     kp->rb_fill[i] = c;
+}
+
+__device__ __forceinline__ void rebin_count_body(const KParams *__restrict__ kp, int bid, int nb)
+{
+    const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
+    if (i < (int64_t)kp->nspecies * kp->g.ntiles) rebin_count_bin<false>(kp, i);
 }
 
 template <typename R>
@@ -2101,13 +2123,11 @@ __device__ __forceinline__ void rebin_scatter_ovf_body(const KParams *__restrict
     }
 }
 
-__device__ __forceinline__ void rebin_finalize_body(const KParams *__restrict__ kp, int bid, int nb)
+__device__ __forceinline__ void rebin_finalize_bin(const KParams *__restrict__ kp, int64_t i)
 {
     const DevState *st = kp->state;
     if (!st->rebin || (st->fatal & 4)) return;
     const int ntiles = kp->g.ntiles;
-    const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)kp->nspecies * ntiles) return;
     const int s = (int)(i / ntiles), t = (int)(i % ntiles);
     const SpeciesDev &S = kp->sp[s];
     const int src = st->par, dst = src ^ 1;
@@ -2116,6 +2136,83 @@ __device__ __forceinline__ void rebin_finalize_body(const KParams *__restrict__ 
     S.cnt_front[src * ntiles + t] = (uint32_t)kp->rb_count[i];
     S.cnt_back[src * ntiles + t] = 0;
     S.cnt_back[dst * ntiles + t] = 0;
+}
+
+__device__ __forceinline__ void rebin_finalize_body(const KParams *__restrict__ kp, int bid, int nb)
+{
+    const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
+    if (i < (int64_t)kp->nspecies * kp->g.ntiles) rebin_finalize_bin(kp, i);
+}
+
+// A single run's re-layout in two phases, each the work of some workgroups of
+// the two field kernels (k_mid, k_end) -- or of a launch of its own where
+// something must run between them -- so that a step without an overflow pays
+// for no launch of it.  A phase ends in its last workgroup to arrive:
+//   relayout_count    counts of the bins and of the overflow list, then the
+//                     scan of the new bins;
+//   relayout_scatter  copies, then the new bins take effect.
+// `nb` workgroups, bid among them.  Returns true in the workgroup that ended
+// the second phase.
+//
+// DATA: the last workgroup reads what the others stored (a fence on both sides;
+// on this device a release writes back the L2).  Without it the arrival only
+// says that a workgroup has read the old bins for the last time, which its
+// copies' addresses depended on.
+template <bool DATA>
+__device__ __forceinline__ bool last_to_arrive(const KParams *__restrict__ kp, int which, int nb)
+{
+    __shared__ int s_last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (DATA) __threadfence();
+        const int n = __hip_atomic_fetch_add(&kp->rl_ticket[which], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = n == nb - 1;
+        if (s_last) kp->rl_ticket[which] = 0;
+        if (DATA) __threadfence();
+    }
+    __syncthreads();
+    return s_last != 0;
+}
+
+template <typename R, bool SPLIT>
+__device__ __forceinline__ void relayout_count(const KParams *__restrict__ kp, int bid, int nb)
+{
+    const DevState *st = kp->state;
+    const int ntiles = kp->g.ntiles;
+    const int64_t nbins = (int64_t)kp->nspecies * ntiles;
+    for (int64_t i = (int64_t)bid * blockDim.x + threadIdx.x; i < nbins; i += (int64_t)nb * blockDim.x)
+        rebin_count_bin<SPLIT>(kp, i);
+    if (!st->rebin) return;
+    const int64_t i0 = (int64_t)bid * blockDim.x + threadIdx.x;
+    for (int s = 0; s < kp->nspecies; ++s) {
+        const SpeciesDev &S = kp->sp[s];
+        const int64_t n = min((int64_t)st->ovf_count[s], (int64_t)S.ovf_cap);
+        for (int64_t p = i0; p < n; p += (int64_t)nb * blockDim.x)
+            atomicAdd(&kp->rl_ovf[(int64_t)s * ntiles + tile_of<R>(kp, S, 2, p)], 1);
+    }
+    if (!last_to_arrive<true>(kp, 0, nb)) return;
+    for (int64_t i = threadIdx.x; i < nbins; i += blockDim.x) {
+        kp->rb_count[i] += kp->rl_ovf[i];
+        kp->rl_ovf[i] = 0;
+    }
+    __syncthreads();
+    for (int s = 0; s < kp->nspecies; ++s) {
+        rebin_scan_body(kp, s, 0);
+        __syncthreads();
+    }
+}
+
+template <typename R>
+__device__ __forceinline__ bool relayout_scatter(const KParams *__restrict__ kp, int bid, int nb)
+{
+    if (!kp->state->rebin) return false;
+    rebin_scatter_body<R>(kp, bid, nb);
+    rebin_scatter_ovf_body<R>(kp, bid, nb);
+    if (!last_to_arrive<false>(kp, 1, nb)) return false;
+    const int64_t nbins = (int64_t)kp->nspecies * kp->g.ntiles;
+    for (int64_t i = threadIdx.x; i < nbins; i += blockDim.x) rebin_finalize_bin(kp, i);
+    __syncthreads();
+    return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -2130,60 +2227,89 @@ __device__ __forceinline__ void rebin_finalize_body(const KParams *__restrict__ 
 // each axis are workgroup-uniform; per node and axis only the choice among
 // them (and the local index) varies, and a partial's offset is the sum of
 // one term per axis.
-// Split tiles: the `parts` FP64 partials of a tile lie one after the other
-// (`pstride` apart).  A tile's partials are summed in order and rounded to the
-// run's precision, as a tile that is not split rounds its LDS sums, and the
-// tiles are then summed in the same order as there: in mixed precision, where
-// the FP64 sums of FP32 terms are exact, the current does not depend on the
-// split.  One thread per node and component, since a small grid has few nodes.
-template <typename R, int D>
-__global__ __launch_bounds__(256) void k_reduce_j_split(const KParams *__restrict__ kp, int parts)
+// The tiles that hold node `i` of an axis, in increasing order of the sum: the
+// one below (local index r + 1 + T) and the node's own (r + 1) when r <= 1,
+// the own and the one above (local 0) when r = T - 1, else the own alone;
+// returns how many (tiles are at least 8 cells, so at most two).
+__device__ __forceinline__ int node_tiles(int i, int T, int nt, int (&ct)[2], int (&cl)[2])
 {
-    const int64_t cells = kp->g.cells;
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (q >= cells) return;
-    const int comp = blockIdx.y;
+    const int tb = i / T, r = i - tb * T;
+    if (r <= 1) {
+        ct[0] = tb == 0 ? nt - 1 : tb - 1;
+        cl[0] = r + 1 + T;
+        ct[1] = tb;
+        cl[1] = r + 1;
+        return 2;
+    }
+    ct[0] = tb;
+    cl[0] = r + 1;
+    ct[1] = tb + 1 == nt ? 0 : tb + 1;
+    cl[1] = 0;
+    return r == T - 1 ? 2 : 1;
+}
+
+// Grid current of one node from the tile partials, FP64, tiles in a fixed
+// order.  SPLIT: the `parts` FP64 partials of a tile lie one after the other;
+// they are summed in order and rounded to the run's precision, as a tile that
+// is not split rounds its LDS sums: in mixed precision, where the FP64 sums of
+// FP32 terms are exact, the current does not depend on the split.
+template <typename R, int D, bool SPLIT>
+__device__ __forceinline__ void node_current(const KParams *__restrict__ kp, const int (&idx)[3], double (&j)[3])
+{
     const int T = kp->g.tile[0], NJ = T + 3;
-    const int NJ_D = D == 3 ? NJ * NJ * NJ : NJ * NJ;
-    const int n[3] = {kp->g.n[0], kp->g.n[1], kp->g.n[2]};
-    const int idx[3] = {(int)(q % n[0]), (int)((q / n[0]) % n[1]), D == 3 ? (int)(q / ((int64_t)n[0] * n[1])) : 0};
+    const int64_t NJ_D = D == 3 ? (int64_t)NJ * NJ * NJ : (int64_t)NJ * NJ;
     int cn[3] = {1, 1, 1}, ct[3][2] = {}, cl[3][2] = {};
 #pragma unroll
-    for (int a = 0; a < D; ++a) {
-        const int tb = idx[a] / T, r = idx[a] - tb * T, nt = kp->g.nt[a];
-        if (r <= 1) {
-            ct[a][0] = tb == 0 ? nt - 1 : tb - 1;
-            cl[a][0] = r + 1 + T;
-            ct[a][1] = tb;
-            cl[a][1] = r + 1;
-            cn[a] = 2;
-        } else {
-            ct[a][0] = tb;
-            cl[a][0] = r + 1;
-            ct[a][1] = tb + 1 == nt ? 0 : tb + 1;
-            cl[a][1] = 0;
-            cn[a] = r == T - 1 ? 2 : 1;
-        }
-    }
-    const GLB double *Js = gbl((const double *)kp->Jsplit) + (int64_t)comp * NJ_D;
-    const int64_t pstride = 3 * (int64_t)NJ_D;
-    double j = 0.0;
-    for (int iz = 0; iz < cn[2]; ++iz)
-        for (int iy = 0; iy < cn[1]; ++iy)
-            for (int ix = 0; ix < cn[0]; ++ix) {
-                const int64_t t = ((int64_t)ct[2][iz] * kp->g.nt[1] + ct[1][iy]) * kp->g.nt[0] + ct[0][ix];
-                const GLB double *p = Js + t * parts * pstride + ((int64_t)cl[2][iz] * NJ + cl[1][iy]) * NJ + cl[0][ix];
-                double sum = 0.0;
-                for (int k0 = 0; k0 < parts; k0 += 8) {
-                    double v[8];
+    for (int a = 0; a < D; ++a) cn[a] = node_tiles(idx[a], T, kp->g.nt[a], ct[a], cl[a]);
+    constexpr int NK = D == 3 ? 8 : 4;
+    auto offset = [&](int k) {
+        const int iz = k >> 2, iy = (k >> 1) & 1, ix = k & 1;
+        const int64_t t = ((int64_t)ct[2][iz] * kp->g.nt[1] + ct[1][iy]) * kp->g.nt[0] + ct[0][ix];
+        const int64_t l = ((int64_t)cl[2][iz] * NJ + cl[1][iy]) * NJ + cl[0][ix];
+        return t * (SPLIT ? kp->split : 1) * 3 * NJ_D + l;
+    };
+    auto has = [&](int k) { return (k >> 2) < cn[2] && ((k >> 1) & 1) < cn[1] && (k & 1) < cn[0]; };
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) v[k] = k0 + k < parts ? p[(k0 + k) * pstride] : 0.0;
+    for (int c = 0; c < 3; ++c) j[c] = 0.0;
+    if constexpr (SPLIT) {
+        const GLB double *Js = gbl((const double *)kp->Jsplit);
+        const int parts = kp->split;
+        for (int k = 0; k < NK; ++k) {
+            if (!has(k)) continue;
+            const GLB double *p = Js + offset(k);
+            double sum[3] = {0.0, 0.0, 0.0};
+            for (int q0 = 0; q0 < parts; q0 += 8) {
+                double v[8][3];
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) sum += v[k];
-                }
-                j += (double)R(sum);
+                for (int q = 0; q < 8; ++q)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) v[q][c] = q0 + q < parts ? p[((q0 + q) * 3 + c) * NJ_D] : 0.0;
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) sum[c] += v[q][c];
             }
-    kp->J[(int64_t)comp * cells + q] = j;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) j[c] += (double)R(sum[c]);
+        }
+    } else {
+        // all of a node's partials are loaded first and then summed
+        const GLB R *Jt = gbl((const R *)kp->Jtile);
+        R v[NK][3];
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            v[k][0] = v[k][1] = v[k][2] = R(0);
+            if (has(k)) {
+                const GLB R *p = Jt + offset(k);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) v[k][c] = p[c * NJ_D];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) j[c] += (double)v[k][c];
+    }
 }
 
 template <typename R>
@@ -2246,81 +2372,23 @@ __device__ __forceinline__ void reduce_j_tile3(const KParams *__restrict__ kp, i
     J[2 * cells + o] = jz;
 }
 
-template <typename R, int D>
-__device__ __forceinline__ void reduce_j_body(const KParams *__restrict__ kp, int bid, int nb)
+template <typename R, int D, bool SPLIT>
+__device__ __forceinline__ void reduce_j_body(const KParams *__restrict__ kp, int bid)
 {
-    if constexpr (D == 3) {
+    if constexpr (D == 3 && !SPLIT) {
         reduce_j_tile3<R>(kp, bid);
         return;
     }
-    // 2D: one node per thread in grid row order
+    // one node per thread in grid row order
     const int64_t cells = kp->g.cells;
-    const int64_t q = (int64_t)bid * blockDim.x + threadIdx.x;
-    if (q >= cells) return;
+    const int64_t o = (int64_t)bid * blockDim.x + threadIdx.x;
+    if (o >= cells) return;
     const int nx = kp->g.n[0], ny = kp->g.n[1];
-    const int T = kp->g.tile[0];
-    int idx[3];
-    const int64_t o = q;
-    idx[0] = (int)(q % nx);
-    idx[1] = (int)((q / nx) % ny);
-    idx[2] = 0;
-    const int NJ = kp->nj;
-    const int64_t NJ_D = (int64_t)NJ * NJ;
-    int tb[3], r[3];
-    for (int a = 0; a < 3; ++a) {
-        tb[a] = idx[a] / T;
-        r[a] = idx[a] - tb[a] * T;
-    }
-    const GLB R *Jt = gbl((const R *)kp->Jtile);
-    // Per axis the tiles holding the node, in increasing tile order: the one
-    // below (local index r + 1 + T) when r <= 1, the node's own tile (r + 1),
-    // the one above (local 0) when r = T - 1; tiles are at least 8 cells, so
-    // at most two per axis.  All of a node's partials are loaded first and
-    // then summed in that fixed order.
-    int cn[3], ct[3][2], cl[3][2];
-    for (int a = 0; a < 3; ++a) {
-        cn[a] = 0;
-        if (a < D) {
-            const int ntile = kp->g.nt[a];
-            if (r[a] <= 1) {
-                ct[a][cn[a]] = tb[a] == 0 ? ntile - 1 : tb[a] - 1;
-                cl[a][cn[a]++] = r[a] + 1 + T;
-            }
-            ct[a][cn[a]] = tb[a];
-            cl[a][cn[a]++] = r[a] + 1;
-            if (r[a] == T - 1 && cn[a] < 2) {
-                ct[a][cn[a]] = tb[a] + 1 == ntile ? 0 : tb[a] + 1;
-                cl[a][cn[a]++] = 0;
-            }
-        } else {
-            ct[a][0] = 0;
-            cl[a][0] = 0;
-            cn[a] = 1;
-        }
-    }
-    R vx[8], vy[8], vz[8];
+    const int idx[3] = {(int)(o % nx), (int)((o / nx) % ny), D == 3 ? (int)(o / ((int64_t)nx * ny)) : 0};
+    double j[3];
+    node_current<R, D, SPLIT>(kp, idx, j);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int iz = k >> 2, iy = (k >> 1) & 1, ix = k & 1;
-        vx[k] = vy[k] = vz[k] = R(0);
-        if (iz < cn[2] && iy < cn[1] && ix < cn[0]) {
-            const int64_t t = ((int64_t)ct[2][iz] * kp->g.nt[1] + ct[1][iy]) * kp->g.nt[0] + ct[0][ix];
-            const GLB R *p = Jt + t * 3 * NJ_D + ((int64_t)cl[2][iz] * NJ + cl[1][iy]) * NJ + cl[0][ix];
-            vx[k] = p[0];
-            vy[k] = p[NJ_D];
-            vz[k] = p[2 * NJ_D];
-        }
-    }
-    double jx = 0.0, jy = 0.0, jz = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        jx += (double)vx[k];
-        jy += (double)vy[k];
-        jz += (double)vz[k];
-    }
-    kp->J[o] = jx;
-    kp->J[cells + o] = jy;
-    kp->J[2 * cells + o] = jz;
+    for (int c = 0; c < 3; ++c) kp->J[c * cells + o] = j[c];
 }
 
 // ---------------------------------------------------------------------------
@@ -2402,10 +2470,147 @@ __device__ __forceinline__ void yee_e_body(const KParams *__restrict__ kp, int b
     Ez[o] = ez;
 }
 
+// The field update of a step in two passes instead of four (current
+// reduction, B half step, E step, B half step), each over the grid once:
+//   field_mid  J of the node from the tile partials, B^{n+1/2} and E^{n+1},
+//              the B^{n+1/2} of the neighbours recomputed from E^n and B^n
+//              (cached) instead of read back after a launch; written to Ft,
+//              since the neighbours still read E^n and B^n;
+//   field_end  B^{n+1} = B^{n+1/2} - (dt/2) curl E^{n+1}, and E^{n+1} in place.
+// The arithmetic is that of yee_b_body and yee_e_body.  Per step, launches and
+// all: 64^2 FP64 54 -> 25 us, 160^2 47 -> 13 us, 1024^2 94 -> 64 us.  Large 3D
+// grids keep the four passes: the recomputed neighbours lie in other planes,
+// and the tile partials are read in tile order there (256x256x512: 1.53 ms
+// against 2.0 ms fused).
+template <typename R, int D>
+struct YeeGrid {
+    const R *E, *B;           // three planes each
+    int64_t cells, nxy;
+    int n[3];
+    R c[3];                   // dt / (2 d) per axis
+
+    __device__ __forceinline__ int64_t up(int64_t o, int i, int a) const
+    {
+        const int64_t st = a == 0 ? 1 : a == 1 ? n[0] : nxy;
+        return i + 1 < n[a] ? o + st : o + st - st * n[a];
+    }
+    __device__ __forceinline__ int64_t down(int64_t o, int i, int a) const
+    {
+        const int64_t st = a == 0 ? 1 : a == 1 ? n[0] : nxy;
+        return i > 0 ? o - st : o - st + st * n[a];
+    }
+    // component `a` of B^{n+1/2} on node o = (i, j, k)
+    __device__ __forceinline__ R half_b(int a, int64_t o, int i, int j, int k) const
+    {
+        const R *Ex = E, *Ey = E + cells, *Ez = E + 2 * cells;
+        if (a == 0) {
+            R b = B[o] - c[1] * (Ez[up(o, j, 1)] - Ez[o]);
+            if constexpr (D == 3) b += c[2] * (Ey[up(o, k, 2)] - Ey[o]);
+            return b;
+        }
+        if (a == 1) {
+            R b = B[cells + o] + c[0] * (Ez[up(o, i, 0)] - Ez[o]);
+            if constexpr (D == 3) b -= c[2] * (Ex[up(o, k, 2)] - Ex[o]);
+            return b;
+        }
+        return B[2 * cells + o] - (c[0] * (Ey[up(o, i, 0)] - Ey[o]) - c[1] * (Ex[up(o, j, 1)] - Ex[o]));
+    }
+};
+
+template <typename R, int D>
+__device__ __forceinline__ YeeGrid<R, D> yee_grid(const KParams *__restrict__ kp, const R *E, const R *B)
+{
+    YeeGrid<R, D> y;
+    y.E = E;
+    y.B = B;
+    y.cells = kp->g.cells;
+    y.nxy = (int64_t)kp->g.n[0] * kp->g.n[1];
+    const double hdt = 0.5 * kp->g.dt;
+    for (int a = 0; a < 3; ++a) {
+        y.n[a] = kp->g.n[a];
+        y.c[a] = R(hdt / kp->g.d[a]);
+    }
+    return y;
+}
+
+// DIAG: on diagnostic steps the block's partial sums of the field record
+// (field_diag_body) of its 256 nodes.
+template <typename R, int D, bool SPLIT, bool DIAG>
+__device__ __forceinline__ void field_mid(const KParams *__restrict__ kp, int bid)
+{
+    const int64_t cells = kp->g.cells;
+    const int64_t o = (int64_t)bid * 256 + threadIdx.x;
+    const int nx = kp->g.n[0], ny = kp->g.n[1];
+    if (DIAG) {
+        __shared__ double sred[4][9];
+        if (diag_step(kp, uniform_step(kp))) {
+            double a[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+            if (o < cells) field_record_node(kp, (const R *)kp->F, o, a);
+            block_sum<9>(a, sred);
+            if (threadIdx.x == 0)
+                for (int c = 0; c < 9; ++c) kp->field_diag[bid * kFieldDiag + c] = a[c];
+        }
+    }
+    if (o >= cells) return;
+    const int i = (int)(o % nx), j = (int)((o / nx) % ny), k = D == 3 ? (int)(o / ((int64_t)nx * ny)) : 0;
+    const int idx[3] = {i, j, k};
+    double J[3];
+    node_current<R, D, SPLIT>(kp, idx, J);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) kp->J[c * cells + o] = J[c];
+    if (kp->flags & PIC_FLAG_FREEZE_FIELDS) return;
+    const R *F = (const R *)kp->F;
+    const YeeGrid<R, D> y = yee_grid<R, D>(kp, F, F + 3 * cells);
+    const R bx = y.half_b(0, o, i, j, k), by = y.half_b(1, o, i, j, k), bz = y.half_b(2, o, i, j, k);
+    const int im = i > 0 ? i - 1 : nx - 1, jm = j > 0 ? j - 1 : ny - 1;
+    const int64_t oi = y.down(o, i, 0), oj = y.down(o, j, 1);
+    const double dt = kp->g.dt;
+    const R cx = R(dt / kp->g.d[0]), cy = R(dt / kp->g.d[1]);
+    const R rdt = R(dt);
+    R ex = F[o] + cy * (bz - y.half_b(2, oj, i, jm, k)) - rdt * R(J[0]);
+    R ey = F[cells + o] - cx * (bz - y.half_b(2, oi, im, j, k)) - rdt * R(J[1]);
+    R ez = F[2 * cells + o] + cx * (by - y.half_b(1, oi, im, j, k)) - cy * (bx - y.half_b(0, oj, i, jm, k)) -
+           rdt * R(J[2]);
+    if constexpr (D == 3) {
+        const int km = k > 0 ? k - 1 : kp->g.n[2] - 1;
+        const int64_t ok = y.down(o, k, 2);
+        const R cz = R(dt / kp->g.d[2]);
+        ex -= cz * (by - y.half_b(1, ok, i, j, km));
+        ey += cz * (bx - y.half_b(0, ok, i, j, km));
+    }
+    R *Ft = (R *)kp->Ft;
+    Ft[o] = ex;
+    Ft[cells + o] = ey;
+    Ft[2 * cells + o] = ez;
+    Ft[3 * cells + o] = bx;
+    Ft[4 * cells + o] = by;
+    Ft[5 * cells + o] = bz;
+}
+
+template <typename R, int D>
+__device__ __forceinline__ void field_end(const KParams *__restrict__ kp, int bid)
+{
+    if (kp->flags & PIC_FLAG_FREEZE_FIELDS) return;
+    const int64_t cells = kp->g.cells;
+    const int64_t o = (int64_t)bid * 256 + threadIdx.x;
+    if (o >= cells) return;
+    const int nx = kp->g.n[0], ny = kp->g.n[1];
+    const int i = (int)(o % nx), j = (int)((o / nx) % ny), k = D == 3 ? (int)(o / ((int64_t)nx * ny)) : 0;
+    const R *Ft = (const R *)kp->Ft;
+    const YeeGrid<R, D> y = yee_grid<R, D>(kp, Ft, Ft + 3 * cells);
+    R *F = (R *)kp->F;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        F[c * cells + o] = Ft[c * cells + o];
+        F[(3 + c) * cells + o] = y.half_b(c, o, i, j, k);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // End of step: diagnostic record, reset of the next destination's mover
 // counters, step and parity update.  One workgroup.
-__device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int parts)
+// parts: workgroups per tile of the particle kernel; nfd: partials of the field record.
+__device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int parts, int nfd)
 {
     __shared__ double sred[kAdvanceThreads / 64][10];
     DevState *st = kp->state;
@@ -2417,10 +2622,10 @@ __device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int
     if (diag_step(kp, step)) {
         const double dv = kp->g.d[0] * kp->g.d[1] * (kp->g.ndim == 3 ? kp->g.d[2] : 1.0);
         double f[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int b = threadIdx.x; b < kp->fd_blocks; b += blockDim.x)
+        for (int b = threadIdx.x; b < nfd; b += blockDim.x)
             for (int c = 0; c < 9; ++c) f[c] += kp->field_diag[b * kFieldDiag + c];
         block_sum<10>(f, sred);
-        pic_diag rec;
+        pic_diag &rec = kp->ring[st->ring_head % kRing];    // written by thread 0
         if (threadIdx.x == 0) {
             for (int c = 0; c < 6; ++c) rec.W[c] = f[c] * dv;
             for (int c = 0; c < 3; ++c) rec.p_field[c] = f[6 + c] * dv;
@@ -2495,7 +2700,6 @@ __device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int
             rec.step = step;
             rec.time = (double)step * kp->g.dt;
             rec.rebins = st->rebins;
-            kp->ring[st->ring_head % kRing] = rec;
         }
     }
     if (!rebin) {
@@ -2619,43 +2823,46 @@ __global__ __launch_bounds__(kShapeBlock[SH]) void kb_particle(const BatchTable 
     }
 }
 
-#define PIC_RUN_KERNELS(NAME, BODY)                                                     \
-    __global__ __launch_bounds__(256) void k_##NAME(const KParams *__restrict__ kp)    \
-    {                                                                                   \
-        BODY(kp, blockIdx.x, gridDim.x);                                                \
-    }                                                                                   \
+// The two field passes of a single run, with the two phases of its re-layout:
+// workgroups [0, nf) take 256 nodes each, the nr after them the re-layout
+// phase (nf or nr may be 0).  k_mid, DIAG: also the field record's partials.
+// k_end, ADV: also the end of the step -- by its first workgroup, whose work
+// touches nothing that the others read, or, in a step with a re-layout, by the
+// workgroup that ended it.
+template <typename R, int D, bool SPLIT, bool DIAG>
+__global__ __launch_bounds__(256) void k_mid(const KParams *__restrict__ kp, int nf, int nr)
+{
+    const int b = blockIdx.x;
+    if (b < nf) field_mid<R, D, SPLIT, DIAG>(kp, b);
+    else relayout_count<R, SPLIT>(kp, b - nf, nr);
+}
+template <typename R, int D, bool ADV>
+__global__ __launch_bounds__(256) void k_end(const KParams *__restrict__ kp, int nf, int nr, int nfd)
+{
+    const int b = ADV ? (int)blockIdx.x - 1 : (int)blockIdx.x;
+    if (ADV && b < 0) {
+        if (!kp->state->rebin) advance_body(kp, kp->split, nfd);
+    } else if (b < nf) {
+        field_end<R, D>(kp, b);
+    } else if (relayout_scatter<R>(kp, b - nf, nr)) {
+        if constexpr (ADV) advance_body(kp, kp->split, nfd);
+    }
+}
+
+#define PIC_BATCH_KERNEL(NAME, BODY)                                                    \
     __global__ __launch_bounds__(256) void kb_##NAME(const BatchTable *__restrict__ bt) \
     {                                                                                   \
         BODY(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);                                \
     }
-PIC_RUN_KERNELS(rebin_scan, rebin_scan_body)
-PIC_RUN_KERNELS(rebin_finalize, rebin_finalize_body)
-#undef PIC_RUN_KERNELS
+PIC_BATCH_KERNEL(rebin_count, rebin_count_body)
+PIC_BATCH_KERNEL(rebin_scan, rebin_scan_body)
+PIC_BATCH_KERNEL(rebin_finalize, rebin_finalize_body)
+#undef PIC_BATCH_KERNEL
 
-template <bool SPLIT>
-__global__ __launch_bounds__(256) void k_rebin_count(const KParams *__restrict__ kp)
-{
-    rebin_count_body<SPLIT>(kp, blockIdx.x);
-}
-__global__ __launch_bounds__(256) void kb_rebin_count(const BatchTable *__restrict__ bt)
-{
-    rebin_count_body<false>(bt->kp[blockIdx.y], blockIdx.x);
-}
-
-template <typename R>
-__global__ __launch_bounds__(256) void k_rebin_count_ovf(const KParams *__restrict__ kp)
-{
-    rebin_count_ovf_body<R>(kp, blockIdx.x, gridDim.x);
-}
 template <typename R>
 __global__ __launch_bounds__(256) void kb_rebin_count_ovf(const BatchTable *__restrict__ bt)
 {
     rebin_count_ovf_body<R>(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);
-}
-template <typename R>
-__global__ __launch_bounds__(256) void k_rebin_scatter(const KParams *__restrict__ kp)
-{
-    rebin_scatter_body<R>(kp, blockIdx.x, gridDim.x);
 }
 template <typename R>
 __global__ __launch_bounds__(256) void kb_rebin_scatter(const BatchTable *__restrict__ bt)
@@ -2663,26 +2870,21 @@ __global__ __launch_bounds__(256) void kb_rebin_scatter(const BatchTable *__rest
     rebin_scatter_body<R>(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);
 }
 template <typename R>
-__global__ __launch_bounds__(256) void k_rebin_scatter_ovf(const KParams *__restrict__ kp)
-{
-    rebin_scatter_ovf_body<R>(kp, blockIdx.x, gridDim.x);
-}
-template <typename R>
 __global__ __launch_bounds__(256) void kb_rebin_scatter_ovf(const BatchTable *__restrict__ bt)
 {
     rebin_scatter_ovf_body<R>(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);
 }
 
-template <typename R, int D>
+template <typename R, int D, bool SPLIT>
 __global__ __launch_bounds__(256) void k_reduce_j(const KParams *__restrict__ kp)
 {
-    reduce_j_body<R, D>(kp, D == 3 ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x, gridDim.x);
+    reduce_j_body<R, D, SPLIT>(kp, D == 3 && !SPLIT ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
 }
 template <typename R, int D>
 __global__ __launch_bounds__(256) void kb_reduce_j(const BatchTable *__restrict__ bt)
 {
     const int2 cb = bt->cell_blocks[blockIdx.x];
-    reduce_j_body<R, D>(bt->kp[cb.x], cb.y, 0);
+    reduce_j_body<R, D, false>(bt->kp[cb.x], cb.y);
 }
 template <typename R, int D>
 __global__ __launch_bounds__(256) void k_yee_b(const KParams *__restrict__ kp, double h)
@@ -2708,14 +2910,14 @@ __global__ __launch_bounds__(256) void kb_yee_e(const BatchTable *__restrict__ b
     yee_e_body<R, D>(bt->kp[cb.x], cb.y, 0);
 }
 
-__global__ __launch_bounds__(kAdvanceThreads) void k_advance(const KParams *__restrict__ kp, int parts)
+__global__ __launch_bounds__(kAdvanceThreads) void k_advance(const KParams *__restrict__ kp, int nfd)
 {
-    advance_body(kp, parts);
+    advance_body(kp, kp->split, nfd);
 }
 // one workgroup per run; the first also rewinds the particle-kernel queues
 __global__ __launch_bounds__(kAdvanceThreads) void kb_advance(const BatchTable *__restrict__ bt)
 {
-    advance_body(bt->kp[blockIdx.x], 1);
+    advance_body(bt->kp[blockIdx.x], 1, bt->kp[blockIdx.x]->fd_blocks);
     if (blockIdx.x == 0 && threadIdx.x < kBatchGroups * kBatchXcds)
         bt->grp[threadIdx.x / kBatchXcds].queue[threadIdx.x % kBatchXcds] = 0;
 }
@@ -2900,25 +3102,35 @@ static int shape_block(int precision_is_mixed, int shape)
     return precision_is_mixed && shape > 0 && shape < kShapes ? kShapeBlock[shape] : kShapeBlock[0];
 }
 
-// Kernel order of a step (groups in brackets): [0 Gauss checks: charge,
-// residual] | [0] field diag | [1] particle | [2] 6 x re-layout | [1] binary
-// collisions (if any) | [3] J reduction | [0 continuity check: charge,
-// residual] | [4] 3 x Yee | [5] advance.
+// Kernel order of a step (groups in brackets).  An ordinary run: [0] field
+// record (large grids; else part of the first field pass) | [1] particle | [3]
+// first field pass (current, E step) and the re-layout's counts | [4] second
+// field pass (B half step) and the re-layout's copies, and with few tiles the
+// end of the step | [5] end of the step (many tiles).  With binary collisions
+// or the Gauss checks the re-layout has two launches of its own [2] after the
+// particle kernel, followed by [1] the collisions; the checks are [0].
 template <typename R, typename A, int D, int T>
 static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L)
 {
     const int ntiles = hp.g.ntiles;
     const int64_t cells = hp.g.cells;
     const unsigned cb = (unsigned)((cells + 255) / 256);
-    const unsigned nst = (unsigned)((hp.nspecies * ntiles + 255) / 256);
     const bool gauss = (hp.flags & PIC_FLAG_GAUSS_RESIDUAL) != 0;
     if (gauss) {
         L.grp = 0;
         L(k_rho<R, D, T, false>, dim3(ntiles), dim3(256), dp);
         L(k_gauss<R, D>, dim3(cb), dim3(256), dp);
     }
-    L.grp = 0;
-    L(k_field_diag<R>, dim3(hp.fd_blocks), dim3(256), dp);
+    // Field passes: fused where the run has room for the second set of planes;
+    // the field record joins the first of them where its per-workgroup
+    // partials fit the table.
+    const bool fused = hp.Ft != nullptr;
+    const bool record = fused && cb <= (unsigned)kFieldDiagBlocks;
+    const int nfd = record ? (int)cb : hp.fd_blocks;
+    if (!record) {
+        L.grp = 0;
+        L(k_field_diag<R>, dim3(hp.fd_blocks), dim3(256), dp);
+    }
     L.grp = 1;
     const unsigned pbk = (unsigned)shape_block(sizeof(R) == 4, hp.shape);
     if (hp.split > 1) {
@@ -2926,16 +3138,23 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
           dim3((unsigned)(ntiles * hp.split)), dim3(kShapeBlock[0]), dp, hp.split);
     } else if (hp.coulomb) L(particle_kernel<R, A, D, T, true>(hp.shape), dim3(ntiles), dim3(pbk), dp);
     else L(particle_kernel<R, A, D, T, false>(hp.shape), dim3(ntiles), dim3(pbk), dp);
-    L.grp = 2;
-    L(hp.split > 1 ? k_rebin_count<true> : k_rebin_count<false>, dim3(nst), dim3(256), dp);
-    L(k_rebin_count_ovf<R>, dim3(256), dim3(256), dp);
-    L(k_rebin_scan, dim3(hp.nspecies), dim3(256), dp);
-    // one workgroup per 8 (species, tile) bins, 1024 to 16384 (the copy
-    // needs many workgroups in flight; an idle launch costs the same)
-    const unsigned scb = (unsigned)std::min<int64_t>(16384, std::max<int64_t>(1024, (int64_t)ntiles * hp.nspecies / 8));
-    L(k_rebin_scatter<R>, dim3(scb), dim3(256), dp);
-    L(k_rebin_scatter_ovf<R>, dim3(256), dim3(256), dp);
-    L(k_rebin_finalize, dim3(nst), dim3(256), dp);
+    // Re-layout: the counts in up to 256 workgroups (they also carry a split
+    // run's counters over, so each takes at least a few bins), the copies in
+    // one per 8 bins, 1024 to 16384 but no more than there are bins.
+    const int64_t bins = (int64_t)ntiles * hp.nspecies;
+    const int nrc = (int)std::min<int64_t>(256, (bins + 255) / 256 + 15);
+    const int nrs = (int)std::min<int64_t>(16384, std::max<int64_t>(std::min<int64_t>(1024, bins), bins / 8));
+    const bool apart = hp.binary || gauss || !fused;     // something between the re-layout and the fields
+    auto mid = [&](int nf, int nr) {
+        auto k = hp.split > 1 ? (record ? k_mid<R, D, true, true> : k_mid<R, D, true, false>)
+                              : (record ? k_mid<R, D, false, true> : k_mid<R, D, false, false>);
+        L(k, dim3((unsigned)(nf + nr)), dim3(256), dp, nf, nr);
+    };
+    if (apart) {
+        L.grp = 2;
+        mid(0, nrc);
+        L(k_end<R, D, false>, dim3((unsigned)nrs), dim3(256), dp, 0, nrs, nfd);
+    }
     if (hp.binary) {
         L.grp = 1;
         int64_t ppc = 0;
@@ -2952,21 +3171,30 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
           dim3(kBinThreads<R>), dp, width, nblk);
     }
     L.grp = 3;
-    if (hp.split > 1) L(k_reduce_j_split<R, D>, dim3(cb, 3), dim3(256), dp, hp.split);
-    else L(k_reduce_j<R, D>, dim3(cb), dim3(256), dp);
+    if (fused) mid((int)cb, apart ? 0 : nrc);
+    else L(hp.split > 1 ? k_reduce_j<R, D, true> : k_reduce_j<R, D, false>, dim3(cb), dim3(256), dp);
     if (gauss) {
         L.grp = 0;
         L(k_rho<R, D, T, true>, dim3(ntiles), dim3(256), dp);
         L(k_continuity<R, D>, dim3(cb), dim3(256), dp);
     }
-    // frozen fields: the Yee kernels still run (fixed launch shape) but exit
-    const double h = (hp.flags & PIC_FLAG_FREEZE_FIELDS) ? 0.0 : 0.5;
     L.grp = 4;
-    L(k_yee_b<R, D>, dim3(cb), dim3(256), dp, h);
-    L(k_yee_e<R, D>, dim3(cb), dim3(256), dp);
-    L(k_yee_b<R, D>, dim3(cb), dim3(256), dp, h);
+    // few tiles: the end of the step is one more workgroup of the last field
+    // pass (with many, its 1024 threads and a launch of its own are faster)
+    const bool adv = fused && !apart && ntiles * hp.split <= kAdvanceTiles;
+    if (fused) {
+        const int nr = apart ? 0 : nrs;
+        if (adv) L(k_end<R, D, true>, dim3((unsigned)(cb + nr + 1)), dim3(256), dp, (int)cb, nr, nfd);
+        else L(k_end<R, D, false>, dim3((unsigned)(cb + nr)), dim3(256), dp, (int)cb, nr, nfd);
+    } else {
+        // frozen fields: the Yee kernels still run (fixed launch shape) but exit
+        const double h = (hp.flags & PIC_FLAG_FREEZE_FIELDS) ? 0.0 : 0.5;
+        L(k_yee_b<R, D>, dim3(cb), dim3(256), dp, h);
+        L(k_yee_e<R, D>, dim3(cb), dim3(256), dp);
+        L(k_yee_b<R, D>, dim3(cb), dim3(256), dp, h);
+    }
     L.grp = 5;
-    L(k_advance, dim3(1), dim3(kAdvanceThreads), dp, hp.split);
+    if (!adv) L(k_advance, dim3(1), dim3(kAdvanceThreads), dp, nfd);
     return L.dry ? hipSuccess : hipGetLastError();
 }
 

@@ -37,6 +37,8 @@ struct Layout {
     size_t F, J;                                            // field buffer
     size_t Jtile, tile_diag, field_diag, moments, state, kparams, rb[4], order, bucket;   // scratch
     size_t rho_tile, rho0, rho_n, gauss_part, cont_part;    // scratch (Gauss-law and continuity checks)
+    size_t rl_ovf = 0, rl_ticket = 0;                       // scratch (re-layout of a single run)
+    size_t Ft = 0;                                          // scratch (planes between the field passes)
     size_t Jsplit = 0, split_cnt = 0, split_diag = 0;                   // scratch (tiles split over workgroups)
     int split = 1;                                          // workgroups per tile of the particle kernel
     size_t ee_part = 0, ee_off = 0;                         // scratch (binary collisions: pairs and list ends per workgroup)
@@ -272,6 +274,10 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
         // layout files depend on.
         L->state_bytes = c.off;
         L->kparams = c.take(sizeof(KParams));
+        L->rl_ovf = c.take((size_t)ns * G.ntiles * 4);
+        L->rl_ticket = c.take(2 * 4);
+        // fused field passes: 2D, and 3D grids with few tiles (see field_mid)
+        if (!lean && (g->ndim == 2 || L->split > 1)) L->Ft = c.take((size_t)G.cells * 6 * L->real);
         if (L->split > 1) {
             L->Jsplit = c.take((size_t)G.ntiles * L->split * 3 * nj_cells * 8);
             L->split_cnt = c.take((size_t)G.ntiles * ns * 2 * kSplitLine * 4);
@@ -906,6 +912,9 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
     K.tile_diag = (double *)at(buffers->scratch, L.tile_diag);
     K.field_diag = (double *)at(buffers->scratch, L.field_diag);
     K.moments = (double *)at(buffers->scratch, L.moments);
+    K.rl_ovf = (int32_t *)at(buffers->scratch, L.rl_ovf);
+    K.rl_ticket = (int32_t *)at(buffers->scratch, L.rl_ticket);
+    K.Ft = L.Ft ? at(buffers->scratch, L.Ft) : nullptr;
     K.split = L.split;
     K.Jsplit = L.split > 1 ? at(buffers->scratch, L.Jsplit) : nullptr;
     K.split_cnt = L.split > 1 ? (uint32_t *)at(buffers->scratch, L.split_cnt) : nullptr;
@@ -952,6 +961,7 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
     INIT_CHK(hipMemsetAsync(buffers->fields, 0, L.field_bytes, r->stream));
     INIT_CHK(hipMemsetAsync(K.Jtile, 0, L.tile_diag - L.Jtile, r->stream));
     INIT_CHK(hipMemsetAsync(K.tile_diag, 0, L.state - L.tile_diag, r->stream));
+    INIT_CHK(hipMemsetAsync(K.rl_ovf, 0, L.rl_ticket + 2 * 4 - L.rl_ovf, r->stream));
     if (L.split > 1) INIT_CHK(hipMemsetAsync(K.split_cnt, 0, L.split_diag - L.split_cnt, r->stream));
     INIT_CHK(hipMemsetAsync(buffers->diag, 0, L.diag_bytes, r->stream));
     DevState st0;
@@ -1144,9 +1154,9 @@ int pic_step_profiled(pic_run *r, int32_t nsteps, double *group_ms)
     if (!r || !group_ms) return fail(r ? &r->err : nullptr, PIC_E_INVALID_ARG, "bad argument");
     if (nsteps < 0) return fail(&r->err, PIC_E_INVALID_ARG, "nsteps < 0");
     if (r->owner) return fail(&r->err, PIC_E_STATE, "run is a member of a batch; step the batch");
-    int groups[32];
+    int groups[kMaxStepKernels];
     const int nk = step_kernel_groups(r->hp, groups);
-    if (nk <= 0 || nk > 32) return fail(&r->err, PIC_E_UNSUPPORTED, "no kernel sequence for this run");
+    if (nk <= 0 || nk > kMaxStepKernels) return fail(&r->err, PIC_E_UNSUPPORTED, "no kernel sequence for this run");
     return profiled_steps(&r->err, r->stream, nsteps, nk, groups, group_ms, [&](hipEvent_t *ev) {
         hipError_t e = launch_step(r->hp, r->dp, r->stream, ev);
         if (e == hipSuccess) {
