@@ -125,6 +125,7 @@ struct KParams {
     int32_t *rb_start;   // [nspecies][tiles]
     int32_t *rb_cap;     // [nspecies][tiles]
     int32_t *rb_fill;    // [nspecies][tiles]
+    int64_t *ex_off;     // [tiles + 1] read-out: first particle of each tile, total
     int32_t *rl_ovf;     // [nspecies][tiles] overflowed particles per new tile (zero between steps)
     int32_t *rl_ticket;  // [2] workgroups that have ended a re-layout phase (zero between steps)
     void *Ft;            // 6 planes: E^{n+1} and B^{n+1/2} between the field passes (null: unfused passes)
@@ -234,6 +235,10 @@ void release_static_scratch(int device);
 // Records a message for pic_last_error(NULL, ...) and returns code.
 int fail_global(int code, const char *fmt, ...);
 
+// Read-out of species s: the tiles' first places (ex_off), then the particles
+// in places [k0, k0 + n) as FP64 x [ndim][n] and u [3][n] and ids [n] to `out`.
+hipError_t launch_export_scan(const KParams &hp, const KParams *dp, int s, hipStream_t st);
+hipError_t launch_export(const KParams &hp, const KParams *dp, int s, int64_t k0, int64_t n, void *out, hipStream_t st);
 hipError_t launch_load_species(const KParams &hp, const KParams *dp, int s, hipStream_t st);
 hipError_t launch_moments(const KParams &hp, const KParams *dp, int s, double delta_uz, hipStream_t st);
 hipError_t launch_shift_u(const KParams &hp, const KParams *dp, int s, double dux, double duy,

@@ -3041,6 +3041,55 @@ __global__ __launch_bounds__(256) void k_shift_u(const KParams *__restrict__ kp,
 }
 
 // ---------------------------------------------------------------------------
+// Read-out of a species: places of the tiles, then its particles packed in
+// that order (the store's order) in FP64.  HBM-bound, one workgroup per tile.
+__global__ __launch_bounds__(kAdvanceThreads) void k_export_scan(const KParams *__restrict__ kp, int s)
+{
+    __shared__ uint32_t swave[kAdvanceThreads / 64];
+    const SpeciesDev &S = kp->sp[s];
+    const int ntiles = kp->g.ntiles, par = kp->state->par;
+    const int per = (ntiles + (int)blockDim.x - 1) / (int)blockDim.x;
+    const int t0 = min(ntiles, (int)threadIdx.x * per), t1 = min(ntiles, t0 + per);
+    uint32_t sum = 0, total;                             // at most 2^32 - 1 particles
+    for (int t = t0; t < t1; ++t) sum += S.cnt_front[par * ntiles + t] + S.cnt_back[par * ntiles + t];
+    uint32_t run = block_excl(sum, swave, &total);
+    for (int t = t0; t < t1; ++t) {
+        kp->ex_off[t] = (int64_t)run;
+        run += S.cnt_front[par * ntiles + t] + S.cnt_back[par * ntiles + t];
+    }
+    if (threadIdx.x == 0) kp->ex_off[ntiles] = (int64_t)total;
+}
+
+template <typename R, int D>
+__global__ __launch_bounds__(256) void k_export(const KParams *__restrict__ kp, int s, int64_t k0, int64_t n,
+                                                double *__restrict__ out)
+{
+    const SpeciesDev &S = kp->sp[s];
+    const int tile = blockIdx.x, ntiles = kp->g.ntiles, par = kp->state->par;
+    const int T = kp->g.tile[0], ts = kp->g.tshift[0];
+    const int ntx = kp->g.nt[0], nty = kp->g.nt[1];
+    const int o0[3] = {(tile % ntx) * T, ((tile / ntx) % nty) * T, (tile / (ntx * nty)) * T};
+    const int64_t nf = S.cnt_front[par * ntiles + tile], nb = S.cnt_back[par * ntiles + tile];
+    const int64_t b0 = S.start[tile], b1 = b0 + S.cap[tile], first = kp->ex_off[tile] - k0;
+    uint32_t *ids = (uint32_t *)(out + (D + 3) * n);
+    for (int64_t j = threadIdx.x; j < nf + nb; j += blockDim.x) {
+        const int64_t k = first + j;
+        if (k < 0 || k >= n) continue;
+        const int64_t slot = j < nf ? b0 + j : b1 - nb + (j - nf);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            double X = (double)((const R *)S.pos[par][a])[slot];
+            if constexpr (sizeof(R) == 4)
+                X = (double)(o0[a] + (int)(((uint32_t)S.cell[par][slot] >> (a * ts)) & (uint32_t)(T - 1))) + X;
+            out[a * n + k] = X * kp->g.d[a];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) out[(D + c) * n + k] = (double)((const R *)S.u[par][c])[slot];
+        ids[k] = S.track_id ? S.id[par][slot] : 0xFFFFFFFFu;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Launches one kernel; with `ev` it is a hipExtLaunchKernelGGL whose start
 // and stop events carry the dispatch's own timestamps (ev[2k], ev[2k+1] for
 // the k-th kernel of the step).
@@ -3311,6 +3360,21 @@ hipError_t batch_particle_occupancy(int precision, int ndim, int g, bool cb, int
     case 2: return mx ? occupancy<float, 2, 32>(cb, shape, n) : occupancy<double, 2, 32>(cb, shape, n);
     default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_export_scan(const KParams &hp, const KParams *dp, int s, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_export_scan, dim3(1), dim3(kAdvanceThreads), 0, st, dp, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_export(const KParams &hp, const KParams *dp, int s, int64_t k0, int64_t n, void *out, hipStream_t st)
+{
+    const bool mixed = hp.precision == PIC_PREC_MIXED;
+    auto k = hp.g.ndim == 3 ? (mixed ? k_export<float, 3> : k_export<double, 3>)
+                            : (mixed ? k_export<float, 2> : k_export<double, 2>);
+    hipLaunchKernelGGL(k, dim3(hp.g.ntiles), dim3(256), 0, st, dp, s, k0, n, (double *)out);
+    return hipGetLastError();
 }
 
 hipError_t launch_load_species(const KParams &hp, const KParams *dp, int s, hipStream_t st)

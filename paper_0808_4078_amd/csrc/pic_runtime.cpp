@@ -37,6 +37,7 @@ struct Layout {
     size_t F, J;                                            // field buffer
     size_t Jtile, tile_diag, field_diag, moments, state, kparams, rb[4], order, bucket;   // scratch
     size_t rho_tile, rho0, rho_n, gauss_part, cont_part;    // scratch (Gauss-law and continuity checks)
+    size_t ex_off = 0;                                      // scratch (read-out of the particles)
     size_t rl_ovf = 0, rl_ticket = 0;                       // scratch (re-layout of a single run)
     size_t Ft = 0;                                          // scratch (planes between the field passes)
     size_t Jsplit = 0, split_cnt = 0, split_diag = 0;                   // scratch (tiles split over workgroups)
@@ -274,6 +275,7 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
         // layout files depend on.
         L->state_bytes = c.off;
         L->kparams = c.take(sizeof(KParams));
+        L->ex_off = c.take((size_t)(G.ntiles + 1) * 8);
         L->rl_ovf = c.take((size_t)ns * G.ntiles * 4);
         L->rl_ticket = c.take(2 * 4);
         // fused field passes: 2D, and 3D grids with few tiles (see field_mid)
@@ -311,6 +313,7 @@ struct pic_run {
     hipGraphExec_t gexec = nullptr;
     pic_batch *owner = nullptr;  // batch this run is a member of
     int static_device = -1;      // device whose library scratch this run holds (pic_init_static_scratch)
+    std::mutex read_mu;          // held by pic_read_particles (its places and parts lie in the run's buffers)
     std::string err;
 };
 
@@ -378,6 +381,23 @@ int read_state(pic_run *r, DevState *st)
     HIPCHK(r, hipStreamSynchronize(r->stream));
     HIPCHK(r, hipMemcpy(st, at(r->buf.scratch, r->L.state), sizeof(DevState), hipMemcpyDeviceToHost));
     return PIC_OK;
+}
+
+// Device-to-host copy into the caller's memory.  The runtime pins large
+// destinations and lets the device write them, which leaves the data out of the
+// CPU's caches: a caller that goes through it then waits for memory (100k
+// particles sorted by id: 2.7 ms instead of 1.0).  What fits the caches goes in
+// pieces that the runtime stages instead.
+hipError_t copy_out(void *dst, const void *src, size_t bytes, hipStream_t st)
+{
+    constexpr size_t kPiece = size_t(512) << 10, kCached = size_t(16) << 20;
+    const size_t step = bytes <= kCached ? kPiece : bytes;
+    for (size_t o = 0; o < bytes; o += step) {
+        hipError_t e = hipMemcpyAsync((char *)dst + o, (const char *)src + o, std::min(step, bytes - o),
+                                      hipMemcpyDeviceToHost, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 int check_fatal(pic_run *r, const DevState &st)
@@ -912,6 +932,7 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
     K.tile_diag = (double *)at(buffers->scratch, L.tile_diag);
     K.field_diag = (double *)at(buffers->scratch, L.field_diag);
     K.moments = (double *)at(buffers->scratch, L.moments);
+    K.ex_off = (int64_t *)at(buffers->scratch, L.ex_off);
     K.rl_ovf = (int32_t *)at(buffers->scratch, L.rl_ovf);
     K.rl_ticket = (int32_t *)at(buffers->scratch, L.rl_ticket);
     K.Ft = L.Ft ? at(buffers->scratch, L.Ft) : nullptr;
@@ -1210,15 +1231,17 @@ int pic_read_fields(pic_run *r, double *E, double *B, double *J)
     if (!r) return fail(nullptr, PIC_E_INVALID_ARG, "null handle");
     HIPCHK(r, hipStreamSynchronize(r->stream));
     const size_t cells = (size_t)r->L.g.cells;
-    const size_t R = r->L.real;
-    std::vector<char> h(cells * 6 * R);
-    HIPCHK(r, hipMemcpy(h.data(), at(r->buf.fields, r->L.F), h.size(), hipMemcpyDeviceToHost));
-    for (int c = 0; c < 6; ++c) {
-        double *dst = c < 3 ? E : B;
+    for (int v = 0; v < 2; ++v) {
+        double *dst = v ? B : E;
         if (!dst) continue;
-        dst += (size_t)(c % 3) * cells;
-        for (size_t o = 0; o < cells; ++o)
-            dst[o] = R == 4 ? (double)((const float *)h.data())[c * cells + o] : ((const double *)h.data())[c * cells + o];
+        const char *src = at(r->buf.fields, r->L.F) + (size_t)v * 3 * cells * r->L.real;
+        if (r->L.real == 8) {
+            HIPCHK(r, hipMemcpy(dst, src, cells * 3 * 8, hipMemcpyDeviceToHost));
+            continue;
+        }
+        std::vector<float> h(cells * 3);
+        HIPCHK(r, hipMemcpy(h.data(), src, h.size() * 4, hipMemcpyDeviceToHost));
+        for (size_t o = 0; o < h.size(); ++o) dst[o] = (double)h[o];
     }
     if (J) HIPCHK(r, hipMemcpy(J, at(r->buf.fields, r->L.J), cells * 3 * 8, hipMemcpyDeviceToHost));
     return PIC_OK;
@@ -1245,71 +1268,55 @@ int pic_write_fields(pic_run *r, const double *E, const double *B)
     return PIC_OK;
 }
 
+// The particles are packed on the device (FP64 x, u and the ids, tile after
+// tile) into the particle set that the next step will overwrite, as many at a
+// time as it holds, and copied straight into the caller's arrays.
 int pic_read_particles(pic_run *r, int s, double *x, double *u, uint32_t *id, int64_t cap, int64_t *count)
 {
     if (!r || !count) return fail(r ? &r->err : nullptr, PIC_E_INVALID_ARG, "bad argument");
     if (s < 0 || s >= r->ns) return fail(&r->err, PIC_E_INVALID_ARG, "species %d", s);
-    DevState st;
-    int rc = read_state(r, &st);
-    if (rc) return rc;
-    rc = check_fatal(r, st);
-    if (rc) return rc;
     const Layout &L = r->L;
     const Layout::Sp &P = L.sp[s];
-    const Geometry &G = L.g;
-    const int nt = G.ntiles, nd = G.ndim, par = st.par;
-    void *b = r->buf.particles[s];
-    std::vector<int32_t> start(nt), tcap(nt);
-    std::vector<uint32_t> cf((size_t)2 * nt), cb((size_t)2 * nt);
-    HIPCHK(r, hipMemcpy(start.data(), at(b, P.start), nt * 4, hipMemcpyDeviceToHost));
-    HIPCHK(r, hipMemcpy(tcap.data(), at(b, P.cap), nt * 4, hipMemcpyDeviceToHost));
-    HIPCHK(r, hipMemcpy(cf.data(), at(b, P.cnt_front), (size_t)2 * nt * 4, hipMemcpyDeviceToHost));
-    HIPCHK(r, hipMemcpy(cb.data(), at(b, P.cnt_back), (size_t)2 * nt * 4, hipMemcpyDeviceToHost));
+    const int nd = L.g.ndim;
+    std::lock_guard<std::mutex> lk(r->read_mu);
+    HIPCHK(r, launch_export_scan(r->hp, r->dp, s, r->stream));
+    DevState st;
     int64_t n = 0;
-    for (int t = 0; t < nt; ++t) n += (int64_t)cf[(size_t)par * nt + t] + cb[(size_t)par * nt + t];
+    HIPCHK(r, hipMemcpyAsync(&st, r->hp.state, sizeof(st), hipMemcpyDeviceToHost, r->stream));
+    HIPCHK(r, hipMemcpyAsync(&n, r->hp.ex_off + L.g.ntiles, sizeof(n), hipMemcpyDeviceToHost, r->stream));
+    HIPCHK(r, hipStreamSynchronize(r->stream));
+    int rc = check_fatal(r, st);
+    if (rc) return rc;
     *count = n;
     if (n == 0) return PIC_OK;
     if (n > cap) return fail(&r->err, PIC_E_BUFFER_TOO_SMALL, "%lld particles, capacity %lld", (long long)n,
                              (long long)cap);
     if (!x || !u) return fail(&r->err, PIC_E_INVALID_ARG, "null output arrays");
-    const size_t ncap = (size_t)P.ncap, R = L.real;
-    std::vector<uint16_t> hcell(R == 4 ? ncap : 0);
-    std::vector<uint32_t> hid(ncap);
-    std::vector<char> hpos[3], hu[3];
-    if (R == 4) HIPCHK(r, hipMemcpy(hcell.data(), at(b, P.cell[par]), ncap * 2, hipMemcpyDeviceToHost));
-    for (int a = 0; a < nd; ++a) {
-        hpos[a].resize(ncap * R);
-        HIPCHK(r, hipMemcpy(hpos[a].data(), at(b, P.pos[par][a]), ncap * R, hipMemcpyDeviceToHost));
-    }
-    for (int c = 0; c < 3; ++c) {
-        hu[c].resize(ncap * R);
-        HIPCHK(r, hipMemcpy(hu[c].data(), at(b, P.u[par][c]), ncap * R, hipMemcpyDeviceToHost));
-    }
-    HIPCHK(r, hipMemcpy(hid.data(), at(b, P.id[par]), ncap * 4, hipMemcpyDeviceToHost));
-    const bool tracked = r->hp.sp[s].track_id != 0;
-    int64_t k = 0;
-    for (int t = 0; t < nt; ++t) {
-        const int64_t nf = cf[(size_t)par * nt + t], nb = cb[(size_t)par * nt + t];
-        const int t0[3] = {(t % G.nt[0]) * G.tile[0], ((t / G.nt[0]) % G.nt[1]) * G.tile[1],
-                           (t / (G.nt[0] * G.nt[1])) * G.tile[2]};
-        for (int64_t j = 0; j < nf + nb; ++j, ++k) {
-            const int64_t slot = j < nf ? start[t] + j : start[t] + tcap[t] - nb + (j - nf);
-            for (int a = 0; a < nd; ++a) {
-                double X;
-                if (R == 4) {
-                    const uint32_t c = hcell[slot];
-                    const int ic = t0[a] + (int)((c >> (a * G.tshift[0])) & (uint32_t)(G.tile[a] - 1));
-                    X = ic + (double)((const float *)hpos[a].data())[slot];
-                } else {
-                    X = ((const double *)hpos[a].data())[slot];
-                }
-                x[(size_t)a * cap + k] = X * G.d[a];
+    const int other = st.par ^ 1;
+    const size_t lo = L.real == 4 ? P.cell[other] : P.pos[other][0];
+    const size_t room = P.id[other] + (size_t)P.ncap * 4 - lo;
+    char *stage = at(r->buf.particles[s], lo);
+    const int64_t m = std::min<int64_t>(n, (int64_t)(room / ((size_t)(nd + 3) * 8 + 4)));   // ncap >= 64: at least a few
+    for (int64_t k0 = 0; k0 < n; k0 += m) {
+        const int64_t k = std::min(m, n - k0);
+        HIPCHK(r, launch_export(r->hp, r->dp, s, k0, k, stage, r->stream));
+        const double *d = (const double *)stage;
+        auto rows = [&](double *out, int nrows) {
+            if (k == cap) {                              // the rows follow each other there too
+                hipError_t e = copy_out(out, d, (size_t)nrows * k * 8, r->stream);
+                d += (size_t)nrows * k;
+                return e;
             }
-            for (int c = 0; c < 3; ++c)
-                u[(size_t)c * cap + k] = R == 4 ? (double)((const float *)hu[c].data())[slot]
-                                              : ((const double *)hu[c].data())[slot];
-            if (id) id[k] = tracked ? hid[slot] : 0xFFFFFFFFu;
-        }
+            for (int c = 0; c < nrows; ++c, d += k) {
+                hipError_t e = copy_out(out + (size_t)c * cap + k0, d, (size_t)k * 8, r->stream);
+                if (e != hipSuccess) return e;
+            }
+            return hipSuccess;
+        };
+        HIPCHK(r, rows(x, nd));
+        HIPCHK(r, rows(u, 3));
+        if (id) HIPCHK(r, copy_out(id + k0, d, (size_t)k * 4, r->stream));
+        HIPCHK(r, hipStreamSynchronize(r->stream));
     }
     return PIC_OK;
 }

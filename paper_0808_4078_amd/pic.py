@@ -410,15 +410,13 @@ class Run:
 
     def read_particles(self, s: int):
         cnt = C.c_int64()
-        rc = lib().pic_read_particles(self.h, s, None, None, None, 0, C.byref(cnt))
-        if rc not in (PIC_OK, -4):
-            _check(rc, "pic_read_particles", self.h)
-        n = cnt.value
-        x = np.zeros((self.ndim, max(n, 1)))
-        u = np.zeros((3, max(n, 1)))
-        ids = np.zeros(max(n, 1), dtype=np.uint32)
-        _check(lib().pic_read_particles(self.h, s, _ptr(x), _ptr(u), _ptr(ids), max(n, 1), C.byref(cnt)),
+        cap = max(int(self.species[s].ppc) * self.cells, 1)      # a species never holds more
+        x = np.empty((self.ndim, cap))
+        u = np.empty((3, cap))
+        ids = np.empty(cap, dtype=np.uint32)
+        _check(lib().pic_read_particles(self.h, s, _ptr(x), _ptr(u), _ptr(ids), cap, C.byref(cnt)),
                "pic_read_particles", self.h)
+        n = cnt.value
         return x[:, :n], u[:, :n], ids[:n]
 
 
