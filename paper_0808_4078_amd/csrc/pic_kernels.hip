@@ -541,7 +541,7 @@ constexpr int kMoverStage = sizeof(R) == 4 ? (D == 3 ? 24 : 64) : 1;
 template <typename R, typename A, int D, int T, bool CB, int SH, bool BS, bool SPLIT, typename KP>
 __device__ __forceinline__ void particle_body(KP kp, int tile, int part, int parts)
 {
-    constexpr int kBlock = kShapeBlock[SH];
+    constexpr int kBlock = shape_threads(sizeof(R) == 8, D, SH);
     constexpr int kBatch = kShapeInflight[SH];
     constexpr int NF = T + 2;
     constexpr int NJ = T + 3;
@@ -2778,7 +2778,7 @@ typedef __attribute__((address_space(4))) const KParams KParamsC;
 // One workgroup per tile; workgroup b takes tile order[b] (see the work
 // order built at the end of each step).
 template <typename R, typename A, int D, int T, bool CB, int SH>
-__global__ __launch_bounds__(kShapeBlock[SH]) void k_particle(const KParams *__restrict__ kp)
+__global__ __launch_bounds__(shape_threads(sizeof(R) == 8, D, SH)) void k_particle(const KParams *__restrict__ kp)
 {
     const KParamsC *kc = (const KParamsC *)kp;
     particle_body<R, A, D, T, CB, SH, true, false>(kc, wave_uniform(kc->order[blockIdx.x]), 0, 1);
@@ -2786,7 +2786,7 @@ __global__ __launch_bounds__(kShapeBlock[SH]) void k_particle(const KParams *__r
 
 // `parts` workgroups per tile.
 template <typename R, typename A, int D, int T, bool CB>
-__global__ __launch_bounds__(kShapeBlock[0]) void k_particle_split(const KParams *__restrict__ kp, int parts)
+__global__ __launch_bounds__(shape_threads(sizeof(R) == 8, D, 0)) void k_particle_split(const KParams *__restrict__ kp, int parts)
 {
     const KParamsC *kc = (const KParamsC *)kp;
     int pos, part;
@@ -2800,7 +2800,7 @@ __global__ __launch_bounds__(kShapeBlock[0]) void k_particle_split(const KParams
 // items of the other classes.  The counters only grow, so every workgroup
 // reaches the exit.
 template <typename R, typename A, int D, int T, bool CB, int SH>
-__global__ __launch_bounds__(kShapeBlock[SH]) void kb_particle(const BatchTable *__restrict__ bt)
+__global__ __launch_bounds__(shape_threads(sizeof(R) == 8, D, SH)) void kb_particle(const BatchTable *__restrict__ bt)
 {
     constexpr int g = T == 8 ? 0 : (T == 16 ? 1 : 2);
     __shared__ int s_item;
@@ -3146,11 +3146,6 @@ static auto batch_particle_kernel(int shape)
     }
     return f;
 }
-static int shape_block(int precision_is_mixed, int shape)
-{
-    return precision_is_mixed && shape > 0 && shape < kShapes ? kShapeBlock[shape] : kShapeBlock[0];
-}
-
 // Kernel order of a step (groups in brackets).  An ordinary run: [0] field
 // record (large grids; else part of the first field pass) | [1] particle | [3]
 // first field pass (current, E step) and the re-layout's counts | [4] second
@@ -3181,10 +3176,10 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
         L(k_field_diag<R>, dim3(hp.fd_blocks), dim3(256), dp);
     }
     L.grp = 1;
-    const unsigned pbk = (unsigned)shape_block(sizeof(R) == 4, hp.shape);
+    const unsigned pbk = (unsigned)shape_threads(sizeof(R) == 8, D, hp.shape);
     if (hp.split > 1) {
         L(hp.coulomb ? k_particle_split<R, A, D, T, true> : k_particle_split<R, A, D, T, false>,
-          dim3((unsigned)(ntiles * hp.split)), dim3(kShapeBlock[0]), dp, hp.split);
+          dim3((unsigned)(ntiles * hp.split)), dim3(pbk), dp, hp.split);
     } else if (hp.coulomb) L(particle_kernel<R, A, D, T, true>(hp.shape), dim3(ntiles), dim3(pbk), dp);
     else L(particle_kernel<R, A, D, T, false>(hp.shape), dim3(ntiles), dim3(pbk), dp);
     // Re-layout: the counts in up to 256 workgroups (they also carry a split
@@ -3292,7 +3287,7 @@ static void batch_particle(Launcher &L, const BatchTable &ht, const BatchTable *
     constexpr int g = T == 8 ? 0 : (T == 16 ? 1 : 2);
     const unsigned nb = ht.grp[g].n_items > 0 ? (unsigned)std::max(1, pblocks) : 1u;
     const int shape = ht.grp[g].shape;
-    const unsigned pbk = (unsigned)shape_block(sizeof(R) == 4, shape);
+    const unsigned pbk = (unsigned)shape_threads(sizeof(R) == 8, D, shape);
     if (ht.coulomb) L(batch_particle_kernel<R, A, D, T, true>(shape), dim3(nb), dim3(pbk), dt);
     else L(batch_particle_kernel<R, A, D, T, false>(shape), dim3(nb), dim3(pbk), dt);
 }
@@ -3345,7 +3340,7 @@ hipError_t launch_batch_step(int precision, int ndim, const BatchTable &ht, cons
 template <typename R, int D, int T>
 static hipError_t occupancy(bool cb, int shape, int *n)
 {
-    const int bk = shape_block(sizeof(R) == 4, shape);
+    const int bk = shape_threads(sizeof(R) == 8, D, shape);
     return cb ? hipOccupancyMaxActiveBlocksPerMultiprocessor(n, batch_particle_kernel<R, double, D, T, true>(shape), bk, 0)
               : hipOccupancyMaxActiveBlocksPerMultiprocessor(n, batch_particle_kernel<R, double, D, T, false>(shape), bk, 0);
 }

@@ -1165,7 +1165,7 @@ int pic_info(pic_run *r, pic_run_info *out)
     out->direct_steps = r->direct_steps;
     out->scratch_bytes = r->L.scratch_bytes;
     out->shape = r->hp.shape;
-    out->block_threads = kShapeBlock[r->hp.shape];
+    out->block_threads = shape_threads(r->L.real == 8, r->L.g.ndim, r->hp.shape);
     out->inflight = kShapeInflight[r->hp.shape];
     return PIC_OK;
 }
