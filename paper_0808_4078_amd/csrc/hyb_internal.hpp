@@ -19,7 +19,8 @@ constexpr int kGDiag = 5;             // per-block node sums: |grad a|^2, a^2, (
 constexpr int kScanChunk = 2048;      // cells per block of the sort's prefix sum
 constexpr int kMaxNodes = 4096;       // nodes per axis
 constexpr int kFftLds = 4096;         // complex values per FFT workgroup (64 KiB of LDS)
-constexpr int kColThreads = 1024;     // threads of a column-transform workgroup (few workgroups: latency hiding)
+constexpr int kColThreads = 1024;     // threads of a column-transform workgroup at most
+constexpr int kSmallCells = 8192;     // nodes up to which one workgroup does the whole solve
 constexpr int kWaveRounds = 8;        // distinct sort keys merged per wave before plain atomics
 constexpr int kMaxTile = 16;          // tile edge (cells) of the particle kernel
 constexpr int kMargin = 2;            // cells of drift since the last sort that the tile's window absorbs
@@ -43,7 +44,7 @@ struct State {
 
 struct Params {
     int nx, ny, lx, ly;            // nodes per axis and their log2
-    int iters, diag_every, sort_every, cols_per_block;
+    int iters, diag_every, sort_every, col_pairs, lcol_pairs;   // col_pairs: mirrored column pairs per workgroup, and log2
     int tile, ltile, tiles_x, ntiles;  // particle tiles: edge (cells) and its log2, tiles along x, count
     int64_t np;                    // beam macro-particles
     int64_t cells;                 // nx * ny
@@ -58,7 +59,7 @@ struct Params {
     double *it[2];                 // solve result (it[(iters-1) & 1] holds a^n after the solve)
     double *rhsR, *rhsC;           // per step: J - Y + n_p psi, and n_p + X - c0 (the sweeps' coefficients)
     Fix *dep[2][4];                // deposit sets (fixed point): n_b, J at a*, chi, chi a*
-    double2 *W;                    // complex FFT plane [ny][nx]
+    double2 *W;                    // complex FFT plane [ny/2][nx] (rows 2j, 2j+1 in one)
     double2 *twx, *twy;            // exp(-2 pi i t / n), t < n/2
     double *lapx, *lapy;           // (4/d^2) sin^2(pi k / n)
     int32_t *cell_count;           // [cells] particles per sort key (tile-major cell index)

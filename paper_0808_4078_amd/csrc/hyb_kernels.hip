@@ -9,6 +9,7 @@
 // the current linearised about a* = 2 a^n - a^(n-1)); the node kernel
 // (Eq. (3) for psi, a^n -> a^(n-1) -> a^(n-2), diagnostics, clears); the
 // particle sort (every sort_every steps); the bookkeeping kernel.
+#include <algorithm>
 #include <hip/hip_ext.h>
 #include <math.h>
 
@@ -501,182 +502,369 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
 // ---- Eq. (2): lap a - (n_p + X) a = J - Y + n_p psi, n_p = max(n0 - n_b, 0);
 // each sweep solves (lap - c0) a_new = J - Y + n_p psi + (n_p + X - c0) a_old.
 
-// In-place radix-2 decimation-in-time transforms of `batch` sequences of
-// length 2^logn stored back to back in LDS, input in bit-reversed order,
-// output in natural order; tw[t] = exp(-2 pi i t / 2^logn).
+// The right-hand side is real, so rows 2j and 2j+1 are transformed as the
+// real and imaginary part of one complex row: W holds ny/2 rows of nx complex
+// values, half of what a transform of the plane itself would.  Its two
+// interleaved half-planes E (even rows) and O (odd rows) are told apart where
+// the symbol is applied: with Z the transform of E + iO,
+//   E(k,l) = (Z(k,l) + conj Z(-k,-l)) / 2,  O(k,l) = (Z(k,l) - conj Z(-k,-l)) / 2i,
+// and the plane's transform is F(k) = E + w O, F(k + ny/2) = E - w O with
+// w = exp(-2 pi i k / ny).  The forward transforms take natural order to
+// bit-reversed order and the inverse ones back (the symbol is applied in
+// bit-reversed order), so no pass reorders.
 __device__ __forceinline__ double2 cmul(double2 w, double2 v)
 {
     return make_double2(w.x * v.x - w.y * v.y, w.x * v.y + w.y * v.x);
 }
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 
-__device__ __forceinline__ double2 twiddle(const double2 *__restrict__ tw, int t, bool inverse)
+// In-place transforms of `batch` sequences of length 2^logn in LDS, element i
+// of sequence b at z[i * es + b * bs]; `wide`: consecutive threads take
+// consecutive sequences (interleaved storage), else consecutive elements.
+// tw[t << tws] = exp(-2 pi i t / 2^logn), t < 2^(logn-1).  Two radix-2 stages
+// are taken per pass, in registers: half the LDS round trips and barriers.
+struct Lines {
+    int logn, lbatch, es, bs, tws;
+    bool wide;
+};
+__device__ __forceinline__ void line_split(const Lines &L, int e, int lper, int *b, int *k)
 {
-    double2 w = tw[t];
-    if (inverse) w.y = -w.y;
-    return w;
+    *b = L.wide ? e & ((1 << L.lbatch) - 1) : e >> lper;
+    *k = L.wide ? e >> L.lbatch : e & ((1 << lper) - 1);
 }
 
-// Stages are taken two at a time: the four values that two consecutive
-// radix-2 stages combine (i, i+h, i+2h, i+3h) are loaded once, both stages'
-// butterflies are done in registers with the same arithmetic as one stage
-// at a time, and they are stored once -- half the LDS round trips and
-// barriers.  An odd stage count ends with one single stage.
-__device__ void fft_lds(double2 *z, int logn, int batch, const double2 *__restrict__ tw, bool inverse)
+// natural order in, bit-reversed order out (decimation in frequency)
+__device__ void fft_forward(double2 *z, const Lines &L, const double2 *__restrict__ tw)
 {
-    const int n = 1 << logn;
-    int s = 1;
-    for (; s + 1 <= logn; s += 2) {
-        const int h = 1 << (s - 1);
-        const int qn = n >> 2;
-        const int total = batch * qn;
-        for (int e = threadIdx.x; e < total; e += blockDim.x) {
-            const int b = e >> (logn - 2);
-            const int k = e & (qn - 1);
-            const int pos = k & (h - 1);
-            const int i = ((k >> (s - 1)) << (s + 1)) + pos;
-            double2 *zb = z + b * n;
-            const double2 w1 = twiddle(tw, pos << (logn - s), inverse);
-            const double2 w2 = twiddle(tw, pos << (logn - s - 1), inverse);
-            const double2 w3 = twiddle(tw, (pos + h) << (logn - s - 1), inverse);
-            const double2 a0 = zb[i], a1 = zb[i + h], a2 = zb[i + 2 * h], a3 = zb[i + 3 * h];
-            // stage s: (i, i+h) and (i+2h, i+3h)
-            const double2 t1 = cmul(w1, a1), t3 = cmul(w1, a3);
-            const double2 b0 = make_double2(a0.x + t1.x, a0.y + t1.y), b1 = make_double2(a0.x - t1.x, a0.y - t1.y);
-            const double2 b2 = make_double2(a2.x + t3.x, a2.y + t3.y), b3 = make_double2(a2.x - t3.x, a2.y - t3.y);
-            // stage s+1: (i, i+2h) and (i+h, i+3h)
-            const double2 u2 = cmul(w2, b2), u3 = cmul(w3, b3);
-            zb[i] = make_double2(b0.x + u2.x, b0.y + u2.y);
-            zb[i + 2 * h] = make_double2(b0.x - u2.x, b0.y - u2.y);
-            zb[i + h] = make_double2(b1.x + u3.x, b1.y + u3.y);
-            zb[i + 3 * h] = make_double2(b1.x - u3.x, b1.y - u3.y);
+    const int logn = L.logn;
+    int lq = logn - 2;
+    for (; lq >= 0; lq -= 2) {
+        const int q = 1 << lq, sh = logn - lq - 2 + L.tws;
+        for (int e = threadIdx.x; e < 1 << (logn - 2 + L.lbatch); e += blockDim.x) {
+            int b, k;
+            line_split(L, e, logn - 2, &b, &k);
+            const int pos = k & (q - 1);
+            double2 *p = z + b * L.bs + (((k >> lq) << (lq + 2)) + pos) * L.es;
+            const int d = q * L.es;
+            const double2 w1 = tw[pos << sh], w2 = tw[pos << (sh + 1)];
+            const double2 a0 = p[0], a1 = p[d], a2 = p[2 * d], a3 = p[3 * d];
+            const double2 b0 = cadd(a0, a2), b1 = cadd(a1, a3);
+            const double2 b2 = cmul(w1, csub(a0, a2)), t = cmul(w1, csub(a1, a3));
+            const double2 b3 = make_double2(t.y, -t.x);          // times -i: the twiddle a quarter turn on
+            p[0] = cadd(b0, b1);
+            p[d] = cmul(w2, csub(b0, b1));
+            p[2 * d] = cadd(b2, b3);
+            p[3 * d] = cmul(w2, csub(b2, b3));
         }
         __syncthreads();
     }
-    if (s == logn) {
-        const int half = 1 << (s - 1);
-        const int hn = n >> 1;
-        const int total = batch * hn;
-        for (int e = threadIdx.x; e < total; e += blockDim.x) {
-            const int b = e >> (logn - 1);
-            const int k = e & (hn - 1);
-            const int pos = k & (half - 1);
-            const int i1 = ((k >> (s - 1)) << s) + pos;
-            double2 *zb = z + b * n;
-            const double2 w = twiddle(tw, pos << (logn - s), inverse);
-            const double2 u = zb[i1], v = cmul(w, zb[i1 + half]);
-            zb[i1] = make_double2(u.x + v.x, u.y + v.y);
-            zb[i1 + half] = make_double2(u.x - v.x, u.y - v.y);
+    if (lq == -1) {                                              // odd stage count: the last one alone
+        for (int e = threadIdx.x; e < 1 << (logn - 1 + L.lbatch); e += blockDim.x) {
+            int b, k;
+            line_split(L, e, logn - 1, &b, &k);
+            double2 *p = z + b * L.bs + 2 * k * L.es;
+            const double2 u = p[0], v = p[L.es];
+            p[0] = cadd(u, v);
+            p[L.es] = csub(u, v);
         }
         __syncthreads();
     }
 }
 
-// First sweep's row transform (one workgroup per row): the step's
-// coefficients R = J - Y + n_p psi and C = n_p + X - c0 are stored for the
-// later sweeps, and the right-hand side R + C a^(0), a^(0) = 2 a^(n-1) -
-// a^(n-2), is transformed along x.
-__global__ __launch_bounds__(kThreads) void k_rows_first(const Params *__restrict__ pp)
+// bit-reversed order in, natural order out, conjugate twiddles, not scaled
+__device__ void fft_inverse(double2 *z, const Lines &L, const double2 *__restrict__ tw)
 {
-    extern __shared__ double2 z[];
-    const Params &P = *pp;
-    const int j = blockIdx.x, nx = P.nx;
+    const int logn = L.logn;
+    if (logn & 1) {
+        for (int e = threadIdx.x; e < 1 << (logn - 1 + L.lbatch); e += blockDim.x) {
+            int b, k;
+            line_split(L, e, logn - 1, &b, &k);
+            double2 *p = z + b * L.bs + 2 * k * L.es;
+            const double2 u = p[0], v = p[L.es];
+            p[0] = cadd(u, v);
+            p[L.es] = csub(u, v);
+        }
+        __syncthreads();
+    }
+    for (int lq = logn & 1; lq <= logn - 2; lq += 2) {
+        const int q = 1 << lq, sh = logn - lq - 2 + L.tws;
+        for (int e = threadIdx.x; e < 1 << (logn - 2 + L.lbatch); e += blockDim.x) {
+            int b, k;
+            line_split(L, e, logn - 2, &b, &k);
+            const int pos = k & (q - 1);
+            double2 *p = z + b * L.bs + (((k >> lq) << (lq + 2)) + pos) * L.es;
+            const int d = q * L.es;
+            double2 w1 = tw[pos << sh], w2 = tw[pos << (sh + 1)];
+            w1.y = -w1.y;
+            w2.y = -w2.y;
+            const double2 a0 = p[0], a1 = cmul(w2, p[d]), a2 = p[2 * d], a3 = cmul(w2, p[3 * d]);
+            const double2 b0 = cadd(a0, a1), b1 = csub(a0, a1);
+            const double2 u2 = cmul(w1, cadd(a2, a3)), t = cmul(w1, csub(a2, a3));
+            const double2 u3 = make_double2(-t.y, t.x);          // times i
+            p[0] = cadd(b0, u2);
+            p[2 * d] = csub(b0, u2);
+            p[d] = cadd(b1, u3);
+            p[3 * d] = csub(b1, u3);
+        }
+        __syncthreads();
+    }
+}
+
+// Where -k lies in bit-reversed order if k lies at position q: the positions
+// [2^t, 2^(t+1)) hold it in reverse.
+__device__ __forceinline__ int mirror_pos(int q)
+{
+    if (q < 2) return q;
+    const int t = 31 - __clz(q);
+    return (3 << t) - 1 - q;
+}
+// The P-th pair of mirrored columns (positions in bit-reversed order):
+// consecutive pairs are consecutive columns.  Pair 0 holds the two columns that
+// mirror themselves.
+__device__ __forceinline__ void column_pair(int P, int *a, int *b)
+{
+    if (P == 0) {
+        *a = 0;
+        *b = 1;
+        return;
+    }
+    const int t = 32 - __clz(P), x = P - (1 << (t - 1));
+    *a = (1 << t) + x;
+    *b = (2 << t) - 1 - x;
+}
+
+// Symbol at element (k, l) and its mirror image: z1 = Z(k,l), z2 = Z(-k,-l),
+// lx = lapx[l]; both are replaced.  inv: 1 / (nx ny).
+__device__ __forceinline__ void apply_symbol(const Params &P, double2 &z1, double2 &z2, int k, double lx, double inv)
+{
+    const int m = P.ny >> 1;
+    const double2 w = P.twy[k];
+    const double2 E = make_double2(0.5 * (z1.x + z2.x), 0.5 * (z1.y - z2.y));
+    const double2 O = make_double2(0.5 * (z1.y + z2.y), 0.5 * (z2.x - z1.x));
+    const double2 wO = cmul(w, O);
+    const double s0 = inv / (-(lx + P.lapy[k]) - P.c0), s1 = inv / (-(lx + P.lapy[k + m]) - P.c0);
+    const double2 f0 = make_double2((E.x + wO.x) * s0, (E.y + wO.y) * s0);
+    const double2 f1 = make_double2((E.x - wO.x) * s1, (E.y - wO.y) * s1);
+    const double2 e = cadd(f0, f1), o = cmul(make_double2(w.x, -w.y), csub(f0, f1));
+    z1 = make_double2(e.x - o.y, e.y + o.x);                     // e + i o
+    z2 = make_double2(e.x + o.y, o.x - e.y);                     // conj(e) + i conj(o)
+}
+
+// The symbol over pair `pr` of columns a and b, elements q (in bit-reversed
+// order) at A[q * es] and B[q * es]; threads [t0, ...) of a group of nt.
+__device__ __forceinline__ void symbol_pair(const Params &P, double2 *A, double2 *B, int es, int pr, int a, int b,
+                                            int t0, int nt, double inv)
+{
+    const int m = P.ny >> 1, lm = P.ly - 1;
+    const double la = P.lapx[brev(a, P.lx)];
+    if (pr) {
+        for (int q = t0; q < m; q += nt) apply_symbol(P, A[q * es], B[mirror_pos(q) * es], brev(q, lm), la, inv);
+        return;
+    }
+    const double lb = P.lapx[brev(b, P.lx)];
+    for (int q = t0; q < 2 * m; q += nt) {
+        double2 *C = q < m ? A : B;
+        const int p = q < m ? q : q - m, r = mirror_pos(p);
+        if (p > r) continue;
+        double2 z1 = C[p * es], z2 = C[r * es];
+        apply_symbol(P, z1, z2, brev(p, lm), q < m ? la : lb, inv);
+        C[p * es] = z1;
+        if (p != r) C[r * es] = z2;
+    }
+}
+
+// The step's coefficients of node o: R = J - Y + n_p psi, C = n_p + X - c0, and
+// the start a^(0) = 2 a^(n-1) - a^(n-2).
+__device__ __forceinline__ void coefficients(const Params &P, int64_t o, double *R, double *C, double *a0)
+{
     const int p = (int)(P.state->step & 1);
     const Fix *nb = P.dep[p][0], *J = P.dep[p][1], *Xc = P.dep[p][2], *Yc = P.dep[p][3];
-    for (int i = threadIdx.x; i < nx; i += blockDim.x) {
-        const int64_t o = (int64_t)j * nx + i;
-        const double ap = 2.0 * P.a1[o] - P.a2[o];
-        const double n_p = fmax(P.n0 - (double)nb[o] * kDepUnit, 0.0);
-        const double c = n_p + (double)Xc[o] * kDepUnit;
-        const double R = (double)J[o] * kDepUnit - (double)Yc[o] * kDepUnit + n_p * P.psi[o];
-        const double C = c - P.c0;
-        P.rhsR[o] = R;
-        P.rhsC[o] = C;
-        z[brev(i, P.lx)] = make_double2(R + C * ap, 0.0);
-    }
-    __syncthreads();
-    fft_lds(z, P.lx, 1, P.twx, false);
-    for (int i = threadIdx.x; i < nx; i += blockDim.x) P.W[(int64_t)j * nx + i] = z[i];
+    *a0 = 2.0 * P.a1[o] - P.a2[o];
+    const double n_p = fmax(P.n0 - (double)nb[o] * kDepUnit, 0.0);
+    *R = (double)J[o] * kDepUnit - (double)Yc[o] * kDepUnit + n_p * P.psi[o];
+    *C = n_p + (double)Xc[o] * kDepUnit - P.c0;
 }
 
-// Between sweeps (one workgroup per row): the inverse row transform gives
-// the sweep's result a, from which the next right-hand side R + C a is
-// transformed along x, without a round trip of a through memory.
-__global__ __launch_bounds__(kThreads) void k_rows_mid(const Params *__restrict__ pp)
+// The passes of a large grid.  Rows: one workgroup per pair of rows, a quarter
+// as many threads as nodes in a row (64 to 1024), so at most 4 nodes of each
+// row per thread.
+__device__ __forceinline__ Lines row_line(const Params &P) { return Lines{P.lx, 0, 1, 0, 0, false}; }
+
+// First sweep's row transform of R + C a^(0); R and C are kept for the others.
+__global__ __launch_bounds__(1024) void k_rows_first(const Params *__restrict__ pp)
 {
     extern __shared__ double2 z[];
     const Params &P = *pp;
-    const int j = blockIdx.x, nx = P.nx;
-    for (int i = threadIdx.x; i < nx; i += blockDim.x) z[brev(i, P.lx)] = P.W[(int64_t)j * nx + i];
-    __syncthreads();
-    fft_lds(z, P.lx, 1, P.twx, true);
-    const double s = 1.0 / (double)P.cells;
-    double v[kFftLds / kThreads];
-    int m = 0;
-    for (int i = threadIdx.x; i < nx; i += blockDim.x, ++m) {
-        const int64_t o = (int64_t)j * nx + i;
-        v[m] = P.rhsR[o] + P.rhsC[o] * (z[i].x * s);
+    const int nx = P.nx;
+    const int64_t o = (int64_t)blockIdx.x * 2 * nx;
+    for (int i = threadIdx.x; i < nx; i += blockDim.x) {
+        double v[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            double R, C, a0;
+            coefficients(P, o + r * nx + i, &R, &C, &a0);
+            P.rhsR[o + r * nx + i] = R;
+            P.rhsC[o + r * nx + i] = C;
+            v[r] = R + C * a0;
+        }
+        z[i] = make_double2(v[0], v[1]);
     }
     __syncthreads();
-    m = 0;
-    for (int i = threadIdx.x; i < nx; i += blockDim.x, ++m) z[brev(i, P.lx)] = make_double2(v[m], 0.0);
-    __syncthreads();
-    fft_lds(z, P.lx, 1, P.twx, false);
-    for (int i = threadIdx.x; i < nx; i += blockDim.x) P.W[(int64_t)j * nx + i] = z[i];
+    fft_forward(z, row_line(P), P.twx);
+    for (int i = threadIdx.x; i < nx; i += blockDim.x) P.W[(int64_t)blockIdx.x * nx + i] = z[i];
 }
 
-// Column transform, division by the symbol -(4/dx^2) sin^2 - (4/dy^2) sin^2 - c0,
-// inverse column transform (cols_per_block columns per workgroup).
+// Between sweeps: the inverse row transform gives the sweep's result a, from
+// which the next right-hand side R + C a is transformed, without a round trip
+// of a through memory.
+__global__ __launch_bounds__(1024) void k_rows_mid(const Params *__restrict__ pp)
+{
+    extern __shared__ double2 z[];
+    const Params &P = *pp;
+    const int nx = P.nx;
+    const int64_t o = (int64_t)blockIdx.x * 2 * nx;
+    double2 *W = P.W + (int64_t)blockIdx.x * nx;
+    double R[4][2], C[4][2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        if (i < nx) z[i] = W[i];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {                                // in flight during the inverse transform
+        const int i = threadIdx.x + k * blockDim.x;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            R[k][r] = i < nx ? P.rhsR[o + r * nx + i] : 0.0;
+            C[k][r] = i < nx ? P.rhsC[o + r * nx + i] : 0.0;
+        }
+    }
+    __syncthreads();
+    fft_inverse(z, row_line(P), P.twx);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        if (i < nx) z[i] = make_double2(R[k][0] + C[k][0] * z[i].x, R[k][1] + C[k][1] * z[i].y);
+    }
+    __syncthreads();
+    fft_forward(z, row_line(P), P.twx);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        if (i < nx) W[i] = z[i];
+    }
+}
+
+// Column transform, inverse symbol, inverse column transform of col_pairs
+// mirrored pairs of columns per workgroup, interleaved in LDS.
 __global__ __launch_bounds__(kColThreads) void k_cols(const Params *__restrict__ pp)
 {
     extern __shared__ double2 z[];
     const Params &P = *pp;
-    const int CB = P.cols_per_block, ny = P.ny, nx = P.nx, ly = P.ly;
-    // Workgroups go to the 8 XCDs in turn, and a row's CB values fill only
-    // part of a 128-byte line: consecutive workgroups on one XCD take
-    // neighbouring column groups, so both halves of a line are fetched into
-    // the same L2 (a bijection of the groups when the count divides by 8).
+    const int G = P.col_pairs, lg = P.lcol_pairs + 1, nx = P.nx, m = P.ny >> 1;
+    // Workgroups go to the 8 XCDs in turn: consecutive workgroups on one XCD
+    // take neighbouring columns, so that a line is fetched into one L2 (a
+    // bijection of the groups when the count divides by 8).
     const int nbk = (int)gridDim.x, bk = (int)blockIdx.x;
-    const int grp = (nbk & 7) ? bk : (bk & 7) * (nbk >> 3) + (bk >> 3);
-    const int c0 = grp * CB;
-    for (int e = threadIdx.x; e < CB * ny; e += blockDim.x) {
-        const int c = e & (CB - 1), j = e / CB;
-        z[c * ny + brev(j, ly)] = P.W[(int64_t)j * nx + c0 + c];
+    const int P0 = G * ((nbk & 7) ? bk : (bk & 7) * (nbk >> 3) + (bk >> 3));
+    auto column = [&](int c) {                                   // column of slot c: the pairs' first, then their second
+        int a, b;
+        column_pair(P0 + (c & (G - 1)), &a, &b);
+        return c < G ? a : b;
+    };
+    const int mycol = column(threadIdx.x & (2 * G - 1));         // the thread count is a multiple of 2 G
+    for (int e = threadIdx.x; e < m << lg; e += blockDim.x) z[e] = P.W[(int64_t)(e >> lg) * nx + mycol];
+    __syncthreads();
+    const Lines L{P.ly - 1, lg, 2 * G, 1, 1, true};
+    fft_forward(z, L, P.twy);
+    const int per = (int)blockDim.x / G, g = (int)threadIdx.x & (G - 1);
+    {
+        int a, b;
+        column_pair(P0 + g, &a, &b);
+        symbol_pair(P, z + g, z + G + g, 2 * G, P0 + g, a, b, (int)threadIdx.x / G, per, 1.0 / (double)P.cells);
     }
     __syncthreads();
-    fft_lds(z, ly, CB, P.twy, false);
-    // scale, writing each value to its bit-reversed slot for the inverse pass
-    for (int e = threadIdx.x; e < CB * ny; e += blockDim.x) {
-        const int c = e >> ly, k = e & (ny - 1);
-        const int r = brev(k, ly);
-        if (k <= r) {
-            const double lxv = P.lapx[c0 + c];
-            const double sk = 1.0 / (-(lxv + P.lapy[k]) - P.c0);
-            const double sr = 1.0 / (-(lxv + P.lapy[r]) - P.c0);
-            const double2 vk = z[c * ny + k], vr = z[c * ny + r];
-            z[c * ny + r] = make_double2(vk.x * sk, vk.y * sk);
-            z[c * ny + k] = make_double2(vr.x * sr, vr.y * sr);
-        }
-    }
-    __syncthreads();
-    fft_lds(z, ly, CB, P.twy, true);
-    for (int e = threadIdx.x; e < CB * ny; e += blockDim.x) {
-        const int c = e & (CB - 1), j = e / CB;
-        P.W[(int64_t)j * nx + c0 + c] = z[c * ny + j];
-    }
+    fft_inverse(z, L, P.twy);
+    for (int e = threadIdx.x; e < m << lg; e += blockDim.x) P.W[(int64_t)(e >> lg) * nx + mycol] = z[e];
 }
 
-// Last sweep's inverse row transform; the real part / (nx ny) is a^n.
-__global__ __launch_bounds__(kThreads) void k_rows_inv(const Params *__restrict__ pp)
+// Last sweep's inverse row transform: a^n.
+__global__ __launch_bounds__(1024) void k_rows_inv(const Params *__restrict__ pp)
 {
     extern __shared__ double2 z[];
     const Params &P = *pp;
-    const int j = blockIdx.x, nx = P.nx;
-    for (int i = threadIdx.x; i < nx; i += blockDim.x) z[brev(i, P.lx)] = P.W[(int64_t)j * nx + i];
+    const int nx = P.nx;
+    for (int i = threadIdx.x; i < nx; i += blockDim.x) z[i] = P.W[(int64_t)blockIdx.x * nx + i];
     __syncthreads();
-    fft_lds(z, P.lx, 1, P.twx, true);
-    const double s = 1.0 / (double)P.cells;
+    fft_inverse(z, row_line(P), P.twx);
+    double *out = P.it[(P.iters - 1) & 1] + (int64_t)blockIdx.x * 2 * nx;
+    for (int i = threadIdx.x; i < nx; i += blockDim.x) {
+        out[i] = z[i].x;
+        out[nx + i] = z[i].y;
+    }
+}
+
+// All sweeps of a small grid (up to kSmallCells nodes) in one workgroup: the
+// plane stays in LDS and R, C in registers, where the passes above would be 2
+// iters + 1 launches of one or two dozen workgroups.
+__global__ __launch_bounds__(1024) void k_solve_small(const Params *__restrict__ pp)
+{
+    extern __shared__ double2 z[];
+    constexpr int PER = kSmallCells / 2 / 1024;
+    const Params &P = *pp;
+    const int nx = P.nx, half = (int)(P.cells >> 1), m = P.ny >> 1;
+    double R[PER][2], C[PER][2];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int e = threadIdx.x + k * 1024;
+        if (e < half) {
+            double v[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                double a0;
+                coefficients(P, (int64_t)(2 * (e >> P.lx) + r) * nx + (e & (nx - 1)), &R[k][r], &C[k][r], &a0);
+                v[r] = R[k][r] + C[k][r] * a0;
+            }
+            z[e] = make_double2(v[0], v[1]);
+        }
+    }
+    __syncthreads();
+    const Lines rows{P.lx, P.ly - 1, 1, nx, 0, false}, cols{P.ly - 1, P.lx, nx, 1, 1, true};
+    const int npair = nx >> 1, per = 1024 / npair, pr = (int)threadIdx.x & (npair - 1);
+    int ca, cb;
+    column_pair(pr, &ca, &cb);
+    for (int it = 0; it < P.iters; ++it) {
+        fft_forward(z, rows, P.twx);
+        fft_forward(z, cols, P.twy);
+        // consecutive threads take consecutive pairs; more pairs than threads: several each
+        if (per > 0) {
+            symbol_pair(P, z + ca, z + cb, nx, pr, ca, cb, (int)threadIdx.x / npair, per, 1.0 / (double)P.cells);
+        } else {
+            for (int p = threadIdx.x; p < npair; p += 1024) {
+                int a, b;
+                column_pair(p, &a, &b);
+                symbol_pair(P, z + a, z + b, nx, p, a, b, 0, 1, 1.0 / (double)P.cells);
+            }
+        }
+        __syncthreads();
+        fft_inverse(z, cols, P.twy);
+        fft_inverse(z, rows, P.twx);
+        if (it + 1 == P.iters) break;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int e = threadIdx.x + k * 1024;
+            if (e < half) z[e] = make_double2(R[k][0] + C[k][0] * z[e].x, R[k][1] + C[k][1] * z[e].y);
+        }
+        __syncthreads();
+    }
+    (void)m;
     double *out = P.it[(P.iters - 1) & 1];
-    for (int i = threadIdx.x; i < nx; i += blockDim.x) out[(int64_t)j * nx + i] = z[i].x * s;
+    for (int e = threadIdx.x; e < half; e += 1024) {
+        const int64_t o = (int64_t)(2 * (e >> P.lx)) * nx + (e & (nx - 1));
+        out[o] = z[e].x;
+        out[o + nx] = z[e].y;
+    }
 }
 
 // ---- node update after the particle kernel: Eq. (3), a history, clears, diagnostics
@@ -1053,14 +1241,20 @@ struct Launcher {
 
 void solve(Launcher &L, const Params &hp, const Params *dp)
 {
-    const size_t row_lds = sizeof(double2) * (size_t)hp.nx;
-    const size_t col_lds = sizeof(double2) * (size_t)hp.cols_per_block * hp.ny;
-    L(0, k_rows_first, dim3(hp.ny), dim3(kThreads), row_lds, dp);
-    for (int it = 0; it < hp.iters; ++it) {
-        L(0, k_cols, dim3(hp.nx / hp.cols_per_block), dim3(kColThreads), col_lds, dp);
-        if (it + 1 < hp.iters) L(0, k_rows_mid, dim3(hp.ny), dim3(kThreads), row_lds, dp);
+    if (hp.cells <= kSmallCells) {
+        L(0, k_solve_small, dim3(1), dim3(1024), sizeof(double2) * (size_t)(hp.cells / 2), dp);
+        return;
     }
-    L(0, k_rows_inv, dim3(hp.ny), dim3(kThreads), row_lds, dp);
+    const size_t row_lds = sizeof(double2) * (size_t)hp.nx;
+    const size_t col_lds = sizeof(double2) * (size_t)hp.col_pairs * hp.ny;
+    const dim3 rows(hp.ny / 2), rt(std::min(1024, std::max(64, hp.nx / 4)));
+    const dim3 cols(hp.nx / 2 / hp.col_pairs), ct(std::min(kColThreads, std::max(64, hp.col_pairs * hp.ny / 4)));
+    L(0, k_rows_first, rows, rt, row_lds, dp);
+    for (int it = 0; it < hp.iters; ++it) {
+        L(0, k_cols, cols, ct, col_lds, dp);
+        if (it + 1 < hp.iters) L(0, k_rows_mid, rows, rt, row_lds, dp);
+    }
+    L(0, k_rows_inv, rows, rt, row_lds, dp);
 }
 
 int scan_chunks(const Params &hp) { return (int)((hp.cells + kScanChunk - 1) / kScanChunk); }
@@ -1091,7 +1285,7 @@ hipError_t launch_init(const Params &hp, const Params *dp, hipStream_t st)
     return hipGetLastError();
 }
 
-int step_launches(const Params &hp) { return 2 * hp.iters + 1 + 9; }
+int step_launches(const Params &hp) { return 2 * hp.iters + 1 + 9; }   // at most
 
 hipError_t launch_step(const Params &hp, const Params *dp, hipStream_t st, hipEvent_t *ev, int *groups, int *nlaunch)
 {

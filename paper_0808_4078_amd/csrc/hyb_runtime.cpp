@@ -124,7 +124,7 @@ int validate(const pic_hyb_desc *d, Layout *L, std::string *err)
     L->rhsC = g.take(C * 8);
     for (int s = 0; s < 2; ++s)
         for (int k = 0; k < 4; ++k) L->dep[s][k] = g.take(C * 8);
-    L->W = g.take(C * 16);
+    L->W = g.take(C * 8);
     L->twx = g.take((size_t)d->nx / 2 * 16);
     L->twy = g.take((size_t)d->ny / 2 * 16);
     L->lapx = g.take((size_t)d->nx * 8);
@@ -236,7 +236,11 @@ int pic_hyb_init(const pic_hyb_desc *desc, void *particles, size_t particle_byte
     P.iters = desc->iters;
     P.diag_every = desc->diag_every;
     P.sort_every = desc->sort_every;
-    P.cols_per_block = std::min(desc->nx, kFftLds / desc->ny);
+    // column pairs per workgroup: 4 (64 bytes of a row), fewer where that would
+    // leave less than a workgroup per CU, or more LDS than kFftLds values
+    P.col_pairs = 4;
+    while (P.col_pairs > 1 && (desc->nx / 2 / P.col_pairs < 256 || P.col_pairs * desc->ny > kFftLds)) P.col_pairs /= 2;
+    P.lcol_pairs = log2_pow2(P.col_pairs);
     P.tile = std::min(kMaxTile, std::min(desc->nx, desc->ny));
     P.ltile = log2_pow2(P.tile);
     P.tiles_x = desc->nx / P.tile;
