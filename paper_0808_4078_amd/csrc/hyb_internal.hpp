@@ -45,6 +45,7 @@ struct State {
 struct Params {
     int nx, ny, lx, ly;            // nodes per axis and their log2
     int iters, diag_every, sort_every, col_pairs, lcol_pairs;   // col_pairs: mirrored column pairs per workgroup, and log2
+    int parts;                     // workgroups per particle tile
     int tile, ltile, tiles_x, ntiles;  // particle tiles: edge (cells) and its log2, tiles along x, count
     int64_t np;                    // beam macro-particles
     int64_t cells;                 // nx * ny
@@ -81,8 +82,10 @@ constexpr int kGroups = 4;
 hipError_t launch_init(const Params &hp, const Params *dp, hipStream_t st);
 // Enqueues one step; with `ev` (2 events per launch) each launch is timed and
 // `groups` receives the group of each launch; *nlaunch the launch count.
+// The sort's kernels themselves skip the steps without one; with_sort = false
+// leaves their six launches out of a step known to be such.
 hipError_t launch_step(const Params &hp, const Params *dp, hipStream_t st, hipEvent_t *ev, int *groups,
-                       int *nlaunch);
+                       int *nlaunch, bool with_sort = true);
 // Launches of one step (for sizing the event arrays).
 int step_launches(const Params &hp);
 

@@ -367,8 +367,9 @@ __device__ __forceinline__ void deposit_terms(const Params &P, const S &star, co
         for (int n = 0; n < 4; ++n) v[4 * k + n] = q[k] * wt[n];
 }
 
-// One workgroup per particle tile: the particles that the last sort placed
-// in tile b (they have drifted by less than kMargin cells since, in
+// One workgroup per particle tile (P.parts where there are few tiles, each with
+// an equal run of the tile's particles: the deposit is summed in integers, so
+// the split changes nothing): the particles that the last sort placed in tile b (they have drifted by less than kMargin cells since, in
 // practice).  Thread t takes kRun consecutive particles at a time (a run;
 // the lanes' runs are adjacent, so every load instruction of the wave reads
 // one contiguous span).  a^n, a^(n-1) and psi on the tile's field window
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     const double *aold = MODE == 0 ? P.a1 : P.a2;                     // a^(n-1)
     Fix *const *dst = MODE == 0 ? P.dep[1 - (int)(step & 1)] : P.dep[0];
     double *X = P.x[cur], *Y = P.y[cur], *UX = P.ux[cur], *UY = P.uy[cur], *PZ = P.pz[cur];
-    const int b = blockIdx.x;
+    const int b = blockIdx.x / P.parts, part = blockIdx.x % P.parts;
     const int tx0 = (b % P.tiles_x) << P.ltile, ty0 = (b / P.tiles_x) << P.ltile;
     const int wx0 = tx0 - kMargin, wy0 = ty0 - kMargin;               // deposit window origin
     const int fx0 = tx0 - kMargin - 1, fy0 = ty0 - kMargin - 1;       // field window origin
@@ -420,7 +421,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     __syncthreads();
     const GlobalNodes gn{nx};
     const WindowNodes wn{fx0, fy0, nx - 1, ny - 1};
-    const int s0 = P.tile_start[cur][b], s1 = P.tile_start[cur][b + 1];
+    int s0 = P.tile_start[cur][b], s1 = P.tile_start[cur][b + 1];
+    if (P.parts > 1) {
+        const int per = ((s1 - s0 + P.parts - 1) / P.parts + 64 * kRun - 1) / (64 * kRun) * (64 * kRun);   // whole waves
+        s0 = min(s1, s0 + per * part);
+        s1 = min(s1, s0 + per);
+    }
     double dacc[kPDiag] = {0.0, 0.0, 0.0};
     for (int base = s0; base < s1; base += kThreads * kRun) {
         Fix v[16];
@@ -496,7 +502,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
 #pragma unroll
         for (int k = 0; k < 4; ++k) fix_add(dst[k] + node, win[k][e]);
     }
-    if (diag) block_sums<kPDiag>(dacc, P.pdiag + (size_t)b * kPDiag);
+    if (diag) block_sums<kPDiag>(dacc, P.pdiag + (size_t)blockIdx.x * kPDiag);
 }
 
 // ---- Eq. (2): lap a - (n_p + X) a = J - Y + n_p psi, n_p = max(n0 - n_b, 0);
@@ -813,7 +819,7 @@ __global__ __launch_bounds__(1024) void k_solve_small(const Params *__restrict__
     extern __shared__ double2 z[];
     constexpr int PER = kSmallCells / 2 / 1024;
     const Params &P = *pp;
-    const int nx = P.nx, half = (int)(P.cells >> 1), m = P.ny >> 1;
+    const int nx = P.nx, half = (int)(P.cells >> 1);
     double R[PER][2], C[PER][2];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -837,16 +843,7 @@ __global__ __launch_bounds__(1024) void k_solve_small(const Params *__restrict__
     for (int it = 0; it < P.iters; ++it) {
         fft_forward(z, rows, P.twx);
         fft_forward(z, cols, P.twy);
-        // consecutive threads take consecutive pairs; more pairs than threads: several each
-        if (per > 0) {
-            symbol_pair(P, z + ca, z + cb, nx, pr, ca, cb, (int)threadIdx.x / npair, per, 1.0 / (double)P.cells);
-        } else {
-            for (int p = threadIdx.x; p < npair; p += 1024) {
-                int a, b;
-                column_pair(p, &a, &b);
-                symbol_pair(P, z + a, z + b, nx, p, a, b, 0, 1, 1.0 / (double)P.cells);
-            }
-        }
+        symbol_pair(P, z + ca, z + cb, nx, pr, ca, cb, (int)threadIdx.x / npair, per, 1.0 / (double)P.cells);
         __syncthreads();
         fft_inverse(z, cols, P.twy);
         fft_inverse(z, rows, P.twx);
@@ -858,7 +855,6 @@ __global__ __launch_bounds__(1024) void k_solve_small(const Params *__restrict__
         }
         __syncthreads();
     }
-    (void)m;
     double *out = P.it[(P.iters - 1) & 1];
     for (int e = threadIdx.x; e < half; e += 1024) {
         const int64_t o = (int64_t)(2 * (e >> P.lx)) * nx + (e & (nx - 1));
@@ -1193,7 +1189,7 @@ __global__ __launch_bounds__(kThreads) void k_advance(const Params *__restrict__
     if (diag) {
         __shared__ double part[kThreads][kPDiag + kGDiag];
         double s[kPDiag + kGDiag] = {};
-        for (int b = threadIdx.x; b < P.ntiles; b += kThreads)
+        for (int b = threadIdx.x; b < P.ntiles * P.parts; b += kThreads)
             for (int k = 0; k < kPDiag; ++k) s[k] += P.pdiag[(size_t)b * kPDiag + k];
         for (int b = threadIdx.x; b < kGridBlocks; b += kThreads)
             for (int k = 0; k < kGDiag; ++k) s[kPDiag + k] += P.gdiag[(size_t)b * kGDiag + k];
@@ -1278,22 +1274,23 @@ hipError_t launch_init(const Params &hp, const Params *dp, hipStream_t st)
 {
     Launcher L{st, nullptr, nullptr};
     sort(L, hp, dp, 1);
-    L(0, k_particle<1>, dim3(hp.ntiles), dim3(kThreads), 0, dp);
+    L(0, k_particle<1>, dim3(hp.ntiles * hp.parts), dim3(kThreads), 0, dp);
     solve(L, hp, dp);
     L(0, k_init_nodes, dim3(kGridBlocks), dim3(kThreads), 0, dp);
-    L(0, k_particle<2>, dim3(hp.ntiles), dim3(kThreads), 0, dp);
+    L(0, k_particle<2>, dim3(hp.ntiles * hp.parts), dim3(kThreads), 0, dp);
     return hipGetLastError();
 }
 
 int step_launches(const Params &hp) { return 2 * hp.iters + 1 + 9; }   // at most
 
-hipError_t launch_step(const Params &hp, const Params *dp, hipStream_t st, hipEvent_t *ev, int *groups, int *nlaunch)
+hipError_t launch_step(const Params &hp, const Params *dp, hipStream_t st, hipEvent_t *ev, int *groups, int *nlaunch,
+                       bool with_sort)
 {
     Launcher L{st, ev, groups};
     solve(L, hp, dp);
-    L(1, k_particle<0>, dim3(hp.ntiles), dim3(kThreads), 0, dp);
+    L(1, k_particle<0>, dim3(hp.ntiles * hp.parts), dim3(kThreads), 0, dp);
     L(2, k_nodes, dim3(kGridBlocks), dim3(kThreads), 0, dp);
-    sort(L, hp, dp, 0);
+    if (with_sort) sort(L, hp, dp, 0);
     L(3, k_advance, dim3(1), dim3(kThreads), 0, dp);
     if (nlaunch) *nlaunch = L.k;
     return hipGetLastError();

@@ -19,8 +19,9 @@ struct pic_hyb {
     Params hp;
     Params *dp = nullptr;
     hipStream_t stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
+    hipGraph_t graph[2] = {};       // one step: [0] without the sort's launches, [1] with them
+    hipGraphExec_t gexec[2] = {};
+    int64_t steps = 0;              // steps enqueued
     int device = 0;
     std::string err;
 };
@@ -64,6 +65,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
     size_t part_bytes = 0, grid_bytes = 0;
+    int parts = 1;
     size_t px[2], py[2], pux[2], puy[2], ppz[2], pid[2];
     size_t a1, a2, psi, it[2], rhsR, rhsC, dep[2][4], W, twx, twy, lapx, lapy, count, start, tstart[2], bins, scan, pdiag, gdiag,
         state, params, ring;
@@ -78,6 +80,14 @@ struct Carver {
         return o;
     }
 };
+
+// Workgroups per particle tile: about 1024 in all (4 per CU) on a grid with few
+// tiles, each with at least 512 particles (64^2, 16 tiles, 16 particles per
+// cell: particle kernel 53 -> 17 us).
+int particle_parts(int64_t ntiles, int64_t np)
+{
+    return (int)std::max<int64_t>(1, std::min<int64_t>(1024 / ntiles, np / ntiles / 512));
+}
 
 int validate(const pic_hyb_desc *d, Layout *L, std::string *err)
 {
@@ -137,7 +147,8 @@ int validate(const pic_hyb_desc *d, Layout *L, std::string *err)
     L->tstart[1] = g.take((ntiles + 1) * 4);
     L->bins = g.take(ntiles * kWinC * kWinC * 4);
     L->scan = g.take(((C + kScanChunk - 1) / kScanChunk) * 4);
-    L->pdiag = g.take(ntiles * kPDiag * 8);
+    L->parts = particle_parts((int64_t)ntiles, d->nparticles);
+    L->pdiag = g.take(ntiles * L->parts * kPDiag * 8);
     L->gdiag = g.take((size_t)kGridBlocks * kGDiag * 8);
     L->state = g.take(sizeof(State));
     L->params = g.take(sizeof(Params));
@@ -152,20 +163,31 @@ T *at(void *base, size_t off)
     return (T *)((char *)base + off);
 }
 
-int capture(pic_hyb *h)
+void drop_graphs(pic_hyb *h)
+{
+    for (int k = 0; k < 2; ++k) {
+        if (h->gexec[k]) (void)hipGraphExecDestroy(h->gexec[k]);
+        if (h->graph[k]) (void)hipGraphDestroy(h->graph[k]);
+    }
+}
+
+// One step as a graph: [0] without the sort's launches, [1] with them (only
+// where some steps sort).
+int capture(pic_hyb *h, int which)
 {
     if (h->desc.flags & PIC_FLAG_NO_GRAPH) return PIC_OK;
+    if (which == 1 && h->desc.sort_every == 0) return PIC_OK;
     hipStream_t cs;
     HCHK(&h->err, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed);
     if (e == hipSuccess) {
-        hipError_t le = launch_step(h->hp, h->dp, cs, nullptr, nullptr, nullptr);
+        hipError_t le = launch_step(h->hp, h->dp, cs, nullptr, nullptr, nullptr, which == 1);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(cs, &g);
         if (le != hipSuccess) e = le;
         if (e == hipSuccess) {
-            e = hipGraphInstantiate(&h->gexec, g, nullptr, nullptr, 0);
-            if (e == hipSuccess) h->graph = g;
+            e = hipGraphInstantiate(&h->gexec[which], g, nullptr, nullptr, 0);
+            if (e == hipSuccess) h->graph[which] = g;
             else (void)hipGraphDestroy(g);
         }
     }
@@ -245,6 +267,7 @@ int pic_hyb_init(const pic_hyb_desc *desc, void *particles, size_t particle_byte
     P.ltile = log2_pow2(P.tile);
     P.tiles_x = desc->nx / P.tile;
     P.ntiles = (desc->nx / P.tile) * (desc->ny / P.tile);
+    P.parts = L.parts;
     P.np = N;
     P.cells = (int64_t)desc->nx * desc->ny;
     P.dx = desc->dx;
@@ -339,9 +362,11 @@ int pic_hyb_init(const pic_hyb_desc *desc, void *particles, size_t particle_byte
     ICHK(launch_init(P, h->dp, st));
     ICHK(hipStreamSynchronize(st));
 #undef ICHK
-    rc = capture(h);
+    rc = capture(h, 0);
+    if (rc == PIC_OK) rc = capture(h, 1);
     if (rc != PIC_OK) {
         g_hyb_error = h->err;
+        drop_graphs(h);
         delete h;
         return rc;
     }
@@ -354,8 +379,12 @@ int pic_hyb_step(pic_hyb *h, int32_t nsteps)
     if (!h) return fail(nullptr, PIC_E_INVALID_ARG, "null handle");
     if (nsteps < 0) return fail(&h->err, PIC_E_INVALID_ARG, "nsteps < 0");
     for (int32_t i = 0; i < nsteps; ++i) {
-        if (h->gexec) HCHK(&h->err, hipGraphLaunch(h->gexec, h->stream));
-        else HCHK(&h->err, launch_step(h->hp, h->dp, h->stream, nullptr, nullptr, nullptr));
+        const int64_t every = h->desc.sort_every;
+        if (h->gexec[0])
+            HCHK(&h->err, hipGraphLaunch(h->gexec[every > 0 && h->steps % every == every - 1 ? 1 : 0], h->stream));
+        else
+            HCHK(&h->err, launch_step(h->hp, h->dp, h->stream, nullptr, nullptr, nullptr));
+        h->steps += 1;
     }
     return PIC_OK;
 }
@@ -378,6 +407,7 @@ int pic_hyb_step_profiled(pic_hyb *h, int32_t nsteps, double *group_ms)
             rc = hip_fail(&h->err, e, "profiled step");
             break;
         }
+        h->steps += 1;
         for (int k = 0; k < nl; ++k) {
             float ms = 0.f;
             if (hipEventElapsedTime(&ms, ev[2 * k], ev[2 * k + 1]) == hipSuccess) group_ms[groups[k]] += ms;
@@ -452,8 +482,7 @@ int pic_hyb_destroy(pic_hyb *h)
 {
     if (!h) return PIC_OK;
     (void)hipStreamSynchronize(h->stream);
-    if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
-    if (h->graph) (void)hipGraphDestroy(h->graph);
+    drop_graphs(h);
     delete h;
     return PIC_OK;
 }

@@ -92,6 +92,25 @@ def test_hybrid_parity_fp64_rectangular(pic, n):
     g.close()
 
 
+@pytest.mark.parametrize("n,iters", [((8, 8), 1), ((16, 8), 2), ((8, 32), 3), ((64, 128), 2), ((1024, 8), 2),
+                                     ((8, 1024), 2), ((8, 2048), 2), ((2048, 8), 2), ((1024, 16), 2), ((16, 1024), 3),
+                                     ((4096, 16), 1), ((8, 4096), 1)])
+def test_hybrid_solve_edges(pic, n, iters):
+    """The solve's paths and their edges: one workgroup up to 8192 nodes (8^2,
+    odd and even numbers of radix-2 stages on either axis, exactly 8192) and
+    the passes above it (1, 2 and 4 column pairs per workgroup, the shortest
+    and longest rows and columns), with few particles per tile and with
+    several workgroups per tile; 4 steps, FP64 to 1e-9 as above."""
+    log(f"case hybrid solve edges {n} iters {iters}")
+    wl = replace(synth.H1, n=n, ppc=3 if n[0] * n[1] > 1024 else 40, iters=iters, steps=4, name=f"H1-{n[0]}x{n[1]}")
+    orc, g = _pair(pic, wl, sort_every=2)
+    _compare(orc, g, wl, 1e-11)
+    orc.step(wl.steps)
+    g.step(wl.steps)
+    _compare(orc, g, wl, 1e-9)
+    g.close()
+
+
 def _same_state(r0, r1):
     """Bitwise equality of two runs' potential, canonical momentum and
     particles (by id: the cell sort's order within a cell is free)."""
