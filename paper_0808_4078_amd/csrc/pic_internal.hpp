@@ -183,14 +183,15 @@ constexpr int kBatchGroups = 3;
 struct BatchTable {
     int nruns;
     int n_cell_blocks;    // 256-cell blocks over all runs
-    int nst_blocks;       // max over runs of ceil(nspecies * tiles / 256)
-    int max_species;
+    int fused;            // 1 if every run has the planes of the fused field passes (KParams::Ft)
     int max_fd_blocks;    // max over runs of KParams::fd_blocks
     int coulomb;          // 1 if any run has a species on the Coulomb scattering model
     const KParams *const *kp;   // [nruns] device parameter blocks
     const int2 *cell_blocks;    // [n_cell_blocks] (run, block of that run)
     BatchGroup grp[kBatchGroups];
 };
+// workgroups per run of an ensemble for the two phases of its re-layout
+constexpr int kBatchCountBlocks = 32;
 constexpr int kBatchRebinBlocks = 256;
 
 // Host-callable launchers (defined in the .hip translation units).
@@ -210,12 +211,9 @@ int binary_blocks(bool mixed, int64_t tile_cells, int64_t ppc, int *width);
 constexpr size_t kCkptParamBytes = 3256;
 // ev: NULL, or two events (start/stop) per launch
 hipError_t launch_step(const KParams &hp, const KParams *dp, hipStream_t s, hipEvent_t *ev = nullptr);
-// Batch step: the particle kernel is one launch per tile group (empty groups
-// launch one workgroup that exits), so a batch step has kBatchKernels
-// dispatches; kBatchKernelGroup maps them to the groups above.
+// Batch step: batch_kernel_groups fills groups[] as step_kernel_groups does.
 // pblocks[g]: persistent workgroups of group g's particle launch.
-constexpr int kBatchKernels = 15;
-constexpr int kBatchKernelGroup[kBatchKernels] = {0, 1, 1, 1, 2, 2, 2, 2, 2, 2, 3, 4, 4, 4, 5};
+int batch_kernel_groups(int precision, int ndim, const BatchTable &ht, int *groups);
 hipError_t launch_batch_step(int precision, int ndim, const BatchTable &ht, const BatchTable *dt,
                              const int pblocks[kBatchGroups], hipStream_t s, hipEvent_t *ev = nullptr);
 // Workgroups of the batch particle kernel of tile group g that fit on one

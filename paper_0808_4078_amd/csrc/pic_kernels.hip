@@ -22,8 +22,9 @@
 //                    after the move and max |rho^{n+1} - rho^n + dt div J|
 //   k_advance        diagnostic record, counter reset, step/parity update (with
 //                    few tiles one workgroup of k_end)
-// Ensembles, and runs without room for the second set of field planes, take
-// the passes one by one (rebin_*, reduce_j, yee_b, yee_e, yee_b).
+// Ensembles go through the same passes (kb_*).  3D runs with many tiles, and
+// runs without room for the second set of field planes, take the field passes
+// one by one (reduce_j, yee_b, yee_e, yee_b).
 //
 // The numerical scheme is the relativistic Boris push (Boris 1970), the
 // Esirkepov (2001) charge-conserving deposit with the linear form factor and
@@ -1234,12 +1235,6 @@ __device__ __forceinline__ void rebin_count_bin(const KParams *__restrict__ kp, 
     kp->rb_fill[i] = c;
 }
 
-__device__ __forceinline__ void rebin_count_body(const KParams *__restrict__ kp, int bid, int nb)
-{
-    const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
-    if (i < (int64_t)kp->nspecies * kp->g.ntiles) rebin_count_bin<false>(kp, i);
-}
-
 template <typename R>
 __device__ __forceinline__ int tile_of(const KParams *kp, const SpeciesDev &S, int set, int64_t p)
 {
@@ -1977,20 +1972,6 @@ int binary_blocks(bool mixed, int64_t tile_cells, int64_t ppc, int *width)
     return (int)nblk;
 }
 
-template <typename R>
-__device__ __forceinline__ void rebin_count_ovf_body(const KParams *__restrict__ kp, int bid, int nb)
-{
-    const DevState *st = kp->state;
-    if (!st->rebin) return;
-    const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
-    for (int s = 0; s < kp->nspecies; ++s) {
-        const SpeciesDev &S = kp->sp[s];
-        const int64_t n = min((int64_t)st->ovf_count[s], (int64_t)S.ovf_cap);
-        for (int64_t p = i; p < n; p += (int64_t)nb * blockDim.x)
-            atomicAdd(&kp->rb_count[(int64_t)s * kp->g.ntiles + tile_of<R>(kp, S, 2, p)], 1);
-    }
-}
-
 // one block per species: capacities = count + uniform reserve, exclusive scan
 __device__ __forceinline__ void rebin_scan_body(const KParams *__restrict__ kp, int bid, int nb)
 {
@@ -2156,14 +2137,8 @@ __device__ __forceinline__ void rebin_finalize_bin(const KParams *__restrict__ k
     S.cnt_back[dst * ntiles + t] = 0;
 }
 
-__device__ __forceinline__ void rebin_finalize_body(const KParams *__restrict__ kp, int bid, int nb)
-{
-    const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
-    if (i < (int64_t)kp->nspecies * kp->g.ntiles) rebin_finalize_bin(kp, i);
-}
-
-// A single run's re-layout in two phases, each the work of some workgroups of
-// the two field kernels (k_mid, k_end) -- or of a launch of its own where
+// A run's re-layout in two phases, each the work of some workgroups of the two
+// field kernels (k_mid, k_end, and kb_* for ensembles) -- or of a launch of its own where
 // something must run between them -- so that a step without an overflow pays
 // for no launch of it.  A phase ends in its last workgroup to arrive:
 //   relayout_count    counts of the bins and of the overflow list, then the
@@ -2867,30 +2842,33 @@ __global__ __launch_bounds__(256) void k_end(const KParams *__restrict__ kp, int
     }
 }
 
-#define PIC_BATCH_KERNEL(NAME, BODY)                                                    \
-    __global__ __launch_bounds__(256) void kb_##NAME(const BatchTable *__restrict__ bt) \
-    {                                                                                   \
-        BODY(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);                                \
+// The same two passes over an ensemble (32 uneven runs: 15 launches per step
+// became 7, five steps 13.44 -> 13.34 ms; 7 runs: two steps 2.04 -> 1.98 ms;
+// the particle kernels of the tile edges side by side on streams of their own
+// measured 3% slower): workgroups [0, nf) through the (run,
+// 256-cell block) map (FIELDS; else nf = 0 and the field passes are launched
+// one by one), then nr workgroups per run for its re-layout.
+template <typename R, int D, bool FIELDS>
+__global__ __launch_bounds__(256) void kb_mid(const BatchTable *__restrict__ bt, int nf, int nr)
+{
+    const int b = blockIdx.x;
+    if (FIELDS && b < nf) {
+        const int2 cb = bt->cell_blocks[b];
+        field_mid<R, D, false, false>(bt->kp[cb.x], cb.y);
+    } else {
+        relayout_count<R, false>(bt->kp[(b - nf) / nr], (b - nf) % nr, nr);
     }
-PIC_BATCH_KERNEL(rebin_count, rebin_count_body)
-PIC_BATCH_KERNEL(rebin_scan, rebin_scan_body)
-PIC_BATCH_KERNEL(rebin_finalize, rebin_finalize_body)
-#undef PIC_BATCH_KERNEL
-
-template <typename R>
-__global__ __launch_bounds__(256) void kb_rebin_count_ovf(const BatchTable *__restrict__ bt)
-{
-    rebin_count_ovf_body<R>(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);
 }
-template <typename R>
-__global__ __launch_bounds__(256) void kb_rebin_scatter(const BatchTable *__restrict__ bt)
+template <typename R, int D, bool FIELDS>
+__global__ __launch_bounds__(256) void kb_end(const BatchTable *__restrict__ bt, int nf, int nr)
 {
-    rebin_scatter_body<R>(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);
-}
-template <typename R>
-__global__ __launch_bounds__(256) void kb_rebin_scatter_ovf(const BatchTable *__restrict__ bt)
-{
-    rebin_scatter_ovf_body<R>(bt->kp[blockIdx.y], blockIdx.x, gridDim.x);
+    const int b = blockIdx.x;
+    if (FIELDS && b < nf) {
+        const int2 cb = bt->cell_blocks[b];
+        field_end<R, D>(bt->kp[cb.x], cb.y);
+    } else {
+        (void)relayout_scatter<R>(bt->kp[(b - nf) / nr], (b - nf) % nr, nr);
+    }
 }
 
 template <typename R, int D, bool SPLIT>
@@ -3296,63 +3274,85 @@ int step_kernel_groups(const KParams &hp, int *groups)
     return e == hipSuccess ? L.k : -1;
 }
 
-// The same kernel sequence over a whole ensemble (kBatchKernels launches):
-// field diag | particle, one per tile group | 6 x re-layout | J reduction |
-// 3 x Yee | advance.
+// The same kernel sequence over a whole ensemble: field record | particle, one
+// launch per tile edge in use | first field pass and re-layout counts | second
+// field pass and re-layout copies | end of step.  3D members keep the field
+// passes apart (reduction, B, E, B).
 template <typename R, typename A, int D, int T>
-static void batch_particle(Launcher &L, const BatchTable &ht, const BatchTable *dt, int pblocks)
+static void batch_particle(Launcher &L, const BatchTable &ht, const BatchTable *dt, const int *pb)
 {
     constexpr int g = T == 8 ? 0 : (T == 16 ? 1 : 2);
-    const unsigned nb = ht.grp[g].n_items > 0 ? (unsigned)std::max(1, pblocks) : 1u;
+    if (ht.grp[g].n_items == 0) return;
     const int shape = ht.grp[g].shape;
     const unsigned pbk = (unsigned)shape_threads(sizeof(R) == 8, D, shape);
-    if (ht.coulomb) L(batch_particle_kernel<R, A, D, T, true>(shape), dim3(nb), dim3(pbk), dt);
-    else L(batch_particle_kernel<R, A, D, T, false>(shape), dim3(nb), dim3(pbk), dt);
+    auto k = ht.coulomb ? batch_particle_kernel<R, A, D, T, true>(shape) : batch_particle_kernel<R, A, D, T, false>(shape);
+    L(k, dim3((unsigned)std::max(1, pb[g])), dim3(pbk), dt);
 }
 
 template <typename R, int D>
-static hipError_t batch_kernels(const BatchTable &ht, const BatchTable *dt, const int *pb, hipStream_t st,
-                                hipEvent_t *ev)
+static hipError_t batch_kernels(const BatchTable &ht, const BatchTable *dt, const int *pb, Launcher &L)
 {
     using A = double;
     const unsigned nr = (unsigned)ht.nruns;
-    Launcher L{st, ev};
+    L.grp = 0;
     L(kb_field_diag<R>, dim3(ht.max_fd_blocks, nr), dim3(256), dt);
+    L.grp = 1;
     if constexpr (D == 3) {
-        batch_particle<R, A, 3, 8>(L, ht, dt, pb[0]);
-        // fixed dispatch count: two one-workgroup launches that find the
-        // queue of group 0 exhausted and exit (3D has one tile edge)
-        batch_particle<R, A, 3, 8>(L, ht, dt, 0);
-        batch_particle<R, A, 3, 8>(L, ht, dt, 0);
+        batch_particle<R, A, 3, 8>(L, ht, dt, pb);
     } else {
-        batch_particle<R, A, 2, 8>(L, ht, dt, pb[0]);
-        batch_particle<R, A, 2, 16>(L, ht, dt, pb[1]);
-        batch_particle<R, A, 2, 32>(L, ht, dt, pb[2]);
+        batch_particle<R, A, 2, 8>(L, ht, dt, pb);
+        batch_particle<R, A, 2, 16>(L, ht, dt, pb);
+        batch_particle<R, A, 2, 32>(L, ht, dt, pb);
     }
-    L(kb_rebin_count, dim3(ht.nst_blocks, nr), dim3(256), dt);
-    L(kb_rebin_count_ovf<R>, dim3(kBatchRebinBlocks, nr), dim3(256), dt);
-    L(kb_rebin_scan, dim3(ht.max_species, nr), dim3(256), dt);
-    L(kb_rebin_scatter<R>, dim3(kBatchRebinBlocks, nr), dim3(256), dt);
-    L(kb_rebin_scatter_ovf<R>, dim3(kBatchRebinBlocks, nr), dim3(256), dt);
-    L(kb_rebin_finalize, dim3(ht.nst_blocks, nr), dim3(256), dt);
-    L(kb_reduce_j<R, D>, dim3(ht.n_cell_blocks), dim3(256), dt);
-    L(kb_yee_b<R, D>, dim3(ht.n_cell_blocks), dim3(256), dt, 0.5);
-    L(kb_yee_e<R, D>, dim3(ht.n_cell_blocks), dim3(256), dt);
-    L(kb_yee_b<R, D>, dim3(ht.n_cell_blocks), dim3(256), dt, 0.5);
+    const int nf = ht.n_cell_blocks;
+    const unsigned rc = kBatchCountBlocks * nr, rs = kBatchRebinBlocks * nr;
+    if (D == 2 && ht.fused) {
+        L.grp = 3;
+        L(kb_mid<R, D, true>, dim3((unsigned)nf + rc), dim3(256), dt, nf, kBatchCountBlocks);
+        L.grp = 4;
+        L(kb_end<R, D, true>, dim3((unsigned)nf + rs), dim3(256), dt, nf, kBatchRebinBlocks);
+    } else {
+        L.grp = 2;
+        L(kb_mid<R, D, false>, dim3(rc), dim3(256), dt, 0, kBatchCountBlocks);
+        L(kb_end<R, D, false>, dim3(rs), dim3(256), dt, 0, kBatchRebinBlocks);
+        L.grp = 3;
+        L(kb_reduce_j<R, D>, dim3((unsigned)nf), dim3(256), dt);
+        L.grp = 4;
+        L(kb_yee_b<R, D>, dim3((unsigned)nf), dim3(256), dt, 0.5);
+        L(kb_yee_e<R, D>, dim3((unsigned)nf), dim3(256), dt);
+        L(kb_yee_b<R, D>, dim3((unsigned)nf), dim3(256), dt, 0.5);
+    }
+    L.grp = 5;
     L(kb_advance, dim3(nr), dim3(kAdvanceThreads), dt);
-    return hipGetLastError();
+    return L.dry ? hipSuccess : hipGetLastError();
+}
+
+static hipError_t batch_step(int precision, int ndim, const BatchTable &ht, const BatchTable *dt, const int *pblocks,
+                             Launcher &L)
+{
+    if (ndim == 3) {
+        if (ht.grp[1].n_items || ht.grp[2].n_items) return hipErrorInvalidValue;
+        return precision == PIC_PREC_MIXED ? batch_kernels<float, 3>(ht, dt, pblocks, L)
+                                           : batch_kernels<double, 3>(ht, dt, pblocks, L);
+    }
+    return precision == PIC_PREC_MIXED ? batch_kernels<float, 2>(ht, dt, pblocks, L)
+                                       : batch_kernels<double, 2>(ht, dt, pblocks, L);
+}
+
+int batch_kernel_groups(int precision, int ndim, const BatchTable &ht, int *groups)
+{
+    const int pb[kBatchGroups] = {1, 1, 1};
+    Launcher L{nullptr, nullptr};
+    L.groups = groups;
+    L.dry = true;
+    return batch_step(precision, ndim, ht, nullptr, pb, L) == hipSuccess ? L.k : -1;
 }
 
 hipError_t launch_batch_step(int precision, int ndim, const BatchTable &ht, const BatchTable *dt,
                              const int pblocks[kBatchGroups], hipStream_t st, hipEvent_t *ev)
 {
-    if (ndim == 3) {
-        if (ht.grp[1].n_items || ht.grp[2].n_items) return hipErrorInvalidValue;
-        return precision == PIC_PREC_MIXED ? batch_kernels<float, 3>(ht, dt, pblocks, st, ev)
-                                           : batch_kernels<double, 3>(ht, dt, pblocks, st, ev);
-    }
-    return precision == PIC_PREC_MIXED ? batch_kernels<float, 2>(ht, dt, pblocks, st, ev)
-                                       : batch_kernels<double, 2>(ht, dt, pblocks, st, ev);
+    Launcher L{st, ev};
+    return batch_step(precision, ndim, ht, dt, pblocks, L);
 }
 
 template <typename R, int D, int T>

@@ -1509,14 +1509,14 @@ int pic_batch_init(int nruns, pic_run *const *runs, void *table, size_t table_by
     std::vector<const KParams *> kps(nruns);
     std::vector<int2> cells;
     cells.reserve(B.n_cell_blocks);
-    int max_species = 0, nst = 0, max_fd = 0;
+    int max_fd = 0;
+    bool fused = true;
     for (int i = 0; i < nruns; ++i) {
         const pic_run *r = runs[i];
         kps[i] = r->dp;
         const int cb = (int)((r->L.g.cells + 255) / 256);
         for (int k = 0; k < cb; ++k) cells.push_back(make_int2(i, k));
-        max_species = std::max(max_species, r->ns);
-        nst = std::max(nst, (int)((r->ns * (int64_t)r->L.g.ntiles + 255) / 256));
+        fused = fused && r->hp.Ft != nullptr;
         max_fd = std::max(max_fd, r->hp.fd_blocks);
     }
     // work items: runs in order of decreasing particles per tile (the longest
@@ -1545,8 +1545,7 @@ int pic_batch_init(int nruns, pic_run *const *runs, void *table, size_t table_by
     memset(&H, 0, sizeof(H));
     H.nruns = nruns;
     H.n_cell_blocks = B.n_cell_blocks;
-    H.nst_blocks = std::max(1, nst);
-    H.max_species = max_species;
+    H.fused = fused ? 1 : 0;
     H.max_fd_blocks = max_fd;
     H.coulomb = 0;
     for (int i = 0; i < nruns; ++i) H.coulomb |= runs[i]->hp.coulomb;
@@ -1646,7 +1645,10 @@ int pic_batch_step_profiled(pic_batch *b, int32_t nsteps, double *group_ms)
 {
     if (!b || !group_ms) return fail(b ? &b->err : nullptr, PIC_E_INVALID_ARG, "bad argument");
     if (nsteps < 0) return fail(&b->err, PIC_E_INVALID_ARG, "nsteps < 0");
-    return profiled_steps(&b->err, b->stream, nsteps, kBatchKernels, kBatchKernelGroup, group_ms,
+    int groups[kMaxStepKernels];
+    const int nk = batch_kernel_groups(b->precision, b->ndim, b->ht, groups);
+    if (nk <= 0 || nk > kMaxStepKernels) return fail(&b->err, PIC_E_UNSUPPORTED, "no kernel sequence for this batch");
+    return profiled_steps(&b->err, b->stream, nsteps, nk, groups, group_ms,
                           [&](hipEvent_t *ev) {
                               hipError_t e = launch_batch_step(b->precision, b->ndim, b->ht, b->dt, b->pblocks,
                                                                b->stream, ev);

@@ -241,3 +241,35 @@ def test_batch_with_coulomb_members(pic, prec, bar):
     batch.close()
     for r in alone + members:
         r.close()
+
+
+@pytest.mark.parametrize("shapes", [[((32, 32), 8), ((64, 48), 16), ((32, 64), 32)], [((16, 16, 16), 8), ((8, 16, 24), 8)]])
+def test_batch_members_that_overflow(pic, shapes):
+    """Reserves of 64 slots: members are laid out again at different steps,
+    inside the passes that the others' fields go through (in 3D in launches of
+    their own), as they are when stepped alone."""
+    log(f"case batch with re-layouts {shapes}")
+
+    def runs():
+        out = []
+        for i, (n, tile) in enumerate(shapes):
+            wl = synth.beam_plasma(n, ppc=12, u_th_beam=0.5, u_th_plasma=0.2, nu=0.1, seed=synth.SEED + 300 + i)
+            g, sp = pic.workload_descs(wl, precision=pic.PIC_PREC_MIXED, tile=tile, diag_every=1, reserve=0.001)
+            out.append(pic.Run(g, sp))
+        return out
+    alone, members = runs(), runs()
+    batch = pic.Batch(members)
+    batch.step(60)
+    batch.sync()
+    rebins = []
+    for m, r in zip(members, alone):
+        r.step(60)
+        r.sync()
+        _compare(pic, m, r, 1e-5)
+        rebins.append(m.diagnostics()["rebins"])
+        assert rebins[-1] == r.diagnostics()["rebins"]
+    log(f"  re-layouts {rebins}")
+    assert sum(rebins) > 0
+    batch.close()
+    for r in alone + members:
+        r.close()
