@@ -294,14 +294,15 @@ int pic_step_profiled(pic_run *run, int32_t nsteps, double *group_ms);
 int pic_sync(pic_run *run);
 
 /* How a run (or a batch) enqueues its steps.
- *   graph           1 if a step is the replay of one captured hipGraph, 0 if
- *                   its kernels are launched one by one (PIC_FLAG_NO_GRAPH,
+ *   graph           1 if steps are replays of captured hipGraphs (a run's, of
+ *                   four steps where a call asks for as many), 0 if their
+ *                   kernels are launched one by one (PIC_FLAG_NO_GRAPH,
  *                   or a run on the library's scratch).
  *   static_scratch  1 if the run lives on the library's own scratch
  *                   (pic_init_static_scratch).
  *   steps_enqueued  steps enqueued so far (graph_launches + direct_steps,
  *                   plus the steps of a restored checkpoint).
- *   graph_launches  steps enqueued as one graph replay.
+ *   graph_launches  steps enqueued by graph replays.
  *   direct_steps    steps enqueued kernel by kernel (including the
  *                   measurement path pic_step_profiled).
  *   scratch_bytes   scratch the run uses (pic_query's scratch_bytes).
@@ -591,7 +592,7 @@ int pic_hyb_init(const pic_hyb_desc *desc, void *particles, size_t particle_byte
                  size_t grid_bytes, void *hip_stream, const double *x, const double *y, const double *ux,
                  const double *uy, const double *uz, pic_hyb **out);
 
-/* Enqueues nsteps steps (one captured graph per step unless
+/* Enqueues nsteps steps (replays of captured graphs of one step or four unless
  * PIC_FLAG_NO_GRAPH).  Asynchronous. */
 int pic_hyb_step(pic_hyb *h, int32_t nsteps);
 

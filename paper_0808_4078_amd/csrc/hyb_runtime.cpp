@@ -19,8 +19,8 @@ struct pic_hyb {
     Params hp;
     Params *dp = nullptr;
     hipStream_t stream = nullptr;
-    hipGraph_t graph[2] = {};       // one step: [0] without the sort's launches, [1] with them
-    hipGraphExec_t gexec[2] = {};
+    hipGraph_t graph[3] = {};       // a step without the sort's launches, one with them, kChainSteps without
+    hipGraphExec_t gexec[3] = {};
     int64_t steps = 0;              // steps enqueued
     int device = 0;
     std::string err;
@@ -165,23 +165,28 @@ T *at(void *base, size_t off)
 
 void drop_graphs(pic_hyb *h)
 {
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < 3; ++k) {
         if (h->gexec[k]) (void)hipGraphExecDestroy(h->gexec[k]);
         if (h->graph[k]) (void)hipGraphDestroy(h->graph[k]);
     }
 }
 
-// One step as a graph: [0] without the sort's launches, [1] with them (only
-// where some steps sort).
+// [0] one step without the sort's launches; [1] one with them (only where some
+// steps sort); [2] kChainSteps steps without (only where as many follow each
+// other).
 int capture(pic_hyb *h, int which)
 {
     if (h->desc.flags & PIC_FLAG_NO_GRAPH) return PIC_OK;
-    if (which == 1 && h->desc.sort_every == 0) return PIC_OK;
+    const int every = h->desc.sort_every;
+    if (which == 1 && every == 0) return PIC_OK;
+    if (which == 2 && every > 0 && every <= kChainSteps) return PIC_OK;
     hipStream_t cs;
     HCHK(&h->err, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed);
     if (e == hipSuccess) {
-        hipError_t le = launch_step(h->hp, h->dp, cs, nullptr, nullptr, nullptr, which == 1);
+        hipError_t le = hipSuccess;
+        for (int k = 0; k < (which == 2 ? kChainSteps : 1) && le == hipSuccess; ++k)
+            le = launch_step(h->hp, h->dp, cs, nullptr, nullptr, nullptr, which == 1);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(cs, &g);
         if (le != hipSuccess) e = le;
@@ -364,6 +369,7 @@ int pic_hyb_init(const pic_hyb_desc *desc, void *particles, size_t particle_byte
 #undef ICHK
     rc = capture(h, 0);
     if (rc == PIC_OK) rc = capture(h, 1);
+    if (rc == PIC_OK) rc = capture(h, 2);
     if (rc != PIC_OK) {
         g_hyb_error = h->err;
         drop_graphs(h);
@@ -378,13 +384,17 @@ int pic_hyb_step(pic_hyb *h, int32_t nsteps)
 {
     if (!h) return fail(nullptr, PIC_E_INVALID_ARG, "null handle");
     if (nsteps < 0) return fail(&h->err, PIC_E_INVALID_ARG, "nsteps < 0");
-    for (int32_t i = 0; i < nsteps; ++i) {
-        const int64_t every = h->desc.sort_every;
-        if (h->gexec[0])
-            HCHK(&h->err, hipGraphLaunch(h->gexec[every > 0 && h->steps % every == every - 1 ? 1 : 0], h->stream));
-        else
+    const int64_t every = h->desc.sort_every;
+    for (int32_t i = 0, n; i < nsteps; i += n) {
+        n = 1;
+        if (h->gexec[0]) {
+            const int64_t left = every > 0 ? every - 1 - h->steps % every : nsteps;   // steps before the next sort
+            if (h->gexec[2] && nsteps - i >= kChainSteps && left >= kChainSteps) n = kChainSteps;
+            HCHK(&h->err, hipGraphLaunch(h->gexec[n > 1 ? 2 : left == 0 ? 1 : 0], h->stream));
+        } else {
             HCHK(&h->err, launch_step(h->hp, h->dp, h->stream, nullptr, nullptr, nullptr));
-        h->steps += 1;
+        }
+        h->steps += n;
     }
     return PIC_OK;
 }

@@ -309,8 +309,8 @@ struct pic_run {
     int64_t steps_enqueued = 0;
     int64_t graph_launches = 0;  // steps enqueued as one graph replay
     int64_t direct_steps = 0;    // steps enqueued kernel by kernel
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
+    hipGraph_t graph[2] = {};   // one step, and kChainSteps steps
+    hipGraphExec_t gexec[2] = {};
     pic_batch *owner = nullptr;  // batch this run is a member of
     int static_device = -1;      // device whose library scratch this run holds (pic_init_static_scratch)
     std::mutex read_mu;          // held by pic_read_particles (its places and parts lie in the run's buffers)
@@ -475,17 +475,18 @@ int loader_moments(pic_run *r)
     return PIC_OK;
 }
 
-// Captures one step as a graph on a private stream.  A failure is returned
-// as PIC_E_HIP (the caller can ask for kernel-by-kernel steps with
-// PIC_FLAG_NO_GRAPH instead).
-int capture_graph(pic_run *r)
+// Captures one step (which = 0) or kChainSteps of them (which = 1) as a graph
+// on a private stream.  A failure is returned as PIC_E_HIP (the caller can ask
+// for kernel-by-kernel steps with PIC_FLAG_NO_GRAPH instead).
+int capture_graph(pic_run *r, int which)
 {
     hipStream_t cs;
     HIPCHK(r, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     const char *what = "hipStreamBeginCapture";
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed);
     if (e == hipSuccess) {
-        hipError_t le = launch_step(r->hp, r->dp, cs);
+        hipError_t le = hipSuccess;
+        for (int k = 0; k < (which ? kChainSteps : 1) && le == hipSuccess; ++k) le = launch_step(r->hp, r->dp, cs);
         hipGraph_t g = nullptr;
         what = "hipStreamEndCapture";
         e = hipStreamEndCapture(cs, &g);
@@ -495,8 +496,8 @@ int capture_graph(pic_run *r)
         }
         if (e == hipSuccess) {
             what = "hipGraphInstantiate";
-            e = hipGraphInstantiate(&r->gexec, g, nullptr, nullptr, 0);
-            if (e == hipSuccess) r->graph = g;
+            e = hipGraphInstantiate(&r->gexec[which], g, nullptr, nullptr, 0);
+            if (e == hipSuccess) r->graph[which] = g;
             else (void)hipGraphDestroy(g);
         } else if (g) {
             (void)hipGraphDestroy(g);
@@ -504,8 +505,8 @@ int capture_graph(pic_run *r)
     }
     (void)hipStreamDestroy(cs);
     if (e != hipSuccess) {
-        r->gexec = nullptr;
-        r->graph = nullptr;
+        r->gexec[which] = nullptr;
+        r->graph[which] = nullptr;
         (void)hipGetLastError();
         return hip_fail(r, e, what);
     }
@@ -1007,7 +1008,8 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
     }
     INIT_CHK(hipStreamSynchronize(r->stream));
     if (!(grid->flags & PIC_FLAG_NO_GRAPH)) {
-        rc = capture_graph(r);
+        rc = capture_graph(r, 0);
+        if (rc == PIC_OK) rc = capture_graph(r, 1);
         if (rc) {
             g_last_error = r->err;
             delete r;
@@ -1141,15 +1143,17 @@ int pic_step(pic_run *r, int32_t nsteps)
     if (!r) return fail(nullptr, PIC_E_INVALID_ARG, "null handle");
     if (nsteps < 0) return fail(&r->err, PIC_E_INVALID_ARG, "nsteps < 0");
     if (r->owner) return fail(&r->err, PIC_E_STATE, "run is a member of a batch; step the batch");
-    for (int32_t i = 0; i < nsteps; ++i) {
-        if (r->gexec) {
-            HIPCHK(r, hipGraphLaunch(r->gexec, r->stream));
-            r->graph_launches += 1;
+    for (int32_t i = 0, n; i < nsteps; i += n) {
+        n = 1;
+        if (r->gexec[0]) {
+            if (r->gexec[1] && nsteps - i >= kChainSteps) n = kChainSteps;
+            HIPCHK(r, hipGraphLaunch(r->gexec[n > 1 ? 1 : 0], r->stream));
+            r->graph_launches += n;
         } else {
             HIPCHK(r, launch_step(r->hp, r->dp, r->stream));
             r->direct_steps += 1;
         }
-        r->steps_enqueued += 1;
+        r->steps_enqueued += n;
     }
     return PIC_OK;
 }
@@ -1158,7 +1162,7 @@ int pic_info(pic_run *r, pic_run_info *out)
 {
     if (!r || !out) return fail(r ? &r->err : nullptr, PIC_E_INVALID_ARG, "null argument");
     memset(out, 0, sizeof(*out));
-    out->graph = r->gexec ? 1 : 0;
+    out->graph = r->gexec[0] ? 1 : 0;
     out->static_scratch = r->static_device >= 0 ? 1 : 0;
     out->steps_enqueued = r->steps_enqueued;
     out->graph_launches = r->graph_launches;
@@ -1327,8 +1331,10 @@ int pic_destroy(pic_run *r)
     if (r->owner) return fail(&r->err, PIC_E_STATE, "run is a member of a batch; destroy the batch first");
     // the caller frees the buffers once this returns: let every enqueued step finish first
     const hipError_t e = hipStreamSynchronize(r->stream);
-    if (r->gexec) (void)hipGraphExecDestroy(r->gexec);
-    if (r->graph) (void)hipGraphDestroy(r->graph);
+    for (int k = 0; k < 2; ++k) {
+        if (r->gexec[k]) (void)hipGraphExecDestroy(r->gexec[k]);
+        if (r->graph[k]) (void)hipGraphDestroy(r->graph[k]);
+    }
     if (r->static_device >= 0) release_static_scratch(r->static_device);
     delete r;
     if (e != hipSuccess) {

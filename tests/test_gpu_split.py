@@ -89,3 +89,26 @@ def test_split_fp64_against_the_oracle(pic, n, tile, ppc):
     log(f"  fields {err:.2e}")
     g.close()
     assert err < 1e-9
+
+
+@pytest.mark.parametrize("n,tile", [((48, 32), 16), ((16, 8, 16), 8)])
+def test_counts_of_steps_in_one_call(pic, n, tile):
+    """Calls of one to eleven steps (replays of four steps and of one) against
+    as many steps launched kernel by kernel: the same bits."""
+    log(f"case steps per call {n}")
+    wl = synth.beam_plasma(n, ppc=8, u_th_beam=0.3, nu=0.1)
+    a = _run(pic, wl, tile, 0)
+    g, sp = pic.workload_descs(wl, precision=pic.PIC_PREC_MIXED, tile=tile, diag_every=1,
+                               flags=pic.PIC_FLAG_TRACK_IDS | pic.PIC_FLAG_NO_GRAPH)
+    b = pic.Run(g, sp)
+    done = 0
+    for k in (1, 3, 4, 5, 8, 11):
+        a.step(k)
+        b.step(k)
+        done += k
+        _same(a, b)
+        ia, ib = a.info(), b.info()
+        assert ia["graph_launches"] == ib["direct_steps"] == ia["steps_enqueued"] == done
+        assert a.diagnostics()["step"] == b.diagnostics()["step"]
+    a.close()
+    b.close()
