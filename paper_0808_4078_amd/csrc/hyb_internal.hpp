@@ -21,6 +21,7 @@ constexpr int kMaxNodes = 4096;       // nodes per axis
 constexpr int kFftLds = 4096;         // complex values per FFT workgroup (64 KiB of LDS)
 constexpr int kColThreads = 1024;     // threads of a column-transform workgroup at most
 constexpr int kSmallCells = 8192;     // nodes up to which one workgroup does the whole solve
+constexpr int kSmallThreads = kSmallCells / 16;   // its threads: eight elements of half the plane each
 constexpr int kChainSteps = 4;        // steps without a sort that one graph replay enqueues: replays lie 5 us apart
 constexpr int kWaveRounds = 8;        // distinct sort keys merged per wave before plain atomics
 constexpr int kMaxTile = 16;          // tile edge (cells) of the particle kernel

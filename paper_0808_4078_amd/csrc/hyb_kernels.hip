@@ -650,18 +650,21 @@ __device__ __forceinline__ void column_pair(int P, int *a, int *b)
     *b = (2 << t) - 1 - x;
 }
 
-// Symbol at element (k, l) and its mirror image: z1 = Z(k,l), z2 = Z(-k,-l),
-// lx = lapx[l]; both are replaced.  inv: 1 / (nx ny).
-__device__ __forceinline__ void apply_symbol(const Params &P, double2 &z1, double2 &z2, int k, double lx, double inv)
+// Symbol of the plane's rows k and k + ny/2 in column l, lx = lapx[l];
+// inv: 1 / (nx ny).
+__device__ __forceinline__ double2 symbol(const Params &P, int k, double lx, double inv)
 {
-    const int m = P.ny >> 1;
-    const double2 w = P.twy[k];
+    return make_double2(inv / (-(lx + P.lapy[k]) - P.c0), inv / (-(lx + P.lapy[k + (P.ny >> 1)]) - P.c0));
+}
+// Its application at element (k, l) and the mirror image: z1 = Z(k,l), z2 =
+// Z(-k,-l), w = twy[k]; both are replaced.
+__device__ __forceinline__ void apply_symbol(double2 &z1, double2 &z2, const double2 w, const double2 sy)
+{
     const double2 E = make_double2(0.5 * (z1.x + z2.x), 0.5 * (z1.y - z2.y));
     const double2 O = make_double2(0.5 * (z1.y + z2.y), 0.5 * (z2.x - z1.x));
     const double2 wO = cmul(w, O);
-    const double s0 = inv / (-(lx + P.lapy[k]) - P.c0), s1 = inv / (-(lx + P.lapy[k + m]) - P.c0);
-    const double2 f0 = make_double2((E.x + wO.x) * s0, (E.y + wO.y) * s0);
-    const double2 f1 = make_double2((E.x - wO.x) * s1, (E.y - wO.y) * s1);
+    const double2 f0 = make_double2((E.x + wO.x) * sy.x, (E.y + wO.y) * sy.x);
+    const double2 f1 = make_double2((E.x - wO.x) * sy.y, (E.y - wO.y) * sy.y);
     const double2 e = cadd(f0, f1), o = cmul(make_double2(w.x, -w.y), csub(f0, f1));
     z1 = make_double2(e.x - o.y, e.y + o.x);                     // e + i o
     z2 = make_double2(e.x + o.y, o.x - e.y);                     // conj(e) + i conj(o)
@@ -669,22 +672,26 @@ __device__ __forceinline__ void apply_symbol(const Params &P, double2 &z1, doubl
 
 // The symbol over pair `pr` of columns a and b, elements q (in bit-reversed
 // order) at A[q * es] and B[q * es]; threads [t0, ...) of a group of nt.
-__device__ __forceinline__ void symbol_pair(const Params &P, double2 *A, double2 *B, int es, int pr, int a, int b,
-                                            int t0, int nt, double inv)
+// sym(q, second, k): the symbol's two values in column a (or b) at q, row k.
+template <class Sym>
+__device__ __forceinline__ void symbol_pair(const Params &P, double2 *A, double2 *B, int es, int pr, int t0, int nt,
+                                            const double2 *tw, Sym sym)
 {
     const int m = P.ny >> 1, lm = P.ly - 1;
-    const double la = P.lapx[brev(a, P.lx)];
     if (pr) {
-        for (int q = t0; q < m; q += nt) apply_symbol(P, A[q * es], B[mirror_pos(q) * es], brev(q, lm), la, inv);
+        for (int q = t0; q < m; q += nt) {
+            const int k = brev(q, lm);
+            apply_symbol(A[q * es], B[mirror_pos(q) * es], tw[k], sym(q, false, k));
+        }
         return;
     }
-    const double lb = P.lapx[brev(b, P.lx)];
     for (int q = t0; q < 2 * m; q += nt) {
         double2 *C = q < m ? A : B;
         const int p = q < m ? q : q - m, r = mirror_pos(p);
         if (p > r) continue;
         double2 z1 = C[p * es], z2 = C[r * es];
-        apply_symbol(P, z1, z2, brev(p, lm), q < m ? la : lb, inv);
+        const int k = brev(p, lm);
+        apply_symbol(z1, z2, tw[k], sym(p, q >= m, k));
         C[p * es] = z1;
         if (p != r) C[r * es] = z2;
     }
@@ -798,7 +805,9 @@ __global__ __launch_bounds__(kColThreads) void k_cols(const Params *__restrict__
     {
         int a, b;
         column_pair(P0 + g, &a, &b);
-        symbol_pair(P, z + g, z + G + g, 2 * G, P0 + g, a, b, (int)threadIdx.x / G, per, 1.0 / (double)P.cells);
+        const double la = P.lapx[brev(a, P.lx)], lb = P.lapx[brev(b, P.lx)], inv = 1.0 / (double)P.cells;
+        symbol_pair(P, z + g, z + G + g, 2 * G, P0 + g, (int)threadIdx.x / G, per, P.twy,
+                    [&](int, bool second, int k) { return symbol(P, k, second ? lb : la, inv); });
     }
     __syncthreads();
     fft_inverse(z, L, P.twy);
@@ -821,55 +830,259 @@ __global__ __launch_bounds__(1024) void k_rows_inv(const Params *__restrict__ pp
     }
 }
 
-// All sweeps of a small grid (up to kSmallCells nodes) in one workgroup: the
-// plane stays in LDS and R, C in registers, where the passes above would be 2
-// iters + 1 launches of one or two dozen workgroups.
-__global__ __launch_bounds__(1024) void k_solve_small(const Params *__restrict__ pp)
+// Transforms of a small grid: three radix-2 stages per pass, in registers.
+// Eight elements q apart starting at position pos of a block of 8 q, w:
+// tw[pos], tw[pos + q], tw[2 pos], tw[4 pos] in units of 1/(8 q) of a turn;
+// NEXT: neighbours (q = 1, pos = 0), all but w[1] are 1.
+__device__ __forceinline__ double2 conj2(double2 v) { return make_double2(v.x, -v.y); }
+__device__ __forceinline__ double2 mul_i(double2 v) { return make_double2(-v.y, v.x); }
+__device__ __forceinline__ double2 mul_mi(double2 v) { return make_double2(v.y, -v.x); }
+
+template <bool NEXT>
+__device__ __forceinline__ double2 turn8(const double2 (&w)[4], int k, bool inv, double2 v)
 {
-    extern __shared__ double2 z[];
-    constexpr int PER = kSmallCells / 2 / 1024;
-    const Params &P = *pp;
-    const int nx = P.nx, half = (int)(P.cells >> 1);
-    double R[PER][2], C[PER][2];
+    if (NEXT && k != 1) return v;
+    return cmul(inv ? conj2(w[k]) : w[k], v);
+}
+template <bool NEXT>
+__device__ __forceinline__ void radix8_forward(double2 (&a)[8], const double2 (&w)[4])
+{
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = threadIdx.x + k * 1024;
-        if (e < half) {
-            double v[2];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                double a0;
-                coefficients(P, (int64_t)(2 * (e >> P.lx) + r) * nx + (e & (nx - 1)), &R[k][r], &C[k][r], &a0);
-                v[r] = R[k][r] + C[k][r] * a0;
-            }
-            z[e] = make_double2(v[0], v[1]);
-        }
+    for (int j = 0; j < 4; ++j) {
+        const double2 t = turn8<NEXT>(w, j & 1, false, csub(a[j], a[j + 4]));
+        a[j] = cadd(a[j], a[j + 4]);
+        a[j + 4] = j < 2 ? t : mul_mi(t);
     }
-    __syncthreads();
-    const Lines rows{P.lx, P.ly - 1, 1, nx, 0, false}, cols{P.ly - 1, P.lx, nx, 1, 1, true};
-    const int npair = nx >> 1, per = 1024 / npair, pr = (int)threadIdx.x & (npair - 1);
+#pragma unroll
+    for (int g = 0; g < 8; g += 4)
+#pragma unroll
+        for (int j = g; j < g + 2; ++j) {
+            const double2 t = turn8<NEXT>(w, 2, false, csub(a[j], a[j + 2]));
+            a[j] = cadd(a[j], a[j + 2]);
+            a[j + 2] = j == g ? t : mul_mi(t);
+        }
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        const double2 t = turn8<NEXT>(w, 3, false, csub(a[j], a[j + 1]));
+        a[j] = cadd(a[j], a[j + 1]);
+        a[j + 1] = t;
+    }
+}
+template <bool NEXT>
+__device__ __forceinline__ void radix8_inverse(double2 (&a)[8], const double2 (&w)[4])
+{
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        const double2 t = turn8<NEXT>(w, 3, true, a[j + 1]);
+        a[j + 1] = csub(a[j], t);
+        a[j] = cadd(a[j], t);
+    }
+#pragma unroll
+    for (int g = 0; g < 8; g += 4)
+#pragma unroll
+        for (int j = g; j < g + 2; ++j) {
+            const double2 v = turn8<NEXT>(w, 2, true, a[j + 2]), t = j == g ? v : mul_i(v);
+            a[j + 2] = csub(a[j], t);
+            a[j] = cadd(a[j], t);
+        }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const double2 v = turn8<NEXT>(w, j & 1, true, a[j + 4]), t = j < 2 ? v : mul_i(v);
+        a[j + 4] = csub(a[j], t);
+        a[j] = cadd(a[j], t);
+    }
+}
+
+// The lines of a small plane in LDS: rows of nx elements (one element of
+// padding after every 8: the passes over elements 1 and 2 apart otherwise meet
+// in a quarter or half of the banks), or its columns of ny/2 elements,
+// consecutive threads on consecutive columns.  tw as in Lines.
+template <bool ROWS>
+struct SmallLines {
+    double2 *z;
+    const double2 *tw;
+    int pitch, logn, llines, tws;
+    __device__ __forceinline__ double2 &at(int b, int i) const
+    {
+        return ROWS ? z[b * pitch + i + (i >> 3)] : z[i * pitch + b + (b >> 3)];
+    }
+    // line and item of work item e, 2^(logn - lr) items per line
+    __device__ __forceinline__ void split(int e, int lr, int *b, int *k) const
+    {
+        *b = ROWS ? e >> (logn - lr) : e & ((1 << llines) - 1);
+        *k = ROWS ? e & ((1 << (logn - lr)) - 1) : e >> llines;
+    }
+    __device__ __forceinline__ int base8(int k, int lq) const
+    {
+        return ((k >> lq) << (lq + 3)) + (k & ((1 << lq) - 1));
+    }
+    __device__ __forceinline__ void twiddles(int k, int lq, double2 (&w)[4]) const
+    {
+        const int q = 1 << lq, pos = k & (q - 1), sh = logn - lq - 3 + tws;
+        w[0] = tw[pos << sh];
+        w[1] = tw[(pos + q) << sh];
+        w[2] = tw[pos << (sh + 1)];
+        w[3] = tw[pos << (sh + 2)];
+    }
+    // distance from element i to i + j 2^lq, i < 2^lq modulo 2^(lq+3): the same for all threads
+    __device__ __forceinline__ int step8(int j, int lq) const
+    {
+        return ROWS ? (j << lq) + ((j << lq) >> 3) : (j << lq) * pitch;
+    }
+    __device__ __forceinline__ void load8(int b, int i, int lq, double2 (&a)[8]) const
+    {
+        const double2 *p = &at(b, i);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a[j] = p[step8(j, lq)];
+    }
+    __device__ __forceinline__ void store8(int b, int i, int lq, const double2 (&a)[8]) const
+    {
+        double2 *p = &at(b, i);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p[step8(j, lq)] = a[j];
+    }
+    template <bool INV, bool NEXT>
+    __device__ __forceinline__ void pass8(int lq) const
+    {
+        for (int e = threadIdx.x; e < 1 << (logn - 3 + llines); e += blockDim.x) {
+            int b, k;
+            split(e, 3, &b, &k);
+            const int i = base8(k, lq);
+            double2 a[8], w[4];
+            twiddles(k, lq, w);
+            load8(b, i, lq, a);
+            if (INV) radix8_inverse<NEXT>(a, w);
+            else radix8_forward<NEXT>(a, w);
+            store8(b, i, lq, a);
+        }
+        __syncthreads();
+    }
+    // the one or two stages that are left of logn, on neighbouring elements (no twiddles but i)
+    template <bool INV>
+    __device__ __forceinline__ void rest() const
+    {
+        const int r = logn % 3;                                  // 1 or 2
+        for (int e = threadIdx.x; e < 1 << (logn - r + llines); e += blockDim.x) {
+            int b, k;
+            split(e, r, &b, &k);
+            const int i = k << r;
+            const double2 a0 = at(b, i), a1 = at(b, i + 1);
+            if (r == 1) {
+                at(b, i) = cadd(a0, a1);
+                at(b, i + 1) = csub(a0, a1);
+            } else {
+                const double2 a2 = at(b, i + 2), a3 = at(b, i + 3);
+                // forward: (a0, a2), (a1, a3), then neighbours; inverse: neighbours first
+                const double2 s0 = INV ? cadd(a0, a1) : cadd(a0, a2), s1 = INV ? csub(a0, a1) : csub(a0, a2);
+                const double2 t0 = INV ? cadd(a2, a3) : cadd(a1, a3);
+                const double2 t1 = INV ? mul_i(csub(a2, a3)) : mul_mi(csub(a1, a3));
+                at(b, i) = cadd(s0, t0);
+                at(b, i + (INV ? 2 : 1)) = csub(s0, t0);
+                at(b, i + (INV ? 1 : 2)) = cadd(s1, t1);
+                at(b, i + 3) = csub(s1, t1);
+            }
+        }
+        __syncthreads();
+    }
+    // natural to bit-reversed order from stage block 2^(lq+3) on; the inverse up to block 2^(lq+3)
+    __device__ __forceinline__ void forward(int lq) const
+    {
+        for (; lq > 0; lq -= 3) pass8<false, false>(lq);
+        if (lq == 0) pass8<false, true>(0);
+        else if (logn % 3 != 0) rest<false>();
+    }
+    __device__ __forceinline__ void inverse(int lq) const
+    {
+        int l = logn % 3;
+        if (l != 0) {
+            rest<true>();
+        } else if (lq >= 0) {
+            pass8<true, true>(0);
+            l = 3;
+        }
+        for (; l <= lq; l += 3) pass8<true, false>(l);
+    }
+};
+
+// All sweeps of a small grid (up to kSmallCells nodes) in one workgroup, where
+// the passes above would be 2 iters + 1 launches of one or two dozen
+// workgroups.  The plane, the twiddles and the symbol stay in LDS.  A sweep is
+// a chain of passes over LDS, each bound by its latency and its barrier: so
+// three radix-2 stages per pass (eight elements per thread), and the inverse
+// rows' last pass, R + C a (R, C in registers) and the forward rows' first
+// pass, which work on the same elements, in one: 9 barriers per sweep of a 64^2
+// grid instead of 14.  64^2, 10 sweeps: 95 -> 74 us.
+__global__ __launch_bounds__(kSmallThreads) void k_solve_small(const Params *__restrict__ pp)
+{
+    constexpr int kItems = kSmallCells / 2;
+    __shared__ double2 z[kItems + kItems / 8];
+    __shared__ double2 sy[kItems / 2 + kItems / 8];              // per pair of columns and row; column 1 apart
+    __shared__ double2 twx[kItems / 8], twy[kItems / 8];         // nx, ny <= kSmallCells / 8
+    const Params &P = *pp;
+    const int nx = P.nx, m = P.ny >> 1, pitch = nx + (nx >> 3), half = (int)(P.cells >> 1);
+    const int npair = nx >> 1, per = kSmallThreads / npair, pr = (int)threadIdx.x & (npair - 1);
+    const int t0 = (int)threadIdx.x / npair;
     int ca, cb;
     column_pair(pr, &ca, &cb);
-    for (int it = 0; it < P.iters; ++it) {
-        fft_forward(z, rows, P.twx);
-        fft_forward(z, cols, P.twy);
-        symbol_pair(P, z + ca, z + cb, nx, pr, ca, cb, (int)threadIdx.x / npair, per, 1.0 / (double)P.cells);
-        __syncthreads();
-        fft_inverse(z, cols, P.twy);
-        fft_inverse(z, rows, P.twx);
-        if (it + 1 == P.iters) break;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = threadIdx.x + k * 1024;
-            if (e < half) z[e] = make_double2(R[k][0] + C[k][0] * z[e].x, R[k][1] + C[k][1] * z[e].y);
-        }
-        __syncthreads();
+    for (int e = threadIdx.x; e < npair; e += kSmallThreads) twx[e] = P.twx[e];
+    for (int e = threadIdx.x; e < m; e += kSmallThreads) twy[e] = P.twy[e];
+    {
+        const double la = P.lapx[brev(ca, P.lx)], inv = 1.0 / (double)P.cells;
+        for (int q = t0; q < m; q += per) sy[q * npair + pr] = symbol(P, brev(q, P.ly - 1), la, inv);
+        const double lb = P.lapx[brev(1, P.lx)];
+        for (int q = threadIdx.x; q < m; q += kSmallThreads) sy[m * npair + q] = symbol(P, brev(q, P.ly - 1), lb, inv);
     }
-    double *out = P.it[(P.iters - 1) & 1];
-    for (int e = threadIdx.x; e < half; e += 1024) {
-        const int64_t o = (int64_t)(2 * (e >> P.lx)) * nx + (e & (nx - 1));
-        out[o] = z[e].x;
-        out[o + nx] = z[e].y;
+    const SmallLines<true> rows{z, twx, pitch, P.lx, P.ly - 1, 0};
+    const SmallLines<false> cols{z, twy, pitch, P.ly - 1, P.lx, 1};
+    // this thread's eight nodes of two rows: the last pass of the inverse rows
+    const int lq = P.lx - 3, q = 1 << lq;
+    const bool mine = (int)threadIdx.x < half >> 3;
+    int row, k0;
+    rows.split(threadIdx.x, 3, &row, &k0);
+    const int64_t o = (int64_t)2 * row * nx + k0;
+    double R[8][2], C[8][2];
+    double2 a[8], w[4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            double a0 = 0.0;
+            R[j][r] = C[j][r] = 0.0;
+            if (mine) coefficients(P, o + r * nx + j * q, &R[j][r], &C[j][r], &a0);
+            (r ? a[j].y : a[j].x) = a0;
+        }
+    __syncthreads();
+    if (mine) rows.twiddles(k0, lq, w);
+    for (int it = 0;; ++it) {
+        if (mine) {
+            if (it > 0) {
+                rows.load8(row, k0, lq, a);
+                radix8_inverse<false>(a, w);
+            }
+            if (it < P.iters) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    a[j] = make_double2(R[j][0] + C[j][0] * a[j].x, R[j][1] + C[j][1] * a[j].y);
+                radix8_forward<false>(a, w);
+                rows.store8(row, k0, lq, a);
+            }
+        }
+        if (it == P.iters) break;
+        __syncthreads();
+        rows.forward(lq - 3);
+        cols.forward(P.ly - 4);
+        symbol_pair(P, z + ca + (ca >> 3), z + cb + (cb >> 3), pitch, pr, t0, per, twy,
+                    [&](int p, bool second, int) { return sy[second ? m * npair + p : p * npair + pr]; });
+        __syncthreads();
+        cols.inverse(P.ly - 4);
+        rows.inverse(lq - 3);
+    }
+    if (!mine) return;
+    double *out = P.it[(P.iters - 1) & 1] + o;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        out[j * q] = a[j].x;
+        out[j * q + nx] = a[j].y;
     }
 }
 
@@ -1248,7 +1461,7 @@ struct Launcher {
 void solve(Launcher &L, const Params &hp, const Params *dp)
 {
     if (hp.cells <= kSmallCells) {
-        L(0, k_solve_small, dim3(1), dim3(1024), sizeof(double2) * (size_t)(hp.cells / 2), dp);
+        L(0, k_solve_small, dim3(1), dim3(kSmallThreads), 0, dp);
         return;
     }
     const size_t row_lds = sizeof(double2) * (size_t)hp.nx;

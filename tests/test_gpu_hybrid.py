@@ -111,6 +111,20 @@ def test_hybrid_solve_edges(pic, n, iters):
     g.close()
 
 
+@pytest.mark.parametrize("n,iters", [((32, 16), 2), ((128, 64), 2), ((256, 32), 3), ((512, 16), 1), ((16, 512), 2)])
+def test_hybrid_solve_in_one_workgroup(pic, n, iters):
+    """Numbers of stages that leave one, two and none after passes of three, on
+    either axis of the one-workgroup solve; tolerances as above."""
+    log(f"case hybrid solve in one workgroup {n} iters {iters}")
+    wl = replace(synth.H1, n=n, ppc=3 if n[0] * n[1] > 1024 else 40, iters=iters, steps=4, name=f"H1-{n[0]}x{n[1]}")
+    orc, g = _pair(pic, wl, sort_every=2)
+    _compare(orc, g, wl, 1e-11)
+    orc.step(wl.steps)
+    g.step(wl.steps)
+    _compare(orc, g, wl, 1e-9)
+    g.close()
+
+
 def _same_state(r0, r1):
     """Bitwise equality of two runs' potential, canonical momentum and
     particles (by id: the cell sort's order within a cell is free)."""
