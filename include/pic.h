@@ -389,8 +389,9 @@ int pic_destroy(pic_run *run);
  * Everything the step reads before writing it is cleared here, so the
  * contents a previous run left behind do not matter.
  * Errors: those of pic_init; INVALID_ARG (buffers->scratch not NULL);
- * BUFFER_TOO_SMALL (pic_query's scratch_bytes exceeds
- * PIC_STATIC_SCRATCH_BYTES: a grid of up to ~1M cells with 16^2 tiles fits);
+ * BUFFER_TOO_SMALL (pic_query's scratch_bytes, less what a run only steps
+ * faster with, exceeds PIC_STATIC_SCRATCH_BYTES: a grid of up to ~1M cells
+ * with 16^2 tiles fits);
  * STATE (the device's scratch is held by another run); UNSUPPORTED (device
  * index >= 64). */
 #define PIC_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
