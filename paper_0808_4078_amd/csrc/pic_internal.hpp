@@ -183,7 +183,7 @@ constexpr int kBatchGroups = 3;
 struct BatchTable {
     int nruns;
     int n_cell_blocks;    // 256-cell blocks over all runs
-    int fused;            // 1 if every run has the planes of the fused field passes (KParams::Ft)
+    int fused;            // 1: fused field passes (every run has KParams::Ft, up to kFusedCells in all)
     int max_fd_blocks;    // max over runs of KParams::fd_blocks
     int coulomb;          // 1 if any run has a species on the Coulomb scattering model
     const KParams *const *kp;   // [nruns] device parameter blocks
@@ -196,6 +196,12 @@ struct BatchTable {
 // 160x160, mixed: 864 -> 833 us).  Eight would save half as much again of that
 // for twice the nodes; four cost 60 us more when the run is made.
 constexpr int kChainSteps = 4;
+// Cells up to which a 2D run, or an ensemble in all, takes the fused field
+// passes: their second set of planes doubles what the passes hold in the
+// last-level cache.  ms per step, one by one / fused, ensembles of 1.1M cells
+// 1.103 / 1.100, 2.2M 2.384 / 2.382, 4.6M 4.72 / 4.79, 21M 20.40 / 20.87; runs of
+// 1M cells 0.515 / 0.493, 2.1M 1.160 / 1.150, 4.2M 1.795 / 1.807, 17M 2.69 / 2.78.
+constexpr int64_t kFusedCells = 1ll << 21;
 // workgroups per run of an ensemble for the two phases of its re-layout
 constexpr int kBatchCountBlocks = 32;
 constexpr int kBatchRebinBlocks = 256;

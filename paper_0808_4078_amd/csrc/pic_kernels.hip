@@ -22,9 +22,9 @@
 //                    after the move and max |rho^{n+1} - rho^n + dt div J|
 //   k_advance        diagnostic record, counter reset, step/parity update (with
 //                    few tiles one workgroup of k_end)
-// Ensembles go through the same passes (kb_*).  3D runs with many tiles, and
-// runs without room for the second set of field planes, take the field passes
-// one by one (reduce_j, yee_b, yee_e, yee_b).
+// Ensembles go through the same passes (kb_*).  3D runs with many tiles, grids
+// above kFusedCells, and runs without room for the second set of field planes,
+// take the field passes one by one (reduce_j, yee_b, yee_e, yee_b).
 //
 // The numerical scheme is the relativistic Boris push (Boris 1970), the
 // Esirkepov (2001) charge-conserving deposit with the linear form factor and
@@ -3276,8 +3276,8 @@ int step_kernel_groups(const KParams &hp, int *groups)
 
 // The same kernel sequence over a whole ensemble: field record | particle, one
 // launch per tile edge in use | first field pass and re-layout counts | second
-// field pass and re-layout copies | end of step.  3D members keep the field
-// passes apart (reduction, B, E, B).
+// field pass and re-layout copies | end of step.  3D members, and ensembles
+// above kFusedCells, keep the field passes apart (reduction, B, E, B).
 template <typename R, typename A, int D, int T>
 static void batch_particle(Launcher &L, const BatchTable &ht, const BatchTable *dt, const int *pb)
 {

@@ -279,7 +279,7 @@ int validate(const pic_grid_desc *g, const pic_species_desc *sp, int ns, Layout 
         L->rl_ovf = c.take((size_t)ns * G.ntiles * 4);
         L->rl_ticket = c.take(2 * 4);
         // fused field passes: 2D, and 3D grids with few tiles (see field_mid)
-        if (!lean && (g->ndim == 2 || L->split > 1)) L->Ft = c.take((size_t)G.cells * 6 * L->real);
+        if (!lean && ((g->ndim == 2 && G.cells <= kFusedCells) || L->split > 1)) L->Ft = c.take((size_t)G.cells * 6 * L->real);
         if (L->split > 1) {
             L->Jsplit = c.take((size_t)G.ntiles * L->split * 3 * nj_cells * 8);
             L->split_cnt = c.take((size_t)G.ntiles * ns * 2 * kSplitLine * 4);
@@ -1551,7 +1551,7 @@ int pic_batch_init(int nruns, pic_run *const *runs, void *table, size_t table_by
     memset(&H, 0, sizeof(H));
     H.nruns = nruns;
     H.n_cell_blocks = B.n_cell_blocks;
-    H.fused = fused ? 1 : 0;
+    H.fused = fused && (int64_t)cells.size() * 256 <= kFusedCells ? 1 : 0;
     H.max_fd_blocks = max_fd;
     H.coulomb = 0;
     for (int i = 0; i < nruns; ++i) H.coulomb |= runs[i]->hp.coulomb;

@@ -112,3 +112,27 @@ def test_counts_of_steps_in_one_call(pic, n, tile):
         assert a.diagnostics()["step"] == b.diagnostics()["step"]
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("n,batch", [((1024, 2048), False), ((1032, 2048), False), ((1024, 2048), True),
+                                     ((1032, 2048), True)])
+def test_field_passes_of_large_grids(pic, n, batch):
+    """Both sides of the grid size (2^21 cells) up to which the field passes are
+    fused, alone and as an ensemble: 3 steps against the oracle, FP64 to 1e-9."""
+    log(f"case field passes {n} batch {batch}")
+    wl = synth.beam_plasma(n, ppc=1, u_th_beam=0.4, u_th_plasma=0.1, nu=0.1)
+    parts = synth.load(wl)
+    orc = oracle_run(wl, parts)
+    orc.step(3)
+    g = gpu_run(wl, parts, pic.PIC_PREC_FP64, tile=8)
+    if batch:
+        b = pic.Batch([g])
+        b.step(3)
+        b.close()
+    else:
+        g.step(3)
+    E, B, _ = g.read_fields()
+    err = rel_err(stack(E, B), stack(orc.f.E, orc.f.B))
+    log(f"  fields {err:.2e}")
+    assert err < 1e-9
+    g.close()
