@@ -2842,12 +2842,13 @@ __global__ __launch_bounds__(256) void k_end(const KParams *__restrict__ kp, int
     }
 }
 
-// The same two passes over an ensemble (32 uneven runs: 15 launches per step
-// became 7, five steps 13.44 -> 13.34 ms; 7 runs: two steps 2.04 -> 1.98 ms;
-// the particle kernels of the tile edges side by side on streams of their own
-// measured 3% slower): workgroups [0, nf) through the (run,
-// 256-cell block) map (FIELDS; else nf = 0 and the field passes are launched
-// one by one), then nr workgroups per run for its re-layout.
+// The same two passes over an ensemble (15 launches per step became 7, or 9
+// with the field passes apart; 7 runs, two steps: 2.04 -> 1.98 ms; 32 uneven
+// runs, 2.2M cells, five steps: 13.33 -> 13.22 ms; the particle kernels of the
+// tile edges side by side on streams of their own measured 3% slower):
+// workgroups [0, nf) through the (run, 256-cell block) map (FIELDS; else nf = 0
+// and the field passes are launched one by one), then nr workgroups per run for
+// its re-layout.
 template <typename R, int D, bool FIELDS>
 __global__ __launch_bounds__(256) void kb_mid(const BatchTable *__restrict__ bt, int nf, int nr)
 {
