@@ -1720,6 +1720,11 @@ static int tune_carve(const pic_grid_desc *grid, const pic_species_desc *sp, int
     for (int a = 0; a < 3; ++a) g.tile[a] = a < g.ndim ? tile : 0;
     int rc = pic_query(&g, sp, ns, &T->sz);
     if (rc) return rc;
+    // the candidates run in every launch shape: shape 0 has the largest scratch
+    // (particle_split)
+    g.shape = 0;
+    rc = pic_query(&g, sp, ns, &T->sz);
+    if (rc) return rc;
     Carver c;
     for (int s = 0; s < ns; ++s) T->part[s] = c.take(T->sz.particle_bytes[s]);
     T->fields = c.take(T->sz.field_bytes);

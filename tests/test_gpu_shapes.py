@@ -122,6 +122,18 @@ def test_tune_shape(pic):
     assert best == 0 and set(ms) == {0}
 
 
+@pytest.mark.parametrize("copies", [1, 3])
+def test_tune_shape_of_a_run_in_another_shape(pic, copies):
+    """The descriptor's own shape does not matter: every shape is timed in the
+    same workspace, also where shape 0 takes several workgroups per tile."""
+    log(f"case tune shape of a run in shape 2, copies {copies}")
+    wl = synth.beam_plasma((64, 64), ppc=64, name="tune-shape-2")
+    g, sp = pic.workload_descs(wl, precision=pic.PIC_PREC_MIXED, tile=16, shape=2)
+    best, ms = pic.tune_shape(g, sp, nsteps=3, copies=copies)
+    assert set(ms) == set(pic.SHAPES) and all(v > 0 for v in ms.values())
+    assert ms[best] == min(ms.values())
+
+
 def test_batch_groups_take_their_shapes(pic):
     """Members of tile edge 8 in shape 2 and of edge 16 in shape 3 in one
     batch, each against its twin stepped alone; members of one edge with

@@ -1,0 +1,55 @@
+"""Host code of libpic over a stand-in for the HIP runtime (stub_hip.c), in a
+process of its own: what it asks of the device, without one."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = tmp_path_factory.mktemp("stub") / "stub_hip.so"
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", os.path.join(HERE, "stub_hip.c"), "-o", str(so)], check=True)
+    return str(so)
+
+
+def run(stub, body, *args):
+    """Runs `body` (with pic, synth, C, L = the library, S = the stub, BASE = a
+    device address) under the stub; returns what it prints."""
+    code = ("import ctypes as C, sys\nimport synth\nfrom paper_0808_4078_amd import pic\n"
+            f"L = pic.lib()\nS = C.CDLL({stub!r})\nBASE = 1 << 45\n" + body)
+    p = subprocess.run([sys.executable, "-c", code, *map(str, args)], cwd=ROOT, capture_output=True, text=True,
+                       env={**os.environ, "LD_PRELOAD": stub}, timeout=300)
+    assert p.returncode == 0, p.stderr
+    return p.stdout.split()
+
+
+# runs that take several workgroups per tile in shape 0 only, 2D and 3D
+@pytest.mark.parametrize("n,ppc,copies", [((64, 64), 64, 1), ((64, 64), 64, 3), ((16, 16, 16), 32, 1)])
+@pytest.mark.parametrize("shape", [0, 1, 4])
+def test_shape_tuner_stays_in_its_workspace(stub, n, ppc, copies, shape):
+    """The tuner tries every launch shape in a workspace that does not depend
+    on the descriptor's: the size is the same, and nothing is filled or copied
+    outside it."""
+    size, outside, rc = map(int, run(stub, f"""
+def descs(shape):
+    return pic.workload_descs(synth.beam_plasma({n}, ppc={ppc}), precision=pic.PIC_PREC_MIXED, shape=shape)
+need = C.c_size_t()
+g, sp = descs(0)
+L.pic_tune_query(C.byref(g), sp, len(sp), {copies}, C.byref(need))
+size = need.value
+g, sp = descs({shape})
+L.pic_tune_query(C.byref(g), sp, len(sp), {copies}, C.byref(need))
+C.c_uint64.in_dll(S, "stub_lo").value = BASE
+C.c_uint64.in_dll(S, "stub_hi").value = BASE + need.value
+best, ms = C.c_int32(), (C.c_double * len(pic.SHAPES))()
+rc = L.pic_tune_shape(C.byref(g), sp, len(sp), {copies}, C.c_void_p(BASE), need, None, 2, C.byref(best), ms)
+print(need.value - size, C.c_uint64.in_dll(S, "stub_outside").value, rc)
+"""))
+    assert rc == 0
+    assert outside == 0
+    assert size == 0
