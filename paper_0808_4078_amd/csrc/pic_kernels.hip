@@ -42,6 +42,7 @@
 #include <hip/hip_runtime.h>
 
 #include "pic_internal.hpp"
+#include "pic_relayout.hpp"
 
 namespace pic {
 
@@ -2143,9 +2144,8 @@ __device__ __forceinline__ void rebin_finalize_bin(const KParams *__restrict__ k
 // for no launch of it.  A phase ends in its last workgroup to arrive:
 //   relayout_count    counts of the bins and of the overflow list, then the
 //                     scan of the new bins;
-//   relayout_scatter  copies, then the new bins take effect.
-// `nb` workgroups, bid among them.  Returns true in the workgroup that ended
-// the second phase.
+//   relayout_end      copies, then the new bins take effect.
+// `nb` workgroups, bid among them.
 //
 // DATA: the last workgroup reads what the others stored (a fence on both sides;
 // on this device a release writes back the L2).  Without it the arrival only
@@ -2195,18 +2195,28 @@ __device__ __forceinline__ void relayout_count(const KParams *__restrict__ kp, i
     }
 }
 
-template <typename R>
-__device__ __forceinline__ bool relayout_scatter(const KParams *__restrict__ kp, int bid, int nb)
-{
-    if (!kp->state->rebin) return false;
-    rebin_scatter_body<R>(kp, bid, nb);
-    rebin_scatter_ovf_body<R>(kp, bid, nb);
-    if (!last_to_arrive<false>(kp, 1, nb)) return false;
-    const int64_t nbins = (int64_t)kp->nspecies * kp->g.ntiles;
-    for (int64_t i = threadIdx.x; i < nbins; i += blockDim.x) rebin_finalize_bin(kp, i);
-    __syncthreads();
-    return true;
-}
+// One workgroup of the second phase; ADV (see relayout_end): parts and nfd as
+// in advance_body.
+template <typename R, bool ADV>
+struct RelayoutCopy {
+    const KParams *__restrict__ kp;
+    int parts, nfd;
+
+    __device__ __forceinline__ bool rebin() const { return kp->state->rebin != 0; }
+    __device__ __forceinline__ void copy(int bid, int nb) const
+    {
+        rebin_scatter_body<R>(kp, bid, nb);
+        rebin_scatter_ovf_body<R>(kp, bid, nb);
+    }
+    __device__ __forceinline__ bool arrive(int nb) const { return last_to_arrive<false>(kp, 1, nb); }
+    __device__ __forceinline__ void finish() const
+    {
+        const int64_t nbins = (int64_t)kp->nspecies * kp->g.ntiles;
+        for (int64_t i = threadIdx.x; i < nbins; i += blockDim.x) rebin_finalize_bin(kp, i);
+        __syncthreads();
+    }
+    __device__ __forceinline__ void advance() const;
+};
 
 // ---------------------------------------------------------------------------
 // Grid current: fixed-order FP64 sum of the tile partials covering each node.
@@ -2746,6 +2756,12 @@ __device__ __forceinline__ void advance_body(const KParams *__restrict__ kp, int
     }
 }
 
+template <typename R, bool ADV>
+__device__ __forceinline__ void RelayoutCopy<R, ADV>::advance() const
+{
+    if constexpr (ADV) advance_body(kp, parts, nfd);
+}
+
 // ---------------------------------------------------------------------------
 // Kernel entry points.  k_*: one run, the grid covers that run's blocks.
 // kb_*: an ensemble; blockIdx.y picks the run, or a table maps each block to
@@ -2819,9 +2835,10 @@ __global__ __launch_bounds__(shape_threads(sizeof(R) == 8, D, SH)) void kb_parti
 // The two field passes of a single run, with the two phases of its re-layout:
 // workgroups [0, nf) take 256 nodes each, the nr after them the re-layout
 // phase (nf or nr may be 0).  k_mid, DIAG: also the field record's partials.
-// k_end, ADV: also the end of the step -- by its first workgroup, whose work
-// touches nothing that the others read, or, in a step with a re-layout, by the
-// workgroup that ended it.
+// k_end, ADV: also the end of the step, and one more workgroup for the
+// re-layout phase, the first of the launch -- in a step without a re-layout it
+// ends the step, which touches nothing that the others read; with one, the
+// workgroup that ended the phase does (relayout_end).
 template <typename R, int D, bool SPLIT, bool DIAG>
 __global__ __launch_bounds__(256) void k_mid(const KParams *__restrict__ kp, int nf, int nr)
 {
@@ -2833,12 +2850,11 @@ template <typename R, int D, bool ADV>
 __global__ __launch_bounds__(256) void k_end(const KParams *__restrict__ kp, int nf, int nr, int nfd)
 {
     const int b = ADV ? (int)blockIdx.x - 1 : (int)blockIdx.x;
-    if (ADV && b < 0) {
-        if (!kp->state->rebin) advance_body(kp, kp->split, nfd);
-    } else if (b < nf) {
+    if (b >= 0 && b < nf) {
         field_end<R, D>(kp, b);
-    } else if (relayout_scatter<R>(kp, b - nf, nr)) {
-        if constexpr (ADV) advance_body(kp, kp->split, nfd);
+    } else {
+        RelayoutCopy<R, ADV> wg{kp, kp->split, nfd};
+        relayout_end<ADV>(wg, b < 0 ? 0 : b - nf + (ADV ? 1 : 0), nr + (ADV ? 1 : 0));
     }
 }
 
@@ -2868,7 +2884,8 @@ __global__ __launch_bounds__(256) void kb_end(const BatchTable *__restrict__ bt,
         const int2 cb = bt->cell_blocks[b];
         field_end<R, D>(bt->kp[cb.x], cb.y);
     } else {
-        (void)relayout_scatter<R>(bt->kp[(b - nf) / nr], (b - nf) % nr, nr);
+        RelayoutCopy<R, false> wg{bt->kp[(b - nf) / nr], 1, 0};
+        relayout_end<false>(wg, (b - nf) % nr, nr);
     }
 }
 

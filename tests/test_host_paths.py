@@ -53,3 +53,14 @@ print(need.value - size, C.c_uint64.in_dll(S, "stub_outside").value, rc)
     assert rc == 0
     assert outside == 0
     assert size == 0
+
+
+def test_one_end_of_step_in_any_order_of_workgroups(tmp_path):
+    """The last field pass of a step carries the re-layout's copies and the
+    step's end: whatever the order its workgroups run in, every part is copied
+    once, the new bins take effect after the last copy, and the step ends once."""
+    exe = tmp_path / "order"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__device__=", "-D__forceinline__=inline", "-I",
+                    os.path.join(ROOT, "paper_0808_4078_amd", "csrc"), os.path.join(HERE, "relayout_order.cpp"),
+                    "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)], capture_output=True, text=True, check=True, timeout=100).stdout.split() == ["0"]
