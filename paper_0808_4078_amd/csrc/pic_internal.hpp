@@ -242,9 +242,11 @@ int init_run(const pic_grid_desc *grid, const pic_species_desc *species, int nsp
              const pic_buffers *buffers, void *hip_stream, pic_run **out, int static_device);
 // The library's scratch: what a caller may count on, and room for what lies
 // behind the part of the scratch that a checkpoint holds (parameter block,
-// binary-collision counts: far below 1 MiB for any run whose other scratch
-// fits PIC_STATIC_SCRATCH_BYTES).
-constexpr size_t kStaticScratch = PIC_STATIC_SCRATCH_BYTES + ((size_t)1 << 20);
+// read-out places, re-layout and binary-collision counts).  That is at most
+// 8 + 4 nspecies bytes per tile, 48 with 8 species and collisions, where the
+// part itself is at least 1452 (8^2 tiles, FP32 currents) + 64 nspecies: at the
+// most 1.4 MiB for a run whose part fits PIC_STATIC_SCRATCH_BYTES.
+constexpr size_t kStaticScratch = PIC_STATIC_SCRATCH_BYTES + ((size_t)2 << 20);
 // One run at a time per device may hold the library's scratch of that device.
 constexpr int kMaxDevices = 64;
 bool claim_static_scratch(int device);     // false if held

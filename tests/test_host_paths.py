@@ -6,6 +6,8 @@ import sys
 
 import pytest
 
+from paper_0808_4078_amd.pic import PIC_E_BUFFER_TOO_SMALL
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
@@ -64,3 +66,28 @@ def test_one_end_of_step_in_any_order_of_workgroups(tmp_path):
                     os.path.join(ROOT, "paper_0808_4078_amd", "csrc"), os.path.join(HERE, "relayout_order.cpp"),
                     "-o", str(exe)], check=True)
     assert subprocess.run([str(exe)], capture_output=True, text=True, check=True, timeout=100).stdout.split() == ["0"]
+
+
+# the largest grids of 128 tiles along x whose checkpointed part fits
+@pytest.mark.parametrize("ny,ns,binary", [(2736, 1, 0), (2432, 4, 0), (2112, 8, 0), (1872, 4, 1), (1680, 8, 1)])
+def test_library_scratch_takes_runs_up_to_its_size(stub, ny, ns, binary):
+    """A run is accepted on the library's scratch as long as the part of it
+    that a checkpoint holds fits in PIC_STATIC_SCRATCH_BYTES, with as many
+    species and tiles as there may be; the next larger grid is refused."""
+    codes = run(stub, f"""
+def init(ny):
+    sp = [dict(density=1.0 / {ns}, ppc=1, binary=k < {binary}) for k in range({ns})]
+    g, s = pic.make_descs(2, (1024, ny), (0.2, 0.2), 0.1, sp, tile=8, nu_ee=0.1, ee_vref=0.1,
+                          flags=pic.PIC_FLAG_HOST_LOAD)
+    b = pic.Buffers()
+    for k in range({ns}):
+        b.particles[k] = BASE
+    b.fields = b.diag = BASE
+    h = C.c_void_p()
+    rc = L.pic_init_static_scratch(C.byref(g), s, {ns}, C.byref(b), None, C.byref(h))
+    if rc == 0:
+        L.pic_destroy(h)
+    return rc
+print(init({ny}), init({ny} + 8))
+""")
+    assert codes == ["0", str(PIC_E_BUFFER_TOO_SMALL)]
