@@ -475,6 +475,14 @@ int loader_moments(pic_run *r)
     return PIC_OK;
 }
 
+void drop_graphs(pic_run *r)
+{
+    for (int k = 0; k < 2; ++k) {
+        if (r->gexec[k]) (void)hipGraphExecDestroy(r->gexec[k]);
+        if (r->graph[k]) (void)hipGraphDestroy(r->graph[k]);
+    }
+}
+
 // Captures one step (which = 0) or kChainSteps of them (which = 1) as a graph
 // on a private stream.  A failure is returned as PIC_E_HIP (the caller can ask
 // for kernel-by-kernel steps with PIC_FLAG_NO_GRAPH instead).
@@ -1012,6 +1020,7 @@ int pic::init_run(const pic_grid_desc *grid, const pic_species_desc *species, in
         if (rc == PIC_OK) rc = capture_graph(r, 1);
         if (rc) {
             g_last_error = r->err;
+            drop_graphs(r);
             delete r;
             return rc;
         }
@@ -1331,10 +1340,7 @@ int pic_destroy(pic_run *r)
     if (r->owner) return fail(&r->err, PIC_E_STATE, "run is a member of a batch; destroy the batch first");
     // the caller frees the buffers once this returns: let every enqueued step finish first
     const hipError_t e = hipStreamSynchronize(r->stream);
-    for (int k = 0; k < 2; ++k) {
-        if (r->gexec[k]) (void)hipGraphExecDestroy(r->gexec[k]);
-        if (r->graph[k]) (void)hipGraphDestroy(r->graph[k]);
-    }
+    drop_graphs(r);
     if (r->static_device >= 0) release_static_scratch(r->static_device);
     delete r;
     if (e != hipSuccess) {

@@ -6,7 +6,7 @@ import sys
 
 import pytest
 
-from paper_0808_4078_amd.pic import PIC_E_BUFFER_TOO_SMALL
+from paper_0808_4078_amd.pic import PIC_E_BUFFER_TOO_SMALL, PIC_E_HIP
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -91,3 +91,22 @@ def init(ny):
 print(init({ny}), init({ny} + 8))
 """)
     assert codes == ["0", str(PIC_E_BUFFER_TOO_SMALL)]
+
+
+@pytest.mark.parametrize("fail", [1, 2])
+def test_failed_capture_leaves_no_graph(stub, fail):
+    """A run whose first or second graph cannot be instantiated is refused, and
+    the graphs made until then are freed."""
+    rc, graphs, execs = map(int, run(stub, f"""
+g, sp = pic.workload_descs(synth.C1, flags=pic.PIC_FLAG_HOST_LOAD)
+b = pic.Buffers()
+for k in range(len(sp)):
+    b.particles[k] = BASE
+b.fields = b.scratch = b.diag = BASE
+C.c_int.in_dll(S, "stub_fail_instantiate").value = {fail}
+h = C.c_void_p()
+rc = L.pic_init(C.byref(g), sp, len(sp), C.byref(b), None, C.byref(h))
+print(rc, C.c_int.in_dll(S, "stub_graphs").value, C.c_int.in_dll(S, "stub_execs").value)
+"""))
+    assert rc == PIC_E_HIP
+    assert graphs == 0 and execs == 0
