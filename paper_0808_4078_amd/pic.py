@@ -410,14 +410,17 @@ class Run:
 
     def read_particles(self, s: int):
         cnt = C.c_int64()
-        cap = max(int(self.species[s].ppc) * self.cells, 1)      # a species never holds more
+        # a species never holds more than its nominal count, and mostly that
+        cap = max(int(self.species[s].ppc) * self.cells, 1) if 0 <= s < self.ns else 1
         x = np.empty((self.ndim, cap))
         u = np.empty((3, cap))
         ids = np.empty(cap, dtype=np.uint32)
         _check(lib().pic_read_particles(self.h, s, _ptr(x), _ptr(u), _ptr(ids), cap, C.byref(cnt)),
                "pic_read_particles", self.h)
         n = cnt.value
-        return x[:, :n], u[:, :n], ids[:n]
+        if n == cap:
+            return x, u, ids
+        return x[:, :n].copy(), u[:, :n].copy(), ids[:n].copy()
 
 
 class Batch:

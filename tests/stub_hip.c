@@ -1,13 +1,15 @@
 /* Stand-in for the HIP runtime calls of libpic's host code, preloaded by tests
  * that run without a GPU: nothing is executed, "device" memory is addresses
  * only.  It records the device range that copies and fills reach, and the
- * graphs that are alive, and can fail the n-th instantiation. */
+ * graphs that are alive, and can fail the n-th instantiation.  A copy to the host
+ * gives zeros, or a word that the test sets. */
 #include <stddef.h>
 #include <stdint.h>
 #include <string.h>
 
 uint64_t stub_lo, stub_hi;          /* device addresses that may be written */
 uint64_t stub_outside;              /* fills and copies that left them */
+int64_t stub_word;                  /* what an 8-byte copy to the host gives */
 int stub_graphs, stub_execs;        /* alive */
 int stub_fail_instantiate;          /* 1-based count of the call that fails, 0: none */
 static int instantiated;
@@ -21,7 +23,10 @@ static int copy(void *d, const void *s, size_t n, int kind)
 {
     (void)s;
     if (kind == 1) touch(d, n);             /* host to device */
-    else if (kind == 2) memset(d, 0, n);    /* device to host */
+    else if (kind == 2) {                   /* device to host: zeros, or the word set */
+        memset(d, 0, n);
+        if (n == sizeof(stub_word)) memcpy(d, &stub_word, n);
+    }
     return 0;
 }
 

@@ -6,7 +6,7 @@ import sys
 
 import pytest
 
-from paper_0808_4078_amd.pic import PIC_E_BUFFER_TOO_SMALL, PIC_E_HIP
+from paper_0808_4078_amd.pic import PIC_E_BUFFER_TOO_SMALL, PIC_E_HIP, PIC_E_INVALID_ARG
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -110,3 +110,29 @@ print(rc, C.c_int.in_dll(S, "stub_graphs").value, C.c_int.in_dll(S, "stub_execs"
 """))
     assert rc == PIC_E_HIP
     assert graphs == 0 and execs == 0
+
+
+@pytest.mark.parametrize("n", [0, 1, 5, 64])
+def test_read_particles_gives_whole_arrays(stub, n):
+    """Run.read_particles with fewer particles in the store than its nominal 64,
+    or all: contiguous arrays of exactly those; a species out of range is an
+    error of the library, whatever its sign."""
+    out = run(stub, f"""
+g, sp = pic.make_descs(2, (8, 8), (0.2, 0.2), 0.1, [dict(density=1.0, ppc=1)],
+                       flags=pic.PIC_FLAG_HOST_LOAD | pic.PIC_FLAG_NO_GRAPH)
+b = pic.Buffers()
+b.particles[0] = b.fields = b.scratch = b.diag = BASE
+r = pic.Run.__new__(pic.Run)
+r.h, r.grid, r.species, r.ns, r.ndim, r.n, r.cells = C.c_void_p(), g, sp, 1, 2, (8, 8), 64
+assert L.pic_init(C.byref(g), sp, 1, C.byref(b), None, C.byref(r.h)) == 0
+C.c_int64.in_dll(S, "stub_word").value = {n}
+x, u, ids = r.read_particles(0)
+print(*x.shape, *u.shape, *ids.shape)
+print(*[int(a.flags.c_contiguous and (a.base is None or a.base.nbytes <= max(a.nbytes, 8 * len(a)))) for a in (x, u, ids)])
+for s in (1, -1):
+    try:
+        r.read_particles(s)
+    except pic.PicError as e:
+        print(e.code)
+""")
+    assert list(map(int, out)) == [2, n, 3, n, n, 1, 1, 1, PIC_E_INVALID_ARG, PIC_E_INVALID_ARG]
