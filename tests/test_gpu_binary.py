@@ -7,6 +7,7 @@ acceptance for the unequal beam and plasma weights.  The pairing and the
 per-step pair counts are integer work and must be identical; momenta and
 fields within the FP64 and mixed bars."""
 import os
+from dataclasses import replace
 
 import numpy as np
 import pytest
@@ -145,6 +146,23 @@ def test_binary_crowded_cells(pic, tile, prec, bar):
     log(f"  worst |du|/max|u| {worst:.2e}")
     g.close()
     assert worst < bar
+
+
+@pytest.mark.parametrize("masses,prec,u_bar,f_bar", [
+    ((1.0, 4.0), "fp64", 1e-11, 1e-9), ((25.0, 0.5), "fp64", 1e-11, 1e-9), ((1.0, 4.0), "mixed", 1e-3, 1e-3),
+    pytest.param((25.0, 0.5), "mixed", 1e-3, 1e-3, marks=pytest.mark.xfail(strict=False, reason=(
+        "FP32 collisions of partners 50 times apart in mass: the light one's momentum is off by 9e-4 of the largest "
+        "after one step, and a particle changes its cell against the oracle at step 10 (also in the kernel that "
+        "served all masses, bit for bit)")))])
+def test_binary_masses(pic, masses, prec, u_bar, f_bar):
+    """Participants of other masses than 1 (one of them, and both): a kernel of
+    their own, against the oracle over 12 steps as in the cases above."""
+    log(f"case binary masses {masses} {prec}")
+    wl = synth.beam_plasma((32, 32), ppc=9, u_th_beam=0.2, u_th_plasma=0.05, nu=0.05, nu_ee=0.5, ee_vref=0.2, steps=12)
+    wl = replace(wl, species=tuple(replace(s, m=m) for s, m in zip(wl.species, masses)))
+    pg, po, wu, fe = _compare(pic, wl, prec, wl.steps, u_bar, f_bar)
+    assert pg == po if prec == "fp64" else all(abs(a - b) <= 3 for a, b in zip(pg, po))
+    assert wu < u_bar and fe < f_bar
 
 
 def test_binary_refused_in_a_batch(pic):
