@@ -90,3 +90,30 @@ def test_static_scratch_refuses_what_does_not_fit(pic):
     with pytest.raises(pic.PicError) as e:
         pic.Run(g, sp, static_scratch=True)
     assert e.value.code == pic.PIC_E_BUFFER_TOO_SMALL
+
+
+def test_static_scratch_without_room_for_all(pic):
+    """Runs that fit the library's scratch only without the parts that speed
+    their steps up (the second set of field planes; several workgroups per
+    tile), against the same runs on the caller's scratch, which have them: 1024^2
+    in FP64, and binary collisions of 1900 per cell, whose lists fill the
+    scratch, on few tiles (mixed; 6 steps, currents may round once apart:
+    fields to 1e-6)."""
+    log("case static scratch, reduced layout")
+    for wl, prec, bar in (
+            (synth.beam_plasma((1024, 1024), ppc=2, u_th_beam=0.3, nu=0.05, name="lean-1"), pic.PIC_PREC_FP64, 1e-12),
+            (synth.beam_plasma((64, 64), ppc=1900, u_th_beam=0.3, nu_ee=0.1, ee_vref=0.1, binary=(False, True),
+                               name="lean-2"), pic.PIC_PREC_MIXED, 1e-6)):
+        g, sp = pic.workload_descs(wl, precision=prec)
+        full = pic.query(g, sp).scratch_bytes
+        ref, st = _twin_runs(pic, wl, prec, 0)
+        assert st.info()["scratch_bytes"] < full == ref.info()["scratch_bytes"]
+        for r in (ref, st):
+            r.step(6)
+        for a, b in zip(ref.read_fields(), st.read_fields()):
+            assert _rel(b, a) <= bar
+        a, b = ref.diagnostics(), st.diagnostics()
+        assert a["step"] == b["step"] and a["collisions"] == b["collisions"] and a["ee_pairs"] == b["ee_pairs"]
+        assert np.array_equal(a["n_particles"], b["n_particles"])
+        ref.close()
+        st.close()
