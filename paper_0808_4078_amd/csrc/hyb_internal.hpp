@@ -20,8 +20,13 @@ constexpr int kScanChunk = 2048;      // cells per block of the sort's prefix su
 constexpr int kMaxNodes = 4096;       // nodes per axis
 constexpr int kFftLds = 4096;         // complex values per FFT workgroup (64 KiB of LDS)
 constexpr int kColThreads = 1024;     // threads of a column-transform workgroup at most
-constexpr int kSmallCells = 8192;     // nodes up to which one workgroup does the whole solve
-constexpr int kSmallThreads = kSmallCells / 16;   // its threads: eight elements of half the plane each
+// Nodes up to which one workgroup does the whole solve: its time grows with the
+// nodes, that of the passes' launches hardly.  us per step of 10 sweeps (of 1),
+// one workgroup / passes: 2048 nodes (64x32) 79 / 98 (40 / 32), 4096 (64^2)
+// 98 / 104 (45 / 33), 128x32 113 / 106 (50 / 34), 512x8 98 / 120 (46 / 35), 8192
+// (128x64) 157 / 112 (56 / 35), 8x1024 152 / 145 (70 / 40).
+constexpr int kSmallCells = 4096;
+constexpr int kSmallThreads = 512;    // its threads: half of them take eight elements each in the transforms, all the symbol
 constexpr int kChainSteps = 4;        // steps without a sort that one graph replay enqueues: replays lie 5 us apart
 constexpr int kWaveRounds = 8;        // distinct sort keys merged per wave before plain atomics
 constexpr int kMaxTile = 16;          // tile edge (cells) of the particle kernel

@@ -125,6 +125,22 @@ def test_hybrid_solve_in_one_workgroup(pic, n, iters):
     g.close()
 
 
+@pytest.mark.parametrize("n,iters", [((8, 512), 2), ((512, 8), 3), ((16, 256), 1), ((256, 16), 2), ((128, 32), 3),
+                                     ((32, 128), 2)])
+def test_hybrid_solve_of_4096_nodes(pic, n, iters):
+    """The largest grids of the one-workgroup solve, every number of stages per
+    axis (the passes begin at 8192 nodes, which the cases above hold);
+    tolerances as above."""
+    log(f"case hybrid solve of 4096 nodes {n} iters {iters}")
+    wl = replace(synth.H1, n=n, ppc=3, iters=iters, steps=4, name=f"H1-{n[0]}x{n[1]}")
+    orc, g = _pair(pic, wl, sort_every=2)
+    _compare(orc, g, wl, 1e-11)
+    orc.step(wl.steps)
+    g.step(wl.steps)
+    _compare(orc, g, wl, 1e-9)
+    g.close()
+
+
 def _same_state(r0, r1):
     """Bitwise equality of two runs' potential, canonical momentum and
     particles (by id: the cell sort's order within a cell is free)."""
