@@ -1977,15 +1977,13 @@ int binary_blocks(bool mixed, int64_t tile_cells, int64_t ppc, int *width)
     return (int)nblk;
 }
 
-// one block per species: capacities = count + uniform reserve, exclusive scan
-__device__ __forceinline__ void rebin_scan_body(const KParams *__restrict__ kp, int bid, int nb)
+// one workgroup, species s: capacities = count + uniform reserve, exclusive scan
+__device__ __forceinline__ void rebin_scan_body(const KParams *__restrict__ kp, int s)
 {
     __shared__ int64_t spart[256];
     __shared__ int64_t s_total;
     DevState *st = kp->state;
     if (!st->rebin) return;
-    const int s = bid;
-    if (s >= kp->nspecies) return;
     const SpeciesDev &S = kp->sp[s];
     const int ntiles = kp->g.ntiles;
     const int32_t *cnt = kp->rb_count + (int64_t)s * ntiles;
@@ -2194,7 +2192,7 @@ __device__ __forceinline__ void relayout_count(const KParams *__restrict__ kp, i
     }
     __syncthreads();
     for (int s = 0; s < kp->nspecies; ++s) {
-        rebin_scan_body(kp, s, 0);
+        rebin_scan_body(kp, s);
         __syncthreads();
     }
 }
@@ -2379,10 +2377,10 @@ __device__ __forceinline__ void reduce_j_tile3(const KParams *__restrict__ kp, i
     J[2 * cells + o] = jz;
 }
 
-template <typename R, int D, bool SPLIT>
+template <typename R, int D>
 __device__ __forceinline__ void reduce_j_body(const KParams *__restrict__ kp, int bid)
 {
-    if constexpr (D == 3 && !SPLIT) {
+    if constexpr (D == 3) {
         reduce_j_tile3<R>(kp, bid);
         return;
     }
@@ -2391,9 +2389,9 @@ __device__ __forceinline__ void reduce_j_body(const KParams *__restrict__ kp, in
     const int64_t o = (int64_t)bid * blockDim.x + threadIdx.x;
     if (o >= cells) return;
     const int nx = kp->g.n[0], ny = kp->g.n[1];
-    const int idx[3] = {(int)(o % nx), (int)((o / nx) % ny), D == 3 ? (int)(o / ((int64_t)nx * ny)) : 0};
+    const int idx[3] = {(int)(o % nx), (int)((o / nx) % ny), 0};
     double j[3];
-    node_current<R, D, SPLIT>(kp, idx, j);
+    node_current<R, 2, false>(kp, idx, j);
 #pragma unroll
     for (int c = 0; c < 3; ++c) kp->J[c * cells + o] = j[c];
 }
@@ -2847,8 +2845,13 @@ template <typename R, int D, bool SPLIT, bool DIAG>
 __global__ __launch_bounds__(256) void k_mid(const KParams *__restrict__ kp, int nf, int nr)
 {
     const int b = blockIdx.x;
-    if (b < nf) field_mid<R, D, SPLIT, DIAG>(kp, b);
-    else relayout_count<R, SPLIT>(kp, b - nf, nr);
+    if constexpr (D == 2 || SPLIT) {
+        if (b < nf) {
+            field_mid<R, D, SPLIT, DIAG>(kp, b);
+            return;
+        }
+    }
+    relayout_count<R, SPLIT>(kp, b - nf, nr);
 }
 template <typename R, int D, bool ADV>
 __global__ __launch_bounds__(256) void k_end(const KParams *__restrict__ kp, int nf, int nr, int nfd)
@@ -2893,16 +2896,16 @@ __global__ __launch_bounds__(256) void kb_end(const BatchTable *__restrict__ bt,
     }
 }
 
-template <typename R, int D, bool SPLIT>
+template <typename R, int D>
 __global__ __launch_bounds__(256) void k_reduce_j(const KParams *__restrict__ kp)
 {
-    reduce_j_body<R, D, SPLIT>(kp, D == 3 && !SPLIT ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
+    reduce_j_body<R, D>(kp, D == 3 ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
 }
 template <typename R, int D>
 __global__ __launch_bounds__(256) void kb_reduce_j(const BatchTable *__restrict__ bt)
 {
     const int2 cb = bt->cell_blocks[blockIdx.x];
-    reduce_j_body<R, D, false>(bt->kp[cb.x], cb.y);
+    reduce_j_body<R, D>(bt->kp[cb.x], cb.y);
 }
 template <typename R, int D>
 __global__ __launch_bounds__(256) void k_yee_b(const KParams *__restrict__ kp, double h)
@@ -3208,8 +3211,9 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
     const int nrs = (int)std::min<int64_t>(16384, std::max<int64_t>(std::min<int64_t>(1024, bins), bins / 8));
     const bool apart = hp.binary || gauss || !fused;     // something between the re-layout and the fields
     auto mid = [&](int nf, int nr) {
+        // 3D runs that are not split have no fused passes (nf = 0)
         auto k = hp.split > 1 ? (record ? k_mid<R, D, true, true> : k_mid<R, D, true, false>)
-                              : (record ? k_mid<R, D, false, true> : k_mid<R, D, false, false>);
+                              : (record ? k_mid<R, D, false, D == 2> : k_mid<R, D, false, false>);
         L(k, dim3((unsigned)(nf + nr)), dim3(256), dp, nf, nr);
     };
     if (apart) {
@@ -3234,7 +3238,7 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
     }
     L.grp = 3;
     if (fused) mid((int)cb, apart ? 0 : nrc);
-    else L(hp.split > 1 ? k_reduce_j<R, D, true> : k_reduce_j<R, D, false>, dim3(cb), dim3(256), dp);
+    else L(k_reduce_j<R, D>, dim3(cb), dim3(256), dp);
     if (gauss) {
         L.grp = 0;
         L(k_rho<R, D, T, true>, dim3(ntiles), dim3(256), dp);
