@@ -407,7 +407,7 @@ int check_fatal(pic_run *r, const DevState &st)
     if (st.fatal & 2) { r->err = "particle left the grid (corrupt state)"; return PIC_E_HIP; }
     if (st.fatal & 8) { r->err = "particle outside its tile's bin (corrupt state)"; return PIC_E_HIP; }
     if (st.fatal & 16) {
-        r->err = "binary collisions: a cell holds more than 4096 participants";
+        r->err = "binary collisions: a cell holds more than 2048 participants";
         return PIC_E_CAPACITY;
     }
     return PIC_OK;

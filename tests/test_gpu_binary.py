@@ -111,6 +111,23 @@ def test_binary_capacity_limit_is_reported(pic):
     g.close()
 
 
+def test_binary_limit_in_the_message(pic):
+    """2049 participants in a cell are one too many, and the message says so."""
+    log("case binary collisions limit")
+    wl = synth.beam_plasma((8, 8), ppc=33, u_th_beam=0.0, u_th_plasma=0.0, nu_ee=1.0, ee_vref=0.1,
+                           binary=(False, True), steps=1)
+    parts = synth.load(wl)
+    parts[1].x[:] = 1.1
+    parts[1].x[:, :2049] = 0.05
+    parts[1].u[:] = 0.0
+    g = gpu_run(wl, parts, pic.PIC_PREC_FP64)
+    g.step(1)
+    with pytest.raises(pic.PicError, match="more than 2048") as e:
+        g.sync()
+    assert e.value.code == pic.PIC_E_CAPACITY
+    g.close()
+
+
 @pytest.mark.parametrize("prec,bar", [("fp64", 1e-11), ("mixed", 1e-3)])
 @pytest.mark.parametrize("tile", [8, 16, 32])
 def test_binary_crowded_cells(pic, tile, prec, bar):
