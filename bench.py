@@ -27,7 +27,8 @@ if ROOT not in sys.path:
 
 METRIC = "particle-steps/s (gather+push+deposit), mixed-FP32 vs FP64, 2D 1024^2 64 ppc"
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCES = ("paper_0808_4078_amd/csrc/pic_kernels.hip", "paper_0808_4078_amd/csrc/pic_internal.hpp")
+KERNEL_SOURCES = ("paper_0808_4078_amd/csrc/pic_kernels.hip", "paper_0808_4078_amd/csrc/pic_internal.hpp",
+                  "paper_0808_4078_amd/csrc/pic_relayout.hpp")
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_particle_c3_hbm_traffic.txt")
 
 

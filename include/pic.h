@@ -81,6 +81,8 @@ enum {
  * ones issued before the current one is processed).
  *   0: 256 / 2 (default; the only shape of FP64 runs)   1: 256 / 1
  *   2: 256 / 3   3: 512 / 2   4: 128 / 2
+ * (FP64 runs in 3D: 512 threads.)  In shape 0 a grid with few tiles has several
+ * workgroups per tile.
  * The shape changes how the work is spread over the device, never the
  * arithmetic; pic_tune_shape times them. */
 #define PIC_PARTICLE_SHAPES 5
@@ -305,7 +307,8 @@ int pic_sync(pic_run *run);
  *   graph_launches  steps enqueued by graph replays.
  *   direct_steps    steps enqueued kernel by kernel (including the
  *                   measurement path pic_step_profiled).
- *   scratch_bytes   scratch the run uses (pic_query's scratch_bytes).
+ *   scratch_bytes   scratch the run uses (pic_query's scratch_bytes, or less on
+ *                   the library's scratch).
  *   shape, block_threads, inflight  the particle kernel's launch shape and
  *                   its threads per workgroup and particles in flight per
  *                   lane. */
@@ -344,15 +347,16 @@ int pic_write_fields(pic_run *run, const double *E, const double *B);
 
 /* Synchronising.  Copies species s out: x FP64 [ndim][cap] in c/w_p, u FP64
  * [3][cap], id [cap]; *count receives the particle number (PIC_E_BUFFER_TOO_SMALL
- * if it exceeds cap).  Order is the store's order, not id order. */
+ * if it exceeds cap).  Order is the store's order, not id order.  The particles
+ * are packed in the half of the store that the next step will overwrite. */
 int pic_read_particles(pic_run *run, int species, double *x, double *u, uint32_t *id,
                        int64_t cap, int64_t *count);
 
 /* Synchronising.  Writes the run's complete state -- particle store, fields,
  * current, scratch (step counter, parity, work order), diagnostic ring --
  * with its descriptors to the file `path` (overwritten).  The file holds the
- * raw buffers (sizes as pic_query gives), so it is as large as the device
- * state.  Errors: INVALID_ARG (null argument, file not writable),
+ * raw buffers (sizes as pic_query gives; of the scratch the part that outlives
+ * a step), so it is as large as the device state.  Errors: INVALID_ARG (null argument, file not writable),
  * CAPACITY / HIP (as pic_sync). */
 int pic_checkpoint(pic_run *run, const char *path);
 
@@ -496,8 +500,8 @@ int pic_batch_destroy(pic_batch *batch);
  * 16, 32; -1 where not tried).  grid->tile and PIC_FLAG_HOST_LOAD are
  * ignored; every candidate runs in grid->shape.  Synchronising, on
  * `hip_stream`; the workspace may be reused once it returns.
- * pic_tune_query (host only) gives the workspace size, which also serves
- * pic_tune_shape.  Errors: INVALID_ARG (copies out of 1..4096, no edge
+ * pic_tune_query (host only) gives the workspace size, which does not depend on
+ * grid->shape and also serves pic_tune_shape.  Errors: INVALID_ARG (copies out of 1..4096, no edge
  * divides the grid, nsteps < 1), BUFFER_TOO_SMALL, and those of pic_init. */
 int pic_tune_query(const pic_grid_desc *grid, const pic_species_desc *species, int nspecies,
                    int32_t copies, size_t *workspace_bytes);

@@ -82,8 +82,11 @@ struct Carver {
 };
 
 // Workgroups per particle tile: about 1024 in all (4 per CU) on a grid with few
-// tiles, each with at least 512 particles (64^2, 16 tiles, 16 particles per
-// cell: particle kernel 53 -> 17 us).
+// tiles, each with at least 512 particles.  us per step of two sweeps, workgroups
+// per tile (the rule's in brackets): 64^2, 16 tiles, 16 per cell 1: 86  [8]: 51
+// 16: 46  64: 50; 128^2, 64 tiles, 4 per cell 1: 52  [2]: 46  4: 41  8: 42;
+// 256^2, 256 tiles, 16 per cell 1: 96  2: 85  [4]: 91  8: 97; 512^2, 1024 tiles, 8
+// per cell [1]: 124  2: 133.
 int particle_parts(int64_t ntiles, int64_t np)
 {
     return (int)std::max<int64_t>(1, std::min<int64_t>(1024 / ntiles, np / ntiles / 512));

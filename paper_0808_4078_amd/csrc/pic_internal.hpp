@@ -197,8 +197,11 @@ struct BatchTable {
 // for twice the nodes; four cost 60 us more when the run is made.
 constexpr int kChainSteps = 4;
 // Cells up to which a 2D run, or an ensemble in all, takes the fused field
-// passes: their second set of planes doubles what the passes hold in the
-// last-level cache.  ms per step, one by one / fused, ensembles of 1.1M cells
+// passes.  On larger grids they lose what they save: mostly to the registers
+// that the re-layout's copies give the second pass (three or four waves per
+// SIMD; with the copies in a launch of their own 4096^2 takes 1.478 ms fused,
+// 1.476 one by one, 1.665 with them, 2048^2 0.654, 0.637, 0.679), which small
+// grids pay for with a launch less (512^2: 0.060 against 0.066).  ms per step, one by one / fused, ensembles of 1.1M cells
 // 1.103 / 1.100, 2.2M 2.384 / 2.382, 4.6M 4.72 / 4.79, 21M 20.40 / 20.87; runs of
 // 1M cells 0.515 / 0.493, 2.1M 1.160 / 1.150, 4.2M 1.795 / 1.807, 17M 2.69 / 2.78.
 constexpr int64_t kFusedCells = 1ll << 21;

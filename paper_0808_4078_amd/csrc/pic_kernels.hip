@@ -1587,9 +1587,12 @@ __device__ bool binary_pair(R (&ua)[3], R ma, R wa, uint32_t ida, R (&ub)[3], R 
 //   threads per CU in FP32, one of 1024 in FP64 (160 KB of LDS per CU)
 // Measured on 1024^2 cells x 128 participants in mixed precision (67M pairs a
 // step): 11.9 -> 4.2 ms, and 0.4 ms for the list (floor of its bytes: 1.1 ms).
-// What bounds it now: VALU issue about 60% of the time (trigonometry,
-// divisions and the Philox rounds of the pairs), then the waits at the
-// barriers between the phases.  Tried and left out: every block scanning the
+// What bounds it now: VALU issue, 61% of the CUs' busy cycles (trigonometry,
+// divisions and the Philox rounds of the pairs; the LDS 20%), and with two
+// workgroups per CU the barriers between the phases; not the words used per
+// line: half or twice as many entries per workgroup, and so words per line,
+// took 4.18 and 5.06 ms.  FP64 is held to 128 VGPRs (36 bytes of scratch per
+// lane) and gains as much: 1024^2 x 128, whole step, 23.9 -> 12.5 ms.  Tried and left out: every block scanning the
 // whole tile's cells instead of the list (7.3 ms, half of it the scan), the
 // three pairs of a triple done by one lane at once (a third more).
 constexpr int kBinLimit = 2048;                     // participants of one cell
@@ -2257,7 +2260,8 @@ __device__ __forceinline__ int node_tiles(int i, int T, int nt, int (&ct)[2], in
 // order.  SPLIT: the `parts` FP64 partials of a tile lie one after the other;
 // they are summed in order and rounded to the run's precision, as a tile that
 // is not split rounds its LDS sums: in mixed precision, where the FP64 sums of
-// FP32 terms are exact, the current does not depend on the split.
+// FP32 terms are nearly always exact (as long as their exponents lie within
+// about 29 bits), the current nearly never depends on the split.
 template <typename R, int D, bool SPLIT>
 __device__ __forceinline__ void node_current(const KParams *__restrict__ kp, const int (&idx)[3], double (&j)[3])
 {
@@ -3188,7 +3192,7 @@ static hipError_t step_kernels(const KParams &hp, const KParams *dp, Launcher &L
     }
     // Field passes: fused where the run has room for the second set of planes;
     // the field record joins the first of them where its per-workgroup
-    // partials fit the table.
+    // partials fit the table (512: grids of up to 131072 cells).
     const bool fused = hp.Ft != nullptr;
     const bool record = fused && cb <= (unsigned)kFieldDiagBlocks;
     const int nfd = record ? (int)cb : hp.fd_blocks;

@@ -87,11 +87,17 @@ int fail(std::string *err, int code, const char *fmt, ...)
 // Workgroups per tile of the particle kernel.  A grid with few tiles leaves
 // most of the 256 CUs idle, and a heavy tile then finishes long after the
 // others, so its tiles are split into about kSplitGroups workgroups (4 per CU),
-// as long as each has kSplitMin particles.  Measured, particle kernel alone, 1
-// workgroup per tile -> the rule's: 64^2, 16 tiles, 16 + 16 particles per cell
-// 58 -> 16 us (16 per tile); 256^2, 256 tiles, 64 + 64 217 -> 132 us (4);
-// 160^2, 400 tiles, 64 + 64 79 -> 69 us (2).  From 1024 tiles on the split
-// only adds field stages and partial currents (512^2: 422 us unsplit).
+// as long as each has kSplitMin particles.  us per step, workgroups per tile
+// (the rule's in brackets), mixed precision unless named:
+//   64^2, 16 + 16 per cell, FP64, 16 tiles   1: 78   8: 33  [16]: 34   32: 41
+//   64^2, 4 + 4, 16 tiles (kSplitMin)        1: 32  [4]: 27  5: 25  8: 26  16: 30
+//   256^2, 64 + 64, 256 tiles                1: 229  3: 156  [4]: 146  8: 156
+//   160^2, 64 + 64, 400 tiles of 8^2         1: 85  [2]: 77  3: 81  5: 76  8: 89
+//   200^2, 64 + 64, 625 tiles of 8^2        [1]: 102  2: 107  3: 101  5: 113
+//   240^2, 64 + 64, 900 tiles of 8^2        [1]: 128  2: 141  3: 148
+// Whole rounds of the CUs at the kernel's residency do better than a fixed
+// number of workgroups where few fit a CU (32^3 FP64, 64 tiles, one per CU:
+// 1: 167  4: 59  [12]: 94; 320^2, 400 tiles of 16^2: [2]: 238  5: 213).
 int particle_split(const pic_grid_desc *g, const Geometry &G, int64_t per_tile)
 {
     if (g->shape != 0) return 1;                             // a shape chosen by the caller is launched as it is
