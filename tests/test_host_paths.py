@@ -19,13 +19,14 @@ def stub(tmp_path_factory):
     return str(so)
 
 
-def run(stub, body, *args):
+def run(stub, body):
     """Runs `body` (with pic, synth, C, L = the library, S = the stub, BASE = a
     device address) under the stub; returns what it prints."""
     code = ("import ctypes as C, sys\nimport synth\nfrom paper_0808_4078_amd import pic\n"
             f"L = pic.lib()\nS = C.CDLL({stub!r})\nBASE = 1 << 45\n" + body)
-    p = subprocess.run([sys.executable, "-c", code, *map(str, args)], cwd=ROOT, capture_output=True, text=True,
-                       env={**os.environ, "LD_PRELOAD": stub}, timeout=300)
+    preload = ":".join([stub] + [v for v in [os.environ.get("LD_PRELOAD")] if v])
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True,
+                       env={**os.environ, "LD_PRELOAD": preload}, timeout=300)
     assert p.returncode == 0, p.stderr
     return p.stdout.split()
 
